@@ -694,113 +694,200 @@ __global__ __launch_bounds__(64 * ATT_PRE_MAX_WAVES) void k_attention_prefix(con
 // of a sequence in one launch).  Workgroup (tile, kv head): the tile's rows
 // tile_r0[k] .. +tile_nr[k]-1 hold consecutive positions of one page table
 // row; its nr x rep query rows (row i = tile row i / rep, GQA head i % rep)
-// are scored 16 per wave against each 32-token block of K and V^T, staged
-// once in LDS for all waves (double buffered, as in the prefix pass).  Query
-// row i sees tokens 0 .. row_pos of its row (causal mask per column).  The
-// whole context is one work item, so the normalised output goes straight to
-// the activation planes.
-constexpr int ATT_TILE_MAX_WAVES = 12;
-
-// Positions per row tile: 32 while the tile's query rows (positions x GQA
-// heads) fit ATT_TILE_MAX_WAVES waves of 16, else 16.
-int att_tile_rows_for(int rep) { return 32 * rep <= 16 * ATT_TILE_MAX_WAVES ? 32 : 16; }
+// are scored 32 per wave against each 32-token block of K and V^T, staged
+// once in LDS for the four waves (double buffered, as in the prefix pass).
+// Query row i sees tokens 0 .. row_pos of its row (causal mask per column).
+// The whole context is one work item, so the normalised output goes straight
+// to the activation planes.
+//
+// 32 query rows a wave (two column groups): each K and V^T fragment read from
+// LDS feeds four MFMAs (two groups, hi and lo planes), 64 MFMAs per 16
+// fragment reads.  With 16 rows a wave the four SIMDs' fragment reads took as
+// many LDS cycles as their MFMAs.  Four waves and at most 256 registers keep
+// two workgroups on a CU, so one's softmax runs beside the other's MFMAs.
+constexpr int ATT_TILE_WAVES = 4;
+constexpr int ATT_TILE_QROWS = 32 * ATT_TILE_WAVES;   // query rows (positions x GQA heads) per workgroup
 
 template <int HD>
-__global__ __launch_bounds__(64 * ATT_TILE_MAX_WAVES) void k_attention_tile(
+__global__ __launch_bounds__(64 * ATT_TILE_WAVES, 2) void k_attention_tile(
     const float* __restrict__ q, int n_q, int n_kv, const bf16_t* __restrict__ pool, KvGeom g, int layer,
     const int32_t* __restrict__ page_tab, int tab_stride, const int32_t* __restrict__ row_tab,
     const int32_t* __restrict__ row_pos, const int32_t* __restrict__ tile_r0, const int32_t* __restrict__ tile_nr,
     const int* __restrict__ d_tiles, ActOut out) {
   constexpr int KROW = KvStage<HD>::KROW, VROW = KvStage<HD>::VROW;
+  constexpr int QT = 2, NTHR = 64 * ATT_TILE_WAVES;
   __shared__ __attribute__((aligned(16))) bf16_t sKV[2][KvStage<HD>::BUF];
   __shared__ int spg[ATT_MAX_CHUNK_PAGES];
 
-  // XCD-aware order: consecutive tiles (one sequence's rows) share an XCD
-  const int64_t b = blockIdx.x;
-  const int64_t per_xcd = (int64_t)gridDim.x / 8;
-  const int64_t w = (b % 8) * per_xcd + b / 8;
-  const int k = (int)(w / n_kv), kvh = (int)(w % n_kv);
-  if (k >= *d_tiles) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nthr = blockDim.x;
+  // Blocks are dealt to the 8 XCDs in turn.  Where the kv heads divide them,
+  // an XCD keeps to one kv head (its L2 then holds that head's K and V only).
+  // Tiles go last first: within a sequence the longest contexts start first,
+  // and neighbouring tiles run on all XCDs at once, so one long sequence
+  // spreads evenly.
+  const int b = (int)blockIdx.x;
+  int k, kvh;
+  if (8 % n_kv == 0) {
+    kvh = (b & 7) % n_kv;
+    k = (b >> 3) * (8 / n_kv) + (b & 7) / n_kv;
+  } else {
+    kvh = b % n_kv;
+    k = b / n_kv;
+  }
+  const int nt = *d_tiles;
+  if (k >= nt) return;
+  k = nt - 1 - k;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rep = n_q / n_kv;
   const int r0 = tile_r0[k], nr = tile_nr[k];
   const int nrows = nr * rep;
   const int c1 = row_pos[r0 + nr - 1] + 1;      // the tile's last row sees the longest context
   const int col = lane & 15, grp = lane >> 4;
-  const bool active = wave * 16 < nrows;
-  const int qi = wave * 16 + col;
-  const bool qv = qi < nrows;
-  const int row = r0 + (qv ? qi / rep : 0), head = kvh * rep + (qv ? qi % rep : 0);
-  const int climit = row_pos[row] + 1;
-
-  kv_stage_pages(spg, page_tab + (int64_t)row_tab[r0] * tab_stride, 0, c1, tid, nthr);
-  bf16x8_t qh[HD / 32], ql[HD / 32];
-  att_load_q<HD>(q + ((int64_t)row * n_q + head) * HD, qv, grp, qh, ql);
+  const bool active = wave * 32 < nrows;
+  int row[QT], head[QT], climit[QT];
+  bool qv[QT];
+  bf16x8_t qh[QT][HD / 32], ql[QT][HD / 32];
+  kv_stage_pages(spg, page_tab + (int64_t)row_tab[r0] * tab_stride, 0, c1, tid, NTHR);
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+    const int qi = wave * 32 + t * 16 + col;
+    qv[t] = qi < nrows;
+    row[t] = r0 + (qv[t] ? qi / rep : 0);
+    head[t] = kvh * rep + (qv[t] ? qi % rep : 0);
+    climit[t] = row_pos[row[t]] + 1;
+    att_load_q<HD>(q + ((int64_t)row[t] * n_q + head[t]) * HD, qv[t], grp, qh[t], ql[t]);
+  }
   __syncthreads();   // page ids
   const int64_t koff = (int64_t)layer * g.layer_stride + (int64_t)kvh * 16 * HD;
   const int64_t voff = (int64_t)layer * g.layer_stride + ((int64_t)n_kv + kvh) * 16 * HD;
 
   KvStagePlan<HD> pl;
-  kv_stage_plan<HD>(pl, koff, voff, tid, nthr);
-  u32x4_t rg[KvStage<HD>::MAXP];
-  auto fetch = [&](int t0) { kv_stage_fetch<HD>(rg, pl, pool, g.page_stride, spg, 0, t0); };
-  auto stash = [&](int buf) { kv_stage_stash<HD>(rg, pl, sKV[buf]); };
-
-  AttState<HD> st;
-  st.m = -INFINITY;
-  st.l = 0.f;
-#pragma unroll
-  for (int i = 0; i < HD / 16; ++i) st.o[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  kv_stage_plan<HD>(pl, koff, voff, tid, NTHR);
   // two register sets in turn keep the next two blocks' loads in flight
   // while one block is multiplied out of LDS
-  u32x4_t rg2[KvStage<HD>::MAXP];
-  auto fetch2 = [&](int t0) { kv_stage_fetch<HD>(rg2, pl, pool, g.page_stride, spg, 0, t0); };
-  auto stash2 = [&](int buf) { kv_stage_stash<HD>(rg2, pl, sKV[buf]); };
+  u32x4_t rg[2][KvStage<HD>::MAXP];
+
+  // Softmax state: m (log2 units) lags the true max by up to ATT_SLACK, as in
+  // att_update; l holds the lane's own tokens only and is summed over the
+  // four lane groups at the end.  The score accumulators start at -m, so they
+  // come out relative to m.
+  float m[QT], l[QT];
+  f32x4_t o[QT][HD / 16];
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+    m[t] = 0.f;
+    l[t] = 0.f;
+#pragma unroll
+    for (int i = 0; i < HD / 16; ++i) o[t][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  }
   auto block = [&](int buf, int t0) {
     if (!active) return;
-    f32x4_t s[2];
+    f32x4_t s[QT][2];
+#pragma unroll
+    for (int t = 0; t < QT; ++t)
+#pragma unroll
+      for (int tt = 0; tt < 2; ++tt) s[t][tt] = f32x4_t{-m[t], -m[t], -m[t], -m[t]};
     const bf16_t* kb0 = &sKV[buf][col * KROW + 8 * grp];
-    att_scores<HD>(s, qh, ql, [&](int tt, int kb) {
-      return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(kb0 + 16 * tt * KROW + kb * 32));
-    });
-    if (t0 + 32 > climit) {                      // causal mask of this column (token 0 is always visible)
+#pragma unroll
+    for (int kb = 0; kb < HD / 32; ++kb)
+#pragma unroll
+      for (int tt = 0; tt < 2; ++tt) {
+        const bf16x8_t kf =
+            __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(kb0 + 16 * tt * KROW + kb * 32));
+#pragma unroll
+        for (int t = 0; t < QT; ++t) s[t][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qh[t][kb], s[t][tt], 0, 0, 0);
+#pragma unroll
+        for (int t = 0; t < QT; ++t) s[t][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, ql[t][kb], s[t][tt], 0, 0, 0);
+      }
+    bf16x8_t ph[QT], plo[QT];
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+      if (t0 + 32 > climit[t]) {                 // causal mask of this column (token 0 is always visible)
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (t0 + 8 * grp + 4 * tt + j >= climit[t]) s[t][tt][j] = -INFINITY;
+      }
+      float mloc = fmaxf(fmaxf(fmaxf(s[t][0][0], s[t][0][1]), fmaxf(s[t][0][2], s[t][0][3])),
+                         fmaxf(fmaxf(s[t][1][0], s[t][1][1]), fmaxf(s[t][1][2], s[t][1][3])));
+      if (t0 == 0 || __any(mloc > ATT_SLACK)) {
+        mloc = fmaxf(mloc, __shfl_xor(mloc, 16, 64));
+        mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
+        const float d = t0 == 0 ? mloc : fmaxf(mloc, 0.f);
+        const float alpha = __builtin_amdgcn_exp2f(-d);   // multiplies zeros on the first block
+        if (t0 != 0) {
+          l[t] *= alpha;
+#pragma unroll
+          for (int i = 0; i < HD / 16; ++i) o[t][i] *= alpha;
+        }
+        m[t] += d;
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt) s[t][tt] -= d;
+      }
+      float p[8];
 #pragma unroll
       for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (t0 + 8 * grp + 4 * tt + j >= climit) s[tt][j] = -INFINITY;
+        for (int j = 0; j < 4; ++j) {
+          const float e = __builtin_amdgcn_exp2f(s[t][tt][j]);   // exp2(-inf) = 0 for masked tokens
+          p[tt * 4 + j] = e;
+          l[t] += e;
+        }
+      split8(p, ph[t], plo[t]);
     }
     const bf16_t* vb0 = &sKV[buf][KvStage<HD>::VBASE + col * VROW + 8 * grp];
-    att_update<HD>(st, s, t0 + 32 > c1, min(8, max(0, c1 - (t0 + 8 * grp))),
-                   [&](int dt) { return *reinterpret_cast<const u32x4_t*>(vb0 + dt * 16 * VROW); });
-  };
-  fetch(0);
-  if (32 < c1) fetch2(32);
-  for (int t0 = 0; t0 < c1; t0 += 64) {
-    stash(0);
-    __syncthreads();                             // block t0 in buffer 0; buffer 1 is free
-    if (t0 + 64 < c1) fetch(t0 + 64);
-    block(0, t0);
-    if (t0 + 32 >= c1) break;
-    stash2(1);
-    __syncthreads();                             // block t0 + 32 in buffer 1; buffer 0 is free
-    if (t0 + 96 < c1) fetch2(t0 + 96);
-    block(1, t0 + 32);
-  }
-  if (active && qv) {
-    const float inv = 1.0f / st.l;
-    bf16_t* o = (bf16_t*)out.base + ((int64_t)row * n_q + head) * HD + 4 * grp;
+    const bool tail = t0 + 32 > c1;
+    const int nval = min(8, max(0, c1 - (t0 + 8 * grp)));
 #pragma unroll
     for (int dt = 0; dt < HD / 16; ++dt) {
-      uint32_t h[2], l[2];
+      u32x4_t vv = *reinterpret_cast<const u32x4_t*>(vb0 + dt * 16 * VROW);
+      if (tail) {   // zero the slots of masked tokens (their memory may hold anything)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int n2 = nval - 2 * e;   // valid tokens in this dword
+          vv[e] = n2 >= 2 ? vv[e] : (n2 == 1 ? (vv[e] & 0xFFFFu) : 0u);
+        }
+      }
+      const bf16x8_t v8 = __builtin_bit_cast(bf16x8_t, vv);
+#pragma unroll
+      for (int t = 0; t < QT; ++t) o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v8, ph[t], o[t][dt], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < QT; ++t) o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v8, plo[t], o[t][dt], 0, 0, 0);
+    }
+  };
+  auto fetch = [&](int set, int t0) { kv_stage_fetch<HD>(rg[set], pl, pool, g.page_stride, spg, 0, t0); };
+  fetch(0, 0);
+  if (32 < c1) fetch(1, 32);
+  for (int t0 = 0; t0 < c1; t0 += 64) {
+    kv_stage_stash<HD>(rg[0], pl, sKV[0]);
+    __syncthreads();                             // block t0 in buffer 0; buffer 1 is free
+    if (t0 + 64 < c1) fetch(0, t0 + 64);
+    block(0, t0);
+    if (t0 + 32 >= c1) break;
+    kv_stage_stash<HD>(rg[1], pl, sKV[1]);
+    __syncthreads();                             // block t0 + 32 in buffer 1; buffer 0 is free
+    if (t0 + 96 < c1) fetch(1, t0 + 96);
+    block(1, t0 + 32);
+  }
+  if (!active) return;
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+    l[t] += __shfl_xor(l[t], 16, 64);
+    l[t] += __shfl_xor(l[t], 32, 64);
+    if (!qv[t]) continue;
+    const float inv = 1.0f / l[t];
+    bf16_t* po = (bf16_t*)out.base + ((int64_t)row[t] * n_q + head[t]) * HD + 4 * grp;
+#pragma unroll
+    for (int dt = 0; dt < HD / 16; ++dt) {
+      uint32_t h[2], lw[2];
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
-        const float v0 = st.o[dt][2 * e] * inv, v1 = st.o[dt][2 * e + 1] * inv;
+        const float v0 = o[t][dt][2 * e] * inv, v1 = o[t][dt][2 * e + 1] * inv;
         h[e] = pack_bf16x2(v0, v1);
-        l[e] = pack_bf16x2(v0 - __uint_as_float(h[e] << 16), v1 - __uint_as_float(h[e] & 0xFFFF0000u));
+        lw[e] = pack_bf16x2(v0 - __uint_as_float(h[e] << 16), v1 - __uint_as_float(h[e] & 0xFFFF0000u));
       }
-      *reinterpret_cast<uint2*>(o + dt * 16) = uint2{h[0], h[1]};
-      *reinterpret_cast<uint2*>(o + out.plane + dt * 16) = uint2{l[0], l[1]};
+      *reinterpret_cast<uint2*>(po + dt * 16) = uint2{h[0], h[1]};
+      *reinterpret_cast<uint2*>(po + out.plane + dt * 16) = uint2{lw[0], lw[1]};
     }
   }
 }
@@ -961,24 +1048,23 @@ hipError_t launch_attention_tile(const float* q, int n_q, int n_kv, int head_dim
                                  hipStream_t st) {
   if (tiles_ub <= 0) return hipSuccess;
   const int rep = n_q / n_kv;
-  const int rows = att_tile_rows_for(rep);
-  if (rows * rep > 16 * ATT_TILE_MAX_WAVES || max_ctx > 16 * ATT_MAX_CHUNK_PAGES) return hipErrorInvalidValue;
-  const int waves = std::max(4, (rows * rep + 15) / 16);
+  if (rep > ATT_TILE_QROWS || max_ctx > 16 * ATT_MAX_CHUNK_PAGES) return hipErrorInvalidValue;
   const int64_t items = (int64_t)tiles_ub * n_kv;
   const unsigned blocks = (unsigned)((items + 7) / 8 * 8);
   const ActOut o{out, a_plane};
   if (head_dim == 128)
-    att_launch(k_attention_tile<128>, dim3(blocks), dim3(64 * waves), st, q, n_q, n_kv, (const bf16_t*)kv_pool, g,
-               layer, page_tab, tab_stride, row_tab, row_pos, tile_r0, tile_nr, d_tiles, o);
+    att_launch(k_attention_tile<128>, dim3(blocks), dim3(64 * ATT_TILE_WAVES), st, q, n_q, n_kv, (const bf16_t*)kv_pool,
+               g, layer, page_tab, tab_stride, row_tab, row_pos, tile_r0, tile_nr, d_tiles, o);
   else if (head_dim == 64)
-    att_launch(k_attention_tile<64>, dim3(blocks), dim3(64 * waves), st, q, n_q, n_kv, (const bf16_t*)kv_pool, g,
-               layer, page_tab, tab_stride, row_tab, row_pos, tile_r0, tile_nr, d_tiles, o);
+    att_launch(k_attention_tile<64>, dim3(blocks), dim3(64 * ATT_TILE_WAVES), st, q, n_q, n_kv, (const bf16_t*)kv_pool,
+               g, layer, page_tab, tab_stride, row_tab, row_pos, tile_r0, tile_nr, d_tiles, o);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-int att_tile_rows(int n_q, int n_kv) { return att_tile_rows_for(n_q / n_kv); }
+// Positions per row tile: as many as the workgroup's query rows hold.
+int att_tile_rows(int n_q, int n_kv) { return ATT_TILE_QROWS / (n_q / n_kv); }
 
 // About ATT_ITEMS_TARGET work items (fewer, longer chunks measured faster than
 // filling every wave slot: less partial traffic and per-item set-up), at least

@@ -106,35 +106,46 @@ __global__ __launch_bounds__(256) void k_recompute_rows(RecomputeRows a, const T
   for (int i = threadIdx.x; i < a.d; i += blockDim.x) a.x[(int64_t)r * a.d + i] = ld_f32<T>(e + i);
 }
 
-// Tiles of the chunk's rows for the row-tile attention: each sequence's rows
-// in the chunk, cut into runs of tr from its first row.  One block of 1024
-// threads; tile k starts at row tile_r0[k] and has tile_nr[k] rows, in row
-// order; *d_tiles gets the count.
-__global__ __launch_bounds__(1024) void k_row_tiles(const int32_t* __restrict__ row_tab,
-                                                    const int32_t* __restrict__ coff, int row0, int n, int tr,
+// Tiles of a run of prefill-style rows for the row-tile attention: sequence
+// s holds rows coff[s] - row0 .. coff[s + 1] - row0 - 1, clipped to the run's
+// n = min(n_ub, *d_rows) rows and cut into pieces of tr from its first row.
+// One block of 1024 threads: a thread per sequence counts its tiles, a scan
+// places them, then a wave per sequence writes them.  Tile k starts at row
+// tile_r0[k] and has tile_nr[k] rows, in row order; *d_tiles gets the count.
+__global__ __launch_bounds__(1024) void k_row_tiles(const int32_t* __restrict__ coff, int n_seq, int row0, int n_ub,
+                                                    int tr, const int* __restrict__ d_rows,
                                                     int32_t* __restrict__ tile_r0, int32_t* __restrict__ tile_nr,
                                                     int* __restrict__ d_tiles) {
   __shared__ int lds[17];
+  __shared__ int s_o[1024], s_f[1024], s_e[1024];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
+  const int n = min(n_ub, *d_rows);
   int carry = 0;
-  for (int base = 0; base < n; base += blockDim.x) {
-    const int r = base + threadIdx.x;
-    int flag = 0, len = 0;
-    if (r < n) {
-      const int s = row_tab[r];
-      const int f = max(coff[s] - row0, 0);         // the sequence's first row in this chunk
-      const int e = min(coff[s + 1] - row0, n);     // one past its last
-      flag = (r - f) % tr == 0;
-      len = min(tr, e - r);
+  for (int base = 0; base < n_seq; base += blockDim.x) {
+    const int s = base + tid;
+    int f = 0, e = 0;
+    if (s < n_seq) {
+      f = max(coff[s] - row0, 0);
+      e = min(coff[s + 1] - row0, n);
     }
     int tot;
-    const int o = block_excl_scan(flag, lds, &tot) + carry;
-    if (flag) {
-      tile_r0[o] = r;
-      tile_nr[o] = len;
+    const int o = block_excl_scan(e > f ? (e - f + tr - 1) / tr : 0, lds, &tot) + carry;
+    s_o[tid] = o;
+    s_f[tid] = f;
+    s_e[tid] = e;
+    __syncthreads();
+    const int ns = min((int)blockDim.x, n_seq - base);
+    for (int k = wave; k < ns; k += nw) {
+      const int f0 = s_f[k], e0 = s_e[k], o0 = s_o[k];
+      for (int j = lane; f0 + j * tr < e0; j += 64) {
+        tile_r0[o0 + j] = f0 + j * tr;
+        tile_nr[o0 + j] = min(tr, e0 - (f0 + j * tr));
+      }
     }
     carry += tot;
+    __syncthreads();
   }
-  if (threadIdx.x == 0) *d_tiles = carry;
+  if (tid == 0) *d_tiles = carry;
 }
 
 // Step 0 of every sequence: its prompt's last-position logits (row seq_grp[s])
@@ -315,10 +326,10 @@ hipError_t launch_recompute_rows(int dtype, const void* embed, const RecomputeRo
   return hipGetLastError();
 }
 
-hipError_t launch_row_tiles(const int32_t* row_tab, const int32_t* coff, int row0, int n, int tile_rows,
+hipError_t launch_row_tiles(const int32_t* coff, int n_seq, int row0, int n, int tile_rows, const int* d_rows,
                             int32_t* tile_r0, int32_t* tile_nr, int* d_tiles, hipStream_t st) {
-  hipLaunchKernelGGL(k_row_tiles, dim3(1), dim3(1024), 0, st, row_tab, coff, row0, n, tile_rows, tile_r0, tile_nr,
-                     d_tiles);
+  hipLaunchKernelGGL(k_row_tiles, dim3(1), dim3(1024), 0, st, coff, n_seq, row0, n, tile_rows, d_rows, tile_r0,
+                     tile_nr, d_tiles);
   return hipGetLastError();
 }
 

@@ -270,10 +270,10 @@ struct RecomputeRows {
   float* x; int32_t* bad_token;
 };
 hipError_t launch_recompute_rows(int dtype, const void* embed, const RecomputeRows& a, int rows, hipStream_t st);
-// Cuts rows 0..n-1 of a recompute chunk (row_tab = sequence, coff = row
-// offsets, row0 = the chunk's first global row) into per-sequence tiles of at
-// most 16 rows for the row-tile attention.
-hipError_t launch_row_tiles(const int32_t* row_tab, const int32_t* coff, int row0, int n, int tile_rows,
+// Cuts rows 0..min(n, *d_rows)-1 of prefill-style rows (sequence s < n_seq
+// holds rows coff[s] - row0 .. coff[s + 1] - row0 - 1) into per-sequence
+// tiles of at most tile_rows rows for the row-tile attention.
+hipError_t launch_row_tiles(const int32_t* coff, int n_seq, int row0, int n, int tile_rows, const int* d_rows,
                             int32_t* tile_r0, int32_t* tile_nr, int* d_tiles, hipStream_t st);
 // Positions per row tile the row-tile attention takes for this GQA shape.
 int att_tile_rows(int n_q, int n_kv);
