@@ -274,8 +274,7 @@ int gemm(rg_policy* pol, hipStream_t st, int kind, const void* A, int K, const v
   if (splits_out) *splits_out = S;
   ep.part = pol->cpart;
   ep.part_stride = (int64_t)rows_ub * N;
-  const bool needs_part = S > 1 || pol->dtype != RG_DTYPE_BF16;
-  if (needs_part && ep.part_stride * S > pol->cpart_elems) return fail(RG_ENOMEM, "GEMM workspace too small");
+  if (S > 1 && ep.part_stride * S > pol->cpart_elems) return fail(RG_ENOMEM, "GEMM workspace too small");
   LAUNCH(kind, launch_gemm(pol->dtype, A, K, pol->a_plane, W, K, d_rows, rows_ub, N, K, S, kps, ep, st));
   return RG_OK;
 }
@@ -352,8 +351,8 @@ int run_layers(rg_policy* pol, hipStream_t st, const int* d_rows, int rows_ub, i
     LAUNCH_TIMED(RG_K_ATTN, launch_attention(pol->dtype, pol->qbuf, pol->nq, pol->nkv, pol->hd, pol->kv_pool, pol->geom, l,
                                        pol->page_tab, tab_stride, pol->row_tab, pol->row_pos, pol->row_beg, ctx_max,
                                        plan, pol->att_o, pol->att_ml, pol->abuf2, pol->a_plane, d_rows, rows_ub, st));
-    // one bf16 slot, or chunks merged inside the attention kernel: it wrote abuf2 itself
-    if ((plan.n_slots > 1 && !att_merges_in_kernel(pol->dtype, plan, rows_ub, pol->nkv)) || pol->dtype != RG_DTYPE_BF16)
+    // one slot, or chunks merged inside the attention kernel: it wrote abuf2 itself
+    if (plan.n_slots > 1 && !att_merges_in_kernel(pol->dtype, plan, rows_ub, pol->nkv))
       LAUNCH(RG_K_ATTN_MERGE, launch_attn_merge(pol->dtype, pol->att_o, pol->att_ml, pol->nq, pol->hd, pol->row_pos,
                                                 pol->row_beg, plan, pol->abuf2, pol->a_plane, d_rows, rows_ub, st));
     }
@@ -363,7 +362,7 @@ int run_layers(rg_policy* pol, hipStream_t st, const int* d_rows, int rows_ub, i
     resid.norm_g = pol->g_ffn[l];
     if ((rc = gemm(pol, st, RG_K_GEMM_O, pol->abuf2, pol->q_dim, pol->w_o[l], pol->d, d_rows, rows_ub, resid, true, &S)))
       return rc;
-    if (S == 1 || pol->dtype != RG_DTYPE_BF16)
+    if (S == 1)
       LAUNCH(RG_K_RMSNORM, launch_rmsnorm(pol->dtype, pol->x, pol->g_ffn[l], pol->d, eps, pol->abuf, pol->a_plane,
                                            nullptr, d_rows, rows_ub, st));
     if ((rc = gemm(pol, st, RG_K_GEMM_GU, pol->abuf, pol->d, pol->w_gu[l], 2 * pol->F, d_rows, rows_ub, swig)))
@@ -373,7 +372,7 @@ int run_layers(rg_policy* pol, hipStream_t st, const int* d_rows, int rows_ub, i
     if ((rc = gemm(pol, st, RG_K_GEMM_DOWN, pol->abuf2, pol->F, pol->w_down[l], pol->d, d_rows, rows_ub, resid, true,
                    &S)))
       return rc;
-    if (gnext && (S == 1 || pol->dtype != RG_DTYPE_BF16))
+    if (gnext && S == 1)
       LAUNCH(RG_K_RMSNORM, launch_rmsnorm(pol->dtype, pol->x, gnext, pol->d, eps, pol->abuf, pol->a_plane, nullptr,
                                            d_rows, rows_ub, st));
   }
@@ -548,7 +547,7 @@ int prefill_and_fork(rg_policy* pol, hipStream_t st, const GroupRun& gr, const i
                                        pol->a_plane, nullptr, d_pre, gr.T_pre, st));
   // bf16 models: attention by row tiles, which stage each K/V block once for
   // all positions and heads of a tile (the row-by-row pass reads a row's whole
-  // context per row: 2.5 ms against 0.67 ms a layer for one 8191-token prompt,
+  // context per row: 2.5 ms against 0.47 ms a layer for one 8191-token prompt,
   // 0.28 against 0.15 ms for 32 of 512, 1.5B widths).
   int* d_tiles = pol->state + 13;
   const int tile_rows = att_tile_rows(pol->nq, pol->nkv);
@@ -753,11 +752,8 @@ int rg_policy_create(const rg_config* cfg, const rg_weights* w, const rg_limits*
   // projection tiles
   pol->logit_rows = std::max<int64_t>({S, P, std::min<int64_t>(M, RG_LM_SLICE_ROWS)});
   const int64_t maxN = std::max<int64_t>({pol->qkv_n, 2LL * pol->F, d});
-  pol->cpart_elems = std::max(M * maxN, (int64_t)RG_SPLIT_MAX * S * maxN);
-  // fp32 models run every projection through the partial buffer, the lm head
-  // too: up to max(M, logit_rows) rows of the vocabulary
-  if (pol->dtype != RG_DTYPE_BF16)
-    pol->cpart_elems = std::max(pol->cpart_elems, std::max(M, pol->logit_rows) * (int64_t)pol->V);
+  // split-K partials (bf16 models; fp32 projections are not split)
+  pol->cpart_elems = pol->dtype == RG_DTYPE_BF16 ? std::max(M * maxN, (int64_t)RG_SPLIT_MAX * S * maxN) : 0;
   // (row, context chunk) slots of one attention launch: decode steps (rows <=
   // S, prefix slots and chunks), and a full activation chunk of prefill or
   // recompute rows, which splits contexts longer than one chunk's span

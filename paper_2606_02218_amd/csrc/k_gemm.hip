@@ -40,11 +40,6 @@ __device__ __forceinline__ bf16x8_t lds_frag(const bf16_t* p) {
   return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(p));
 }
 
-template <typename KV>
-__device__ __forceinline__ void kv_store(KV* p, float v);
-template <> __device__ __forceinline__ void kv_store<float>(float* p, float v) { *p = v; }
-template <> __device__ __forceinline__ void kv_store<bf16_t>(bf16_t* p, float v) { *p = f32_to_bf16(v); }
-
 // Sum of the split partials of element (r, c), in split order.  The loads
 // of a batch of 16 splits are all issued before its first add.
 __device__ __forceinline__ float split_sum(const GemmEpi& ep, int S, int64_t off) {
@@ -62,22 +57,22 @@ __device__ __forceinline__ float split_sum(const GemmEpi& ep, int S, int64_t off
   return acc;
 }
 
-// QKV epilogue of row r for packed column c (a lower-half tile column: bit 4
-// of c is 0) holding dim d of its head, and c + 16 holding dim d + half.
-template <typename KV>
-__device__ __forceinline__ void qkv_store(const GemmEpi& ep, int r, int c, float a, float b) {
+// QKV epilogue of row r of an fp32 model for packed column c (a lower-half
+// tile column: bit 4 of c is 0) holding dim d of its head, and c + 16 holding
+// dim d + half.
+__device__ __forceinline__ void qkv_store_f32(const GemmEpi& ep, int r, int c, float a, float b) {
   const int hd = ep.hd, half = hd / 2;
   const int head = c / hd, p = c % hd;
   const int d = (p >> 5) * 16 + (p & 15);
   const int pos = ep.row_pos[r];
-  KV* pool = (KV*)ep.kv_pool;
+  float* pool = (float*)ep.kv_pool;
   if (head >= ep.n_q + ep.n_kv) {                     // value head: no rotation, V^T layout
     const int kvh = head - ep.n_q - ep.n_kv;
     const int page = ep.page_tab[(int64_t)ep.row_tab[r] * ep.tab_stride + pos / 16];
-    KV* vb = pool + (int64_t)page * ep.geom.page_stride + (int64_t)ep.layer * ep.geom.layer_stride +
-             ((int64_t)ep.n_kv + kvh) * 16 * hd;
-    kv_store<KV>(vb + kv_v_off(pos & 15, d, hd), a);
-    kv_store<KV>(vb + kv_v_off(pos & 15, d + half, hd), b);
+    float* vb = pool + (int64_t)page * ep.geom.page_stride + (int64_t)ep.layer * ep.geom.layer_stride +
+                ((int64_t)ep.n_kv + kvh) * 16 * hd;
+    vb[kv_v_off(pos & 15, d, hd)] = a;
+    vb[kv_v_off(pos & 15, d + half, hd)] = b;
     return;
   }
   const float co = ep.rope_cos[(int64_t)pos * half + d], si = ep.rope_sin[(int64_t)pos * half + d];
@@ -89,10 +84,10 @@ __device__ __forceinline__ void qkv_store(const GemmEpi& ep, int r, int c, float
   } else {
     const int kvh = head - ep.n_q;
     const int page = ep.page_tab[(int64_t)ep.row_tab[r] * ep.tab_stride + pos / 16];
-    KV* kp = pool + (int64_t)page * ep.geom.page_stride + (int64_t)ep.layer * ep.geom.layer_stride +
-             (int64_t)kvh * 16 * hd;
-    kv_store<KV>(kp + kv_k_off(pos & 15, d), ra);
-    kv_store<KV>(kp + kv_k_off(pos & 15, d + half), rb);
+    float* kp = pool + (int64_t)page * ep.geom.page_stride + (int64_t)ep.layer * ep.geom.layer_stride +
+                (int64_t)kvh * 16 * hd;
+    kp[kv_k_off(pos & 15, d)] = ra;
+    kp[kv_k_off(pos & 15, d + half)] = rb;
   }
 }
 
@@ -164,43 +159,6 @@ __device__ __forceinline__ void qkv_tile_store(const f32x4_t (&acc)[WM][WN], con
           kp[kv_k_off(slot, d + half)] = f32_to_bf16(rr);
         }
       }
-    }
-  }
-}
-
-// Epilogue of a finished tile whose split partials are in ep.part: rows
-// m0..m0+BM-1, columns n0..n0+BN-1 (< N); only rows below M are stored.
-// STORE, RESIDUAL and SWIGLU sum the partials of every row of the tile (all
-// inside the partial buffer; columns past N read a column in range) before
-// testing row and column, so their loads wait neither for the row count nor
-// for a test of a kernel argument; QKV needs the row's position and page and
-// tests first.  Every thread of the block calls it.
-template <int EPI, int BM, int BN, int NT, int SPLIT, typename KV>
-__device__ void tile_epilogue(const GemmEpi& ep, int S, int m0, int n0, int M, int N, int tid) {
-  if constexpr (EPI == GEMM_EPI_STORE || EPI == GEMM_EPI_RESIDUAL) {
-    for (int i = tid; i < BM * BN; i += NT) {
-      const int r = m0 + i / BN, c = n0 + i % BN;
-      const float v = split_sum(ep, S, (int64_t)r * N + min(c, N - 1));
-      if (r >= M || c >= N) continue;
-      if constexpr (EPI == GEMM_EPI_STORE) ep.C[(int64_t)r * ep.ldc + c] = v;
-      else ep.x[(int64_t)r * ep.ldx + c] += v;
-    }
-  } else if constexpr (EPI == GEMM_EPI_SWIGLU) {
-    for (int i = tid; i < BM * (BN / 2); i += NT) {
-      const int r = m0 + i / (BN / 2), q = i % (BN / 2);
-      const int gc = n0 + (q >> 4) * 32 + (q & 15);    // gate column; up is 16 further
-      const int gl = min(gc, N - 17);                    // gc itself while in range (N % 32 == 0)
-      const float gt = split_sum(ep, S, (int64_t)r * N + gl);
-      const float up = split_sum(ep, S, (int64_t)r * N + gl + 16);
-      if (r >= M || gc >= N) continue;
-      act_store<SPLIT>(ep.act, (int64_t)r * ep.act_ld + (gc >> 5) * 16 + (q & 15), gt / (1.0f + expf(-gt)) * up);
-    }
-  } else {  // GEMM_EPI_QKV: packed columns; a lower-half tile owns the rotated pair
-    for (int i = tid; i < BM * BN; i += NT) {
-      const int r = m0 + i / BN, c = n0 + i % BN;
-      if (r >= M || c >= N || ((c >> 4) & 1)) continue;
-      const int64_t roff = (int64_t)r * N;
-      qkv_store<KV>(ep, r, c, split_sum(ep, S, roff + c), split_sum(ep, S, roff + c + 16));
     }
   }
 }
@@ -402,7 +360,7 @@ __global__ __launch_bounds__((BM / (16 * WM)) * (BN / (16 * WN)) * 64) void k_ge
 // its x and g loads and a batch of its split partials before the first add,
 // and the row stays in registers between the sum of squares and the store.
 // The sums run in split order, as in split_sum.
-template <int SPLIT, int CPT>
+template <int CPT>
 __global__ __launch_bounds__(1024) void k_split_residual_norm(const int* __restrict__ d_rows,
                                                                const float* __restrict__ part, int64_t pst,
                                                                float* __restrict__ x, const float* __restrict__ norm_g,
@@ -452,7 +410,7 @@ __global__ __launch_bounds__(1024) void k_split_residual_norm(const int* __restr
     const int c = threadIdx.x + k * NT;
     if (c < N && r < rows_now) {
       xr[c] = xv[k];
-      act_store<SPLIT>(ep.norm_out, (int64_t)r * N + c, xv[k] * inv * gv[k]);
+      act_store<1>(ep.norm_out, (int64_t)r * N + c, xv[k] * inv * gv[k]);
     }
   }
 }
@@ -462,8 +420,7 @@ __global__ __launch_bounds__(1024) void k_split_residual_norm(const int* __restr
 // lower half of a 32-column group) and their rotation partners c+16..c+19.
 // The partials of both column quads are summed in split order (as split_sum),
 // rotated, and written as one 16-byte q piece per half or one 8-byte key piece
-// per half (values: their transposed layout, one element at a time).  Same
-// arithmetic as qkv_store; one wave per 64 quads of a row.
+// per half (values: their transposed layout, one element at a time); one wave per 64 quads of a row.
 __global__ __launch_bounds__(64) void k_qkv_epilogue4(const int* __restrict__ d_rows, const float* __restrict__ part,
                                                       int64_t pst, int N, int S, GemmEpi ep) {
   typedef float f4 __attribute__((ext_vector_type(4)));
@@ -534,36 +491,131 @@ __global__ __launch_bounds__(64) void k_qkv_epilogue4(const int* __restrict__ d_
   }
 }
 
-// Sum of split partials + epilogue: one block of 128 threads per (128
-// columns, row).  SPLIT: activation output as hi/lo bf16 planes.
-template <int EPI, int SPLIT, typename KV>
+// Sum of split partials + STORE, RESIDUAL or SWIGLU epilogue: one block of 128
+// threads (SWIGLU: 64) per (128 columns, row).  Sums the partials (all inside the partial
+// buffer; columns past N read a column in range) before testing row and
+// column, so the loads wait neither for the row count nor for a test of a
+// kernel argument.
+template <int EPI>
 __global__ __launch_bounds__(128) void k_split_epilogue(const int* __restrict__ d_rows, float* __restrict__ part,
                                                         int64_t pst, int N, int S, GemmEpi ep) {
   const int r = blockIdx.y;
   const int rows_now = *d_rows;
   ep.part = part;          // the preloaded copies
   ep.part_stride = pst;
-  if constexpr (EPI == GEMM_EPI_QKV) {
-    if (r >= rows_now) return;
+  if constexpr (EPI == GEMM_EPI_SWIGLU) {
+    const int q = threadIdx.x;                                     // 64 threads: a pair of columns each
+    const int gc = blockIdx.x * 128 + (q >> 4) * 32 + (q & 15);   // gate column; up is 16 further
+    const int gl = min(gc, N - 17);                                // gc itself while in range (N % 32 == 0)
+    const float gt = split_sum(ep, S, (int64_t)r * N + gl);
+    const float up = split_sum(ep, S, (int64_t)r * N + gl + 16);
+    if (r >= rows_now || gc >= N) return;
+    act_store<1>(ep.act, (int64_t)r * ep.act_ld + (gc >> 5) * 16 + (q & 15), gt / (1.0f + expf(-gt)) * up);
+  } else {
+    const int c = blockIdx.x * 128 + threadIdx.x;
+    const float v = split_sum(ep, S, (int64_t)r * N + min(c, N - 1));
+    if (r >= rows_now || c >= N) return;
+    if constexpr (EPI == GEMM_EPI_STORE) ep.C[(int64_t)r * ep.ldc + c] = v;
+    else ep.x[(int64_t)r * ep.ldx + c] += v;
   }
-  tile_epilogue<EPI, 1, 128, 128, SPLIT, KV>(ep, S, r, blockIdx.x * 128, rows_now, N, threadIdx.x);
 }
 
-// fp32 models: plain fp32 FMA, one thread per output, 64 columns x 4 rows per
-// block, into the partial buffer; k_split_epilogue then runs the epilogue.
-__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, int lda,
-                                                  const float* __restrict__ W, int ldw,
-                                                  float* __restrict__ C, const int* __restrict__ d_rows, int N,
-                                                  int K) {
-  const int M = *d_rows;
-  const int r = blockIdx.y * 4 + (threadIdx.x >> 6);
-  const int n = blockIdx.x * 64 + (threadIdx.x & 63);
-  if (r >= M || n >= N) return;
-  const float* a = A + (int64_t)r * lda;
-  const float* w = W + (int64_t)n * ldw;
-  float acc = 0.f;
-  for (int k = 0; k < K; ++k) acc = fmaf(a[k], w[k], acc);
-  C[(int64_t)r * N + n] = acc;
+// fp32 models: v_mfma_f32_16x16x4_f32 (full fp32 products and sums).  A block
+// owns 16 WMT rows x 32 columns; its four waves split K in turns of 16 and
+// meet in LDS, where the partial sums are added in wave order and the
+// epilogue runs.  Lane (l % 16, l / 16) loads four consecutive k's of its row
+// and column (16 bytes, 64 contiguous bytes per row); MFMA j of a turn takes
+// the j-th of each, the same k on both sides.  These launches are small (fp32
+// is the toy decoder's type): what counts is the length of the load chain.  A
+// thread per output walking K alone took 22.9 us a launch in the 128-wide
+// decoder's decode step and needed a second launch for the epilogue; this
+// takes 3.6-4.6 us with it.
+template <int WMT, int EPI>
+__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, const float* __restrict__ W,
+                                                  const int* __restrict__ d_rows, int lda, int ldw, int rows_cap,
+                                                  int N, int K, GemmEpi ep) {
+  constexpr int BM = 16 * WMT;
+  __shared__ float red[4][BM][33];
+  const int rows_now = *d_rows;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lk = (lane >> 4) * 4;
+  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * 32;
+  const float* wp[2];
+  const float* ap[WMT];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) wp[j] = W + (int64_t)min(n0 + j * 16 + lr, N - 1) * ldw + lk;
+#pragma unroll
+  for (int i = 0; i < WMT; ++i) ap[i] = A + (int64_t)min(m0 + i * 16 + lr, rows_cap - 1) * lda + lk;
+  f32x4_t acc[WMT][2];
+#pragma unroll
+  for (int i = 0; i < WMT; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  // U turns' loads are issued before the first product; turns past K read the
+  // last one again and are skipped
+  constexpr int U = WMT == 1 ? 4 : 2;
+  for (int k = wave * 16; k < K; k += 64 * U) {
+    f32x4_t w[U][2], a[U][WMT];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int kk = min(k + 64 * u, K - 16);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) w[u][j] = *reinterpret_cast<const f32x4_t*>(wp[j] + kk);
+#pragma unroll
+      for (int i = 0; i < WMT; ++i) a[u][i] = *reinterpret_cast<const f32x4_t*>(ap[i] + kk);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (k + 64 * u < K) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int i = 0; i < WMT; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][e], w[u][j][e], acc[i][j], 0, 0, 0);
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < WMT; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) red[wave][i * 16 + (lane >> 4) * 4 + e][j * 16 + lr] = acc[i][j][e];
+  __syncthreads();
+  const int M = min(rows_now, rows_cap);
+  for (int i = tid; i < BM * 16; i += 256) {   // columns c and c + 16 of a row
+    const int rr = i >> 4, cc = i & 15, r = m0 + rr, c = n0 + cc;
+    if (r >= M || c >= N) continue;
+    const float v0 = (red[0][rr][cc] + red[1][rr][cc]) + (red[2][rr][cc] + red[3][rr][cc]);
+    const float v1 = (red[0][rr][cc + 16] + red[1][rr][cc + 16]) + (red[2][rr][cc + 16] + red[3][rr][cc + 16]);
+    if constexpr (EPI == GEMM_EPI_QKV) {
+      qkv_store_f32(ep, r, c, v0, v1);
+    } else if constexpr (EPI == GEMM_EPI_SWIGLU) {
+      act_store<0>(ep.act, (int64_t)r * ep.act_ld + (n0 >> 1) + cc, v0 / (1.0f + expf(-v0)) * v1);
+    } else if constexpr (EPI == GEMM_EPI_RESIDUAL) {
+      ep.x[(int64_t)r * ep.ldx + c] += v0;
+      if (c + 16 < N) ep.x[(int64_t)r * ep.ldx + c + 16] += v1;
+    } else {
+      ep.C[(int64_t)r * ep.ldc + c] = v0;
+      if (c + 16 < N) ep.C[(int64_t)r * ep.ldc + c + 16] = v1;
+    }
+  }
+}
+
+template <int WMT>
+hipError_t launch_f32(const float* A, int lda, const float* W, int ldw, const int* d_rows, int rows_ub, int N, int K,
+                      const GemmEpi& ep, hipStream_t st) {
+  const dim3 grid((N + 31) / 32, (rows_ub + 16 * WMT - 1) / (16 * WMT));
+#define RG_F32(E) hipLaunchKernelGGL((k_gemm_f32<WMT, E>), grid, dim3(256), 0, st, A, W, d_rows, lda, ldw, rows_ub, N, K, ep)
+  switch (ep.mode) {
+    case GEMM_EPI_STORE: RG_F32(GEMM_EPI_STORE); break;
+    case GEMM_EPI_RESIDUAL: RG_F32(GEMM_EPI_RESIDUAL); break;
+    case GEMM_EPI_SWIGLU: RG_F32(GEMM_EPI_SWIGLU); break;
+    case GEMM_EPI_QKV: RG_F32(GEMM_EPI_QKV); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef RG_F32
+  return hipGetLastError();
 }
 
 template <int BM, int BN, int WM, int WN, int STAGES, int BK = 64>
@@ -622,13 +674,12 @@ hipError_t launch_tiled(const void* A, int lda, int64_t a_plane, const void* W, 
   return hipGetLastError();
 }
 
-template <int SPLIT, typename KV>
 hipError_t launch_split_epilogue(const int* d_rows, int rows_ub, int N, int S, const GemmEpi& ep, hipStream_t st) {
   if (ep.mode == GEMM_EPI_RESIDUAL && ep.norm_g) {
     const int cpt = (N + 1023) / 1024;
 #define RG_SRN(C)                                                                                             \
-  hipLaunchKernelGGL((k_split_residual_norm<SPLIT, C>), dim3(rows_ub), dim3(1024), 0, st, d_rows, ep.part,        \
-                     ep.part_stride, ep.x, ep.norm_g, N, S, ep.ldx, ep)
+  hipLaunchKernelGGL((k_split_residual_norm<C>), dim3(rows_ub), dim3(1024), 0, st, d_rows, ep.part, ep.part_stride,   \
+                     ep.x, ep.norm_g, N, S, ep.ldx, ep)
     if (cpt <= 1) RG_SRN(1);
     else if (cpt <= 2) RG_SRN(2);
     else if (cpt <= 4) RG_SRN(4);
@@ -637,29 +688,22 @@ hipError_t launch_split_epilogue(const int* d_rows, int rows_ub, int N, int S, c
 #undef RG_SRN
     return hipGetLastError();
   }
-  if constexpr (SPLIT == 1) {
-    if (ep.mode == GEMM_EPI_QKV && N % 32 == 0 && ep.hd % 32 == 0 && ep.part_stride % 4 == 0) {
-      hipLaunchKernelGGL(k_qkv_epilogue4, dim3((N / 8 + 63) / 64, rows_ub), dim3(64), 0, st, d_rows, ep.part,
-                         ep.part_stride, N, S, ep);
-      return hipGetLastError();
-    }
-  }
   dim3 grid((N + 127) / 128, rows_ub);
   switch (ep.mode) {
     case GEMM_EPI_STORE:
-      hipLaunchKernelGGL((k_split_epilogue<GEMM_EPI_STORE, SPLIT, KV>), grid, dim3(128), 0, st, d_rows, ep.part,
-                         ep.part_stride, N, S, ep);
+      hipLaunchKernelGGL((k_split_epilogue<GEMM_EPI_STORE>), grid, dim3(128), 0, st, d_rows, ep.part, ep.part_stride,
+                         N, S, ep);
       break;
     case GEMM_EPI_RESIDUAL:
-      hipLaunchKernelGGL((k_split_epilogue<GEMM_EPI_RESIDUAL, SPLIT, KV>), grid, dim3(128), 0, st, d_rows, ep.part,
+      hipLaunchKernelGGL((k_split_epilogue<GEMM_EPI_RESIDUAL>), grid, dim3(128), 0, st, d_rows, ep.part,
                          ep.part_stride, N, S, ep);
       break;
     case GEMM_EPI_SWIGLU:
-      hipLaunchKernelGGL((k_split_epilogue<GEMM_EPI_SWIGLU, SPLIT, KV>), grid, dim3(128), 0, st, d_rows, ep.part,
-                         ep.part_stride, N, S, ep);
+      hipLaunchKernelGGL((k_split_epilogue<GEMM_EPI_SWIGLU>), grid, dim3(64), 0, st, d_rows, ep.part, ep.part_stride,
+                         N, S, ep);
       break;
     case GEMM_EPI_QKV:
-      hipLaunchKernelGGL((k_split_epilogue<GEMM_EPI_QKV, SPLIT, KV>), grid, dim3(128), 0, st, d_rows, ep.part,
+      hipLaunchKernelGGL(k_qkv_epilogue4, dim3((N / 8 + 63) / 64, rows_ub), dim3(64), 0, st, d_rows, ep.part,
                          ep.part_stride, N, S, ep);
       break;
     default: return hipErrorInvalidValue;
@@ -725,7 +769,7 @@ int gemm_tile_cols(int dtype, int rows_ub, int N, int K) {
 hipError_t launch_gemm(int dtype, const void* A, int lda, int64_t a_plane, const void* W, int ldw, const int* d_rows,
                        int rows_ub, int N, int K, int splits, int k_per_split, const GemmEpi& ep, hipStream_t st) {
   if (rows_ub <= 0) return hipSuccess;
-  if ((splits > 1 || dtype != 1) && !ep.part) return hipErrorInvalidValue;
+  if (splits > 1 && !ep.part) return hipErrorInvalidValue;
   if (splits > GEMM_MAX_SPLITS) return hipErrorInvalidValue;
   if ((ep.mode == GEMM_EPI_SWIGLU || ep.mode == GEMM_EPI_QKV) && N % 32) return hipErrorInvalidValue;
   if (ep.mode == GEMM_EPI_QKV && (ep.hd % 32 || 128 % ep.hd)) return hipErrorInvalidValue;
@@ -745,13 +789,11 @@ hipError_t launch_gemm(int dtype, const void* A, int lda, int64_t a_plane, const
       default: e = launch_tiled<256, 256, 4, 8, 1>(A, lda, a_plane, W, ldw, d_rows, rows_ub, N, K, splits, k_per_split, ep, st); break;
     }
     if (e != hipSuccess || splits == 1) return e;
-    return launch_split_epilogue<1, bf16_t>(d_rows, rows_ub, N, splits, ep, st);
+    return launch_split_epilogue(d_rows, rows_ub, N, splits, ep, st);
   }
-  // fp32: whole-K product into the partial buffer, then the epilogue
-  if (splits != 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_gemm_f32, dim3((N + 63) / 64, (rows_ub + 3) / 4), dim3(256), 0, st, (const float*)A, lda,
-                     (const float*)W, ldw, ep.part, d_rows, N, K);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_split_epilogue<0, float>(d_rows, rows_ub, N, 1, ep, st);
+  // fp32: 64-row tiles once 16-row ones give every CU two blocks
+  if (splits != 1 || K % 16) return hipErrorInvalidValue;
+  if ((int64_t)((N + 31) / 32) * ((rows_ub + 15) / 16) > 512)
+    return launch_f32<4>((const float*)A, lda, (const float*)W, ldw, d_rows, rows_ub, N, K, ep, st);
+  return launch_f32<1>((const float*)A, lda, (const float*)W, ldw, d_rows, rows_ub, N, K, ep, st);
 }

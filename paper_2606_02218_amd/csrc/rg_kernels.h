@@ -68,12 +68,12 @@ struct GemmEpi {
   float* q_out; void* kv_pool; KvGeom geom; int layer;      // QKV
   const int32_t* page_tab; int tab_stride; const int32_t* row_tab; const int32_t* row_pos;
   const float* rope_cos; const float* rope_sin; int n_q, n_kv, hd;
-  float* part; int64_t part_stride;       // split partials [S][rows][N] (S > 1 and fp32 models)
+  float* part; int64_t part_stride;       // split partials [S][rows][N] (S > 1)
 };
 
 // y = A W^T over rows < *d_rows with K split `splits` ways (bf16 models: K
-// and k_per_split multiples of 64, N a multiple of 16; fp32 models: one
-// split), then the epilogue ep.
+// and k_per_split multiples of 64, N a multiple of 16; fp32 models: K a
+// multiple of 16, one split), then the epilogue ep.
 hipError_t launch_gemm(int dtype, const void* A, int lda, int64_t a_plane, const void* W, int ldw, const int* d_rows,
                        int rows_ub, int N, int K, int splits, int k_per_split, const GemmEpi& ep, hipStream_t st);
 
