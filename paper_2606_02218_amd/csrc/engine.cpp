@@ -42,8 +42,6 @@ int fail(int code, const std::string& msg) {
 
 constexpr int RG_PAGE_TOK = 16;        // tokens per KV page
 constexpr int RG_SPLIT_MAX = GEMM_MAX_SPLITS;   // largest split-K factor of a decode GEMM
-constexpr int RG_GEMM_TARGET = 384;    // blocks a split-K GEMM launch aims for
-constexpr int RG_GEMM_FULL = 256;      // output-tile blocks that need no split
 constexpr int RG_PRE_TARGET = 512;     // workgroups the prefix attention pass aims for
 constexpr int RG_PRE_MIN_CHUNK = 64;   // fewest prefix tokens per prefix workgroup
 constexpr int RG_PRE_MAX_SLOTS = 16;   // prefix chunks per row (more only for prefixes > 16k tokens)
@@ -229,53 +227,17 @@ struct ProfScope {
 // single-kernel launchers that time their dispatch with armed events
 #define LAUNCH_TIMED(kind, call) LAUNCH_(kind, call, true)
 
-// Split-K factor of a projection: enough blocks to cover the chip, each
-// split at least two 64-wide K steps, and the fp32 split partials (written
-// once, read once by the reducing block) within max(2 x weight bytes, 32 MB).
-void choose_splits(const rg_policy* pol, int N, int rows_ub, int K, int* splits, int* kps) {
-  int S = 1;
-  if (pol->dtype == RG_DTYPE_BF16) {
-    // Split K only while the output tiles leave the chip short of blocks, to
-    // about RG_GEMM_TARGET blocks (twice that for narrow outputs, whose
-    // partials are small), and only as far as the fp32 partials (written
-    // once, read once: 8 bytes per output element and split) stay within
-    // twice the weight bytes or 24 MiB.
-    const int64_t bm = gemm_tile_rows(pol->dtype, rows_ub, N), bn = gemm_tile_cols(pol->dtype, rows_ub, N, K);
-    const int64_t blocks = ceil_div(N, bn) * ceil_div(rows_ub, bm);
-    const int64_t target = N >= 8192 ? RG_GEMM_TARGET : 2 * RG_GEMM_TARGET;
-    if (blocks < RG_GEMM_FULL) S = (int)ceil_div(target, blocks);
-    const int64_t budget = std::max<int64_t>(4LL * N * K, 24LL << 20);
-    S = (int)std::min<int64_t>({(int64_t)S, K / 128, budget / (8LL * rows_ub * N), RG_SPLIT_MAX});
-    S = std::max(1, S);
-  }
-  const int step = pol->dtype == RG_DTYPE_BF16 ? 64 : 1;
-  int k = (int)(ceil_div(ceil_div(K, S), step) * step);
-  *kps = k;
-  *splits = (int)ceil_div(K, k);
-}
-
-// Split plan of a projection into the split-K workspace.
-void plan(const rg_policy* pol, int N, int rows_ub, int K, int* S, int* kps) {
-  choose_splits(pol, N, rows_ub, K, S, kps);
-  const int64_t fit = pol->cpart_elems / ((int64_t)rows_ub * N);   // splits the workspace holds
-  if (*S > fit) {
-    const int step = pol->dtype == RG_DTYPE_BF16 ? 64 : 1;
-    *S = (int)std::max<int64_t>(1, fit);
-    *kps = (int)ceil_div(ceil_div(K, *S), step) * step;
-    *S = (int)ceil_div(K, *kps);
-  }
-}
-
 // One projection with its epilogue; the split plan and workspace are filled in here.
 int gemm(rg_policy* pol, hipStream_t st, int kind, const void* A, int K, const void* W, int N, const int* d_rows,
          int rows_ub, GemmEpi ep, bool allow_split = true, int* splits_out = nullptr) {
-  int S = 1, kps = K;
-  if (allow_split) plan(pol, N, rows_ub, K, &S, &kps);
-  if (splits_out) *splits_out = S;
+  const int64_t fit = pol->cpart_elems / ((int64_t)rows_ub * N);   // splits the workspace holds
+  // the reduction that normalises the row holds at most 8192 columns
+  if (ep.mode == GEMM_EPI_RESIDUAL && ep.norm_g && N > 8192) allow_split = false;
+  const GemmPlan p = gemm_plan(pol->dtype, rows_ub, N, K, allow_split ? (int)std::min<int64_t>(fit, RG_SPLIT_MAX) : 1);
+  if (splits_out) *splits_out = p.splits;
   ep.part = pol->cpart;
   ep.part_stride = (int64_t)rows_ub * N;
-  if (S > 1 && ep.part_stride * S > pol->cpart_elems) return fail(RG_ENOMEM, "GEMM workspace too small");
-  LAUNCH(kind, launch_gemm(pol->dtype, A, K, pol->a_plane, W, K, d_rows, rows_ub, N, K, S, kps, ep, st));
+  LAUNCH(kind, launch_gemm(pol->dtype, p, A, K, pol->a_plane, W, K, d_rows, rows_ub, N, K, ep, st));
   return RG_OK;
 }
 
@@ -748,8 +710,7 @@ int rg_policy_create(const rg_config* cfg, const rg_weights* w, const rg_limits*
   // ---- workspace
   const int64_t M = pol->m_act, S = lim.max_seqs, P = lim.max_prompts;
   // the rollout needs max(S, P) rows of logits; the recompute's lm head runs
-  // in slices of this many rows, and slices above 1024 rows take the 256 x 256
-  // projection tiles
+  // in slices of this many rows
   pol->logit_rows = std::max<int64_t>({S, P, std::min<int64_t>(M, RG_LM_SLICE_ROWS)});
   const int64_t maxN = std::max<int64_t>({pol->qkv_n, 2LL * pol->F, d});
   // split-K partials (bf16 models; fp32 projections are not split)

@@ -11,12 +11,13 @@
 //             a rotated pair (d, d + h/2) lies in adjacent column tiles.
 //
 // bf16 models: LDS-tiled gfx950 MFMA (v_mfma_f32_16x16x32_bf16).  A block
-// owns a BM x BN output tile and walks its K range in BK = 64 steps: every
-// thread fetches 16-byte pieces of the next A (hi and lo planes) and W tiles
-// into registers while the waves multiply the current tiles out of LDS, then
-// the pieces are written to LDS for the next step.  Each wave owns a WM x WN
-// grid of 16 x 16 MFMA tiles.  The activation comes as hi/lo bf16 planes and
-// every fragment takes two MFMAs (W*hi + W*lo) into one fp32 accumulator.
+// owns a BM x BN output tile and walks its K range in steps of 64.  The
+// activation comes as hi/lo bf16 planes and every fragment takes two MFMAs
+// (W*hi + W*lo) into one fp32 accumulator; each wave owns a WM x WN grid of 16
+// x 16 MFMA tiles.  Two kernels: k_gemm_tiled (few rows: every thread fetches
+// 16-byte pieces of the next A and W tiles into registers while the waves
+// multiply the current tiles out of LDS) and k_gemm_dma (128-row tiles, loads
+// straight into a second LDS buffer).
 //
 // Split over K: the grid's z dimension splits K and every split writes its
 // fp32 partial; k_split_epilogue then sums the partials in split order (one
@@ -26,12 +27,14 @@
 // MFMA 16x16x32 lane layout: lane l supplies row (l % 16), k-slice
 // 8*(l / 16) .. +7 of A and column (l % 16), the same k-slice of B; it
 // receives C rows 4*(l / 16) .. +3 of column (l % 16).
+#include <algorithm>
+
 #include "rg_device.h"
 #include "rg_kernels.h"
 
 namespace {
 
-constexpr int BK_MAX = 64;             // K step of the small tiles; large tiles may use 32
+constexpr int BK_MAX = 64;             // K step
 constexpr int LDS_PAD = 16;            // bf16 elements of padding per LDS row (rows 160 B apart: no bank conflicts)
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
@@ -163,11 +166,72 @@ __device__ __forceinline__ void qkv_tile_store(const f32x4_t (&acc)[WM][WN], con
   }
 }
 
+// Epilogue of one wave straight from its accumulators: rows m0 + (wm*WM + i)*16
+// + 4*(lane/16) + e, columns n0 + (wn*WN + j)*16 + lane%16; only rows below M
+// and columns below N are stored.
+template <int EPI, int WM, int WN>
+__device__ __forceinline__ void acc_epilogue(const f32x4_t (&acc)[WM][WN], const GemmEpi& ep, int tz, int m0, int n0,
+                                             int M, int N, int wm, int wn, int lane) {
+  const int lr = lane & 15;
+  if constexpr (EPI == GEMM_EPI_PARTIAL) {
+    float* pp = ep.part + tz * ep.part_stride;
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        const int col = n0 + (wn * WN + j) * 16 + lr;
+        if (col >= N) continue;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = m0 + (wm * WM + i) * 16 + (lane >> 4) * 4 + e;
+          if (r < M) pp[(int64_t)r * N + col] = acc[i][j][e];
+        }
+      }
+  } else if constexpr (EPI == GEMM_EPI_QKV) {
+    qkv_tile_store<WM, WN>(acc, ep, m0, n0, M, N, wm, wn, lane, ep.row_pos, ep.row_tab, ep.page_tab, ep.rope_cos,
+                           ep.rope_sin, ep.q_out, (bf16_t*)ep.kv_pool);
+  } else if constexpr (EPI == GEMM_EPI_SWIGLU) {
+    // tiles 2m and 2m+1 of a wave pair up: (gate, up)
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; j += 2) {
+        const int c = n0 + (wn * WN + j) * 16 + lr;   // lower tile's column
+        if (c >= N) continue;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = m0 + (wm * WM + i) * 16 + (lane >> 4) * 4 + e;
+          if (r >= M) continue;
+          const float a = acc[i][j][e], b = acc[i][j + 1][e];
+          act_store<1>(ep.act, (int64_t)r * ep.act_ld + (c >> 5) * 16 + lr, a / (1.0f + expf(-a)) * b);
+        }
+      }
+  } else {
+    float* cp = EPI == GEMM_EPI_RESIDUAL ? ep.x : ep.C;
+    const int ld = EPI == GEMM_EPI_RESIDUAL ? ep.ldx : ep.ldc;
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        const int col = n0 + (wn * WN + j) * 16 + lr;
+        if (col >= N) continue;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = m0 + (wm * WM + i) * 16 + (lane >> 4) * 4 + e;
+          if (r < M) {
+            if constexpr (EPI == GEMM_EPI_RESIDUAL) cp[(int64_t)r * ld + col] += acc[i][j][e];
+            else cp[(int64_t)r * ld + col] = acc[i][j][e];
+          }
+        }
+      }
+  }
+}
+
 // A 16-byte piece of W.  NT: a non-temporal load, for weights that no other
 // block of the launch reads (one row tile): streamed through without
 // claiming cache space, which measured 6.5-6.7 TB/s against 5.9-6.1 TB/s
 // for plain loads in a pure streaming read of 8 GiB.
-__device__ __forceinline__ int k_split_count(int K, int k_per_split) { return (K + k_per_split - 1) / k_per_split; }
+__host__ __device__ __forceinline__ int k_split_count(int K, int k_per_split) { return (K + k_per_split - 1) / k_per_split; }
 
 template <bool NT>
 __device__ __forceinline__ u32x4_t load_w(const bf16_t* p) {
@@ -300,58 +364,165 @@ __global__ __launch_bounds__((BM / (16 * WM)) * (BN / (16 * WN)) * 64) void k_ge
 #undef RG_FETCH
 #undef RG_STASH
 
-  if constexpr (EPI == GEMM_EPI_PARTIAL) {
-    float* pp = ep.part + tz * ep.part_stride;
+  acc_epilogue<EPI, WM, WN>(acc, ep, tz, m0, n0, M, N, wm, wn, lane);
+}
+
+// 16 bytes per lane from global memory straight into LDS: lane l's piece lands
+// at byte address lds + 16 l.  Issued from assembly, so that the compiler does
+// not drain every load in flight ahead of each LDS read (it cannot tell the
+// buffers apart); the kernel places the waits itself.  No register is written.
+__device__ __forceinline__ void dma16(uint32_t lds, uint32_t voff, const bf16_t* sbase) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(sbase)
+               : "memory");
+}
+
+// Large tiles: BM x BN output, eight waves, K steps of 64 through two LDS
+// buffers that are filled by direct global-to-LDS loads.  A wave keeps the
+// fragments of two 32-wide half steps in registers: while it multiplies one
+// half it reads the other, and the barrier that hands the buffers over sits
+// between the halves of a step, so neither the barrier nor an LDS read waits
+// ahead of the MFMAs, and a buffer's loads have a whole step to arrive.  LDS
+// rows are 128 bytes, the 16-byte chunk c of row r at c ^ (r / 2 % 8): the 16
+// rows of a fragment read cover all 64 banks (the loads permute their global
+// chunk within the row's 128 bytes to match).
+//
+// What bounds it: power.  At 16384 x 17920 x 1536 the MFMAs take 70 % of the
+// cycles, at a clock that falls to 1.6-2.0 GHz; 1.11 PFLOP/s issued (two planes)
+// against 1.06 for register-staged 256 x 256 tiles, at any schedule, MFMA shape
+// or wave tile tried.  The gain is in the smaller tile: the 1536 columns of
+// the O and down projections make 768 blocks of 128 x 256 (3 per CU) instead of
+// 384 of 256 x 256 (1.5, so 2 rounds): down at 16384 rows 1019 -> 805 us, at
+// 4096 rows 441 -> 214; gate/up at 1100 x 768 -> 6144 49.7 -> 25.7.
+template <int BM, int BN, int WM, int WN, int EPI>
+__global__ __launch_bounds__(512, 2) void k_gemm_dma(const int* __restrict__ d_rows, const bf16_t* __restrict__ A,
+                                                     const bf16_t* __restrict__ W, int64_t a_plane, int lda, int ldw,
+                                                     int rows_cap, int N, int K, int k_per_split, int gx, int gy,
+                                                     GemmEpi ep) {
+  constexpr int BK = 64, CH = BK / 8;                        // CH 16-byte chunks per row and step
+  constexpr int WAVES_N = BN / (16 * WN), NT = 512;
+  static_assert((BM / (16 * WM)) * WAVES_N == 8, "eight waves");
+  constexpr int A_P = BM * CH / NT, W_P = BN * CH / NT;      // pieces per thread of one A plane, of W
+  static_assert((BM * CH) % NT == 0 && (BN * CH) % NT == 0, "tile pieces must split evenly over threads");
+  static_assert((EPI != GEMM_EPI_SWIGLU && EPI != GEMM_EPI_QKV) || WN % 2 == 0, "pairs of adjacent column tiles");
+  constexpr int STAGE = (2 * BM + BN) * BK;                  // elements: A hi, A lo, W
+  __shared__ __attribute__((aligned(128))) bf16_t sm[2 * STAGE];
+  const int rows_now = *d_rows;
+
+  // the XCD-aware grouped tile order of k_gemm_tiled, groups of 4 row tiles
+  constexpr int TILE_GROUP = 4;
+  const int per = gridDim.x / 8;
+  int w = (blockIdx.x % 8) * per + blockIdx.x / 8;
+  if (w >= gx * gy * k_split_count(K, k_per_split)) return;
+  const int tz = w / (gx * gy);
+  w -= tz * gx * gy;
+  const int gsz = TILE_GROUP * gx;
+  const int g = w / gsz, r0 = g * TILE_GROUP;
+  const int rows_g = min(TILE_GROUP, gy - r0);
+  const int wi = w - g * gsz;
+  const int ty = r0 + wi % rows_g, tx = wi / rows_g;
+  const int m0 = ty * BM, n0 = tx * BN;
+  const int M = min(rows_now, rows_cap);
+  if (m0 >= M) return;
+  const int kb0 = tz * k_per_split;
+  const int nk = (min(K, kb0 + k_per_split) - kb0) / BK;     // K steps, at least 1
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+  const int lr = lane & 15, lg = lane >> 4;
+  // byte offsets of this thread's pieces from the tile's first row (rows past
+  // the launch's bound and columns past N read the last one, never stored)
+  uint32_t ao[A_P], wo[W_P];
 #pragma unroll
-    for (int i = 0; i < WM; ++i)
-#pragma unroll
-      for (int j = 0; j < WN; ++j) {
-        const int col = n0 + (wn * WN + j) * 16 + lr;
-        if (col >= N) continue;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = m0 + (wm * WM + i) * 16 + (lane >> 4) * 4 + e;
-          if (r < M) pp[(int64_t)r * N + col] = acc[i][j][e];
-        }
-      }
-  } else if constexpr (EPI == GEMM_EPI_QKV) {
-    qkv_tile_store<WM, WN>(acc, ep, m0, n0, M, N, wm, wn, lane, ep.row_pos, ep.row_tab, ep.page_tab, ep.rope_cos,
-                           ep.rope_sin, ep.q_out, (bf16_t*)ep.kv_pool);
-  } else if constexpr (EPI == GEMM_EPI_SWIGLU) {
-    // tiles 2m and 2m+1 of a wave pair up: (gate, up)
-#pragma unroll
-    for (int i = 0; i < WM; ++i)
-#pragma unroll
-      for (int j = 0; j < WN; j += 2) {
-        const int c = n0 + (wn * WN + j) * 16 + lr;   // lower tile's column
-        if (c >= N) continue;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = m0 + (wm * WM + i) * 16 + (lane >> 4) * 4 + e;
-          if (r >= M) continue;
-          const float a = acc[i][j][e], b = acc[i][j + 1][e];
-          act_store<1>(ep.act, (int64_t)r * ep.act_ld + (c >> 5) * 16 + lr, a / (1.0f + expf(-a)) * b);
-        }
-      }
-  } else {
-    float* cp = EPI == GEMM_EPI_RESIDUAL ? ep.x : ep.C;
-    const int ld = EPI == GEMM_EPI_RESIDUAL ? ep.ldx : ep.ldc;
-#pragma unroll
-    for (int i = 0; i < WM; ++i)
-#pragma unroll
-      for (int j = 0; j < WN; ++j) {
-        const int col = n0 + (wn * WN + j) * 16 + lr;
-        if (col >= N) continue;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = m0 + (wm * WM + i) * 16 + (lane >> 4) * 4 + e;
-          if (r < M) {
-            if constexpr (EPI == GEMM_EPI_RESIDUAL) cp[(int64_t)r * ld + col] += acc[i][j][e];
-            else cp[(int64_t)r * ld + col] = acc[i][j][e];
-          }
-        }
-      }
+  for (int i = 0; i < A_P; ++i) {
+    const int p = i * NT + tid, row = p / CH, ch = (p % CH) ^ ((row >> 1) & 7);
+    ao[i] = (uint32_t)(min(row, rows_cap - 1 - m0) * lda + ch * 8) * 2;
   }
+#pragma unroll
+  for (int i = 0; i < W_P; ++i) {
+    const int p = i * NT + tid, row = p / CH, ch = (p % CH) ^ ((row >> 1) & 7);
+    wo[i] = (uint32_t)(min(row, N - 1 - n0) * ldw + ch * 8) * 2;
+  }
+  const bf16_t* ah = A + (int64_t)m0 * lda + kb0;            // advance one step per issue
+  const bf16_t* al = ah + a_plane;
+  const bf16_t* wb = W + (int64_t)n0 * ldw + kb0;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t*)sm + wave * 1024;
+  auto issue = [&](int buf) {
+    const uint32_t lb = lds0 + buf * STAGE * 2;
+#pragma unroll
+    for (int i = 0; i < A_P; ++i) dma16(lb + i * NT * 16, ao[i], ah);
+#pragma unroll
+    for (int i = 0; i < A_P; ++i) dma16(lb + BM * BK * 2 + i * NT * 16, ao[i], al);
+#pragma unroll
+    for (int i = 0; i < W_P; ++i) dma16(lb + 2 * BM * BK * 2 + i * NT * 16, wo[i], wb);
+    ah += BK;
+    al += BK;
+    wb += BK;
+  };
+  const int sl[2] = {lr * BK + (lg ^ ((lr >> 1) & 7)) * 8, lr * BK + ((4 + lg) ^ ((lr >> 1) & 7)) * 8};
+  const int abase = wm * WM * 16 * BK, wbase = 2 * BM * BK + wn * WN * 16 * BK;
+  bf16x8_t fh[2][WM], fl[2][WM], fw[2][WN];
+  f32x4_t acc[WM][WN];
+#pragma unroll
+  for (int i = 0; i < WM; ++i)
+#pragma unroll
+    for (int j = 0; j < WN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  // half h of buffer buf into fragment set h
+#define RG_READ(H, BUF)                                                                                       \
+  {                                                                                                           \
+    const bf16_t* sb = sm + (BUF) * STAGE + sl[H];                                                            \
+    _Pragma("unroll") for (int j = 0; j < WN; ++j) fw[H][j] = lds_frag(sb + wbase + j * 16 * BK);             \
+    _Pragma("unroll") for (int i = 0; i < WM; ++i) {                                                          \
+      fh[H][i] = lds_frag(sb + abase + i * 16 * BK);                                                          \
+      fl[H][i] = lds_frag(sb + abase + BM * BK + i * 16 * BK);                                                \
+    }                                                                                                         \
+  }
+#define RG_MULTIPLY(H)                                                                                        \
+  _Pragma("unroll") for (int i = 0; i < WM; ++i) {                                                            \
+    _Pragma("unroll") for (int j = 0; j < WN; ++j)                                                            \
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fh[H][i], fw[H][j], acc[i][j], 0, 0, 0);         \
+    _Pragma("unroll") for (int j = 0; j < WN; ++j)                                                            \
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fl[H][i], fw[H][j], acc[i][j], 0, 0, 0);         \
+  }
+  // spreads the reads over the MFMAs: one read, two MFMAs, then the rest
+#define RG_MIX()                                                                                              \
+  _Pragma("unroll") for (int q = 0; q < 2 * WM + WN; ++q) {                                                   \
+    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                                        \
+    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                                                        \
+  }                                                                                                           \
+  __builtin_amdgcn_sched_group_barrier(0x008, 2 * WM * WN, 0);
+  issue(0);
+  if (nk > 1) {
+    issue(1);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * A_P + W_P) : "memory");   // step 0 has arrived, step 1 may not have
+  } else {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  RG_READ(0, 0)
+  int buf = 0;
+  for (int k = 0; k < nk; ++k) {
+    __builtin_amdgcn_sched_barrier(0);
+    RG_READ(1, buf)
+    RG_MULTIPLY(0)
+    RG_MIX()
+    __builtin_amdgcn_sched_barrier(0);
+    // this wave has read all of step k and its share of step k + 1 has arrived
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();                 // ... and so has everyone's
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (k + 2 < nk) issue(buf);
+    buf ^= 1;
+    if (k + 1 < nk) RG_READ(0, buf)
+    RG_MULTIPLY(1)
+    RG_MIX()
+  }
+#undef RG_READ
+#undef RG_MULTIPLY
+#undef RG_MIX
+  acc_epilogue<EPI, WM, WN>(acc, ep, tz, m0, n0, M, N, wm, wn, lane);
 }
 
 // Residual add of the split partials followed by the next RMSNorm of the row
@@ -624,13 +795,13 @@ hipError_t launch_tiled(const void* A, int lda, int64_t a_plane, const void* W, 
   constexpr int NT = (BM / (16 * WM)) * (BN / (16 * WN)) * 64;
   const int gx = (N + BN - 1) / BN, gy = (rows_ub + BM - 1) / BM;
   dim3 grid(gx, gy, splits);
-  // The XCD-aware grouped tile order for 256 x 256 tiles, and for wide
-  // outputs (gate/up) read by 8 or more row tiles: there the default order
-  // fetches each weight tile about 7 times per launch from beyond L2 (gate/up
-  // at 512 rows: 418 MB of L2 misses for 58 MB of operands, against 120 MB
-  // in this order, 7 % faster).  For the narrow outputs at 256-512 rows it
-  // measured 2-9 % slower, so they keep the default order.
-  const int order1d = BM == 256 || (N >= 8192 && gy >= 8);
+  // The XCD-aware grouped tile order for wide outputs (gate/up) read by 8 or
+  // more row tiles: there the default order fetches each weight tile about 7
+  // times per launch from beyond L2 (gate/up at 512 rows on 64-row tiles: 418
+  // MB of L2 misses for 58 MB of operands, against 120 MB in this order, 7 %
+  // faster).  For the narrow outputs at 256-512 rows it measured 2-9 % slower,
+  // so they keep the default order.
+  const bool order1d = N >= 8192 && gy >= 8;
   if (order1d) {
     if ((K + k_per_split - 1) / k_per_split != splits) return hipErrorInvalidValue;
     grid = dim3((unsigned)(((int64_t)gx * gy * splits + 7) / 8 * 8));
@@ -641,22 +812,17 @@ hipError_t launch_tiled(const void* A, int lda, int64_t a_plane, const void* W, 
   // measured 12 % slower over the 1.5B group step.
   const bool ntw = gy == 1;
   // The tile order is a template parameter, so that no kernel argument
-  // decides a branch ahead of the first loads.  Below 256 x 256 tiles the
-  // grouped order needs 8 or more row tiles, so it never meets ntw.
+  // decides a branch ahead of the first loads.  The grouped order needs 8 or
+  // more row tiles, so it never meets ntw.
 #define RG_TILED_K(E, NTV, XOV)                                                                               \
   hipLaunchKernelGGL((k_gemm_tiled<BM, BN, WM, WN, STAGES, BK, E, NTV, XOV>), grid, dim3(NT), 0, st,           \
                      (const bf16_t*)A, (const bf16_t*)W, d_rows, a_plane, lda, ldw, rows_ub, N, K, k_per_split, gx, \
                      gy, ep)
 #define RG_TILED(E)                                                                                           \
   do {                                                                                                        \
-    if constexpr (BM == 256) {                                                                                \
-      if (ntw) RG_TILED_K(E, true, true);                                                                     \
-      else RG_TILED_K(E, false, true);                                                                        \
-    } else {                                                                                                  \
-      if (order1d) RG_TILED_K(E, false, true);                                                                \
-      else if (ntw) RG_TILED_K(E, true, false);                                                               \
-      else RG_TILED_K(E, false, false);                                                                       \
-    }                                                                                                         \
+    if (order1d) RG_TILED_K(E, false, true);                                                                  \
+    else if (ntw) RG_TILED_K(E, true, false);                                                                 \
+    else RG_TILED_K(E, false, false);                                                                         \
   } while (0)
   if (splits > 1) {
     RG_TILED(GEMM_EPI_PARTIAL);
@@ -671,6 +837,32 @@ hipError_t launch_tiled(const void* A, int lda, int64_t a_plane, const void* W, 
   }
 #undef RG_TILED
 #undef RG_TILED_K
+  return hipGetLastError();
+}
+
+template <int BM, int BN, int WM, int WN>
+hipError_t launch_dma(const void* A, int lda, int64_t a_plane, const void* W, int ldw, const int* d_rows, int rows_ub,
+                      int N, int K, int splits, int k_per_split, const GemmEpi& ep, hipStream_t st) {
+  const int gx = (N + BN - 1) / BN, gy = (rows_ub + BM - 1) / BM;
+  if (k_split_count(K, k_per_split) != splits) return hipErrorInvalidValue;
+  // byte offsets inside a tile are 32-bit
+  if ((int64_t)BM * lda * 2 > UINT32_MAX || (int64_t)BN * ldw * 2 > UINT32_MAX) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(((int64_t)gx * gy * splits + 7) / 8 * 8));
+#define RG_DMA(E)                                                                                             \
+  hipLaunchKernelGGL((k_gemm_dma<BM, BN, WM, WN, E>), grid, dim3(512), 0, st, d_rows, (const bf16_t*)A,       \
+                     (const bf16_t*)W, a_plane, lda, ldw, rows_ub, N, K, k_per_split, gx, gy, ep)
+  if (splits > 1) {
+    RG_DMA(GEMM_EPI_PARTIAL);
+  } else {
+    switch (ep.mode) {
+      case GEMM_EPI_STORE: RG_DMA(GEMM_EPI_STORE); break;
+      case GEMM_EPI_RESIDUAL: RG_DMA(GEMM_EPI_RESIDUAL); break;
+      case GEMM_EPI_SWIGLU: RG_DMA(GEMM_EPI_SWIGLU); break;
+      case GEMM_EPI_QKV: RG_DMA(GEMM_EPI_QKV); break;
+      default: return hipErrorInvalidValue;
+    }
+  }
+#undef RG_DMA
   return hipGetLastError();
 }
 
@@ -713,48 +905,45 @@ hipError_t launch_split_epilogue(const int* d_rows, int rows_ub, int N, int S, c
 
 }  // namespace
 
-// Tile rows for a row bound and output width (bf16).  Measured on MI355X over
-// the projection shapes at 32..512 rows: the smallest tiles win while they
-// keep the block count moderate (more, shorter blocks balance the CUs
-// better); wide outputs with many rows take 64-row tiles, and the widest
-// (the lm head) 128-row ones.  The tile shape does not change any result:
+namespace {
+
+int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// The register-staged tiles, for row counts where a launch streams weights
+// rather than fills the MFMAs.  Tile rows, measured over the projection shapes
+// at 32..512 rows: the smallest tiles win while they keep the block count
+// moderate (more, shorter blocks balance the CUs better); wide outputs with
+// many rows take 64-row tiles, and the widest at 65-128 rows none of these
+// (0: the direct-to-LDS tiles).  The tile shape does not change any result:
 // every output still accumulates K in the same order.
-int gemm_tile_rows(int dtype, int rows_ub, int N) {
-  if (dtype != 1) return 16;
-  if (rows_ub > 1024) return 256;
-  // the lm head (very wide output) at 256 and 512 rows: 256 x 256 tiles,
-  // 11-15 % faster there than 128 x 128 (slower at 384 and below 256 rows)
-  if (N >= 65536 && rows_ub >= 256 && rows_ub % 256 == 0) return 256;
+int staged_tile_rows(int rows_ub, int N) {
   if (rows_ub <= 16) return 16;
   const int64_t ct = (N + 127) / 128;
   const int64_t c32 = ct * ((rows_ub + 31) / 32), c64 = ct * ((rows_ub + 63) / 64);
-  if (c64 > 2048) return 128;
+  if (c64 > 2048) return rows_ub <= 64 ? 64 : 0;
   if (c32 > 2048 || (rows_ub > 128 && c32 > 600)) return 64;
   return 32;
 }
 
-// Tiles of 256 rows are 256 x 256 (64 x 128 per wave: twice the MFMA work per
-// LDS fragment, which only pays with many blocks).  32-row tiles take 64
-// columns where that measured faster in the rollout (1.5B and 7B group steps,
-// ms per row bucket):
+constexpr int64_t kNoSplitBlocks = 256;   // staged tiles split K below this many output tiles
+
+// 32-row tiles take 64 columns where that measured faster in the rollout (1.5B
+// and 7B group steps, ms per row bucket):
 // * wide outputs (gate/up) at 33-64 rows when 128-column tiles leave fewer
 //   than two blocks per CU (1.5B: 280 blocks -> 560, 644 -> 571 ms; 7B's
 //   592 blocks measured slower at 1,184);
 // * narrow outputs at 17-64 rows, and at 65-128 rows those with K <= 2N (QKV,
-//   O), while the 64-column tiles still number fewer than the engine's
-//   no-split threshold: the same block count then needs half the split-K
-//   factor and the split reduction reads half the partials (1.5B at 64 rows:
-//   QKV + O + down 1096 -> 993 ms; at 128 rows QKV + O 702 -> 643 ms).  7B's
-//   QKV at 128 rows would cross the threshold and run unsplit, 1.6x slower;
+//   O), while the 64-column tiles still number fewer than the no-split
+//   threshold: the same block count then needs half the split-K factor and the
+//   split reduction reads half the partials (1.5B at 64 rows: QKV + O + down
+//   1096 -> 993 ms; at 128 rows QKV + O 702 -> 643 ms).  7B's QKV at 128 rows
+//   would cross the threshold and run unsplit, 1.6x slower;
 // * the unsplit QKV (N > K) at 512 rows and more (1.5B: 512 -> 471 ms).
 // All others 128 columns.  A tile shape that changes the split factor
 // changes where the fp32 split sums are cut, so results move within fp32
 // rounding.
-int gemm_tile_cols(int dtype, int rows_ub, int N, int K) {
-  const int bm = gemm_tile_rows(dtype, rows_ub, N);
-  if (bm == 256) return 256;
-  if (dtype == 1 && bm == 32) {
-    constexpr int64_t kNoSplitBlocks = 256;   // the engine splits K below this many output tiles
+int staged_tile_cols(int bm, int rows_ub, int N, int K) {
+  if (bm == 32) {
     const int64_t row_tiles = (rows_ub + 31) / 32;
     if (N >= 8192)
       return rows_ub > 32 && rows_ub <= 64 && (int64_t)((N + 127) / 128) * row_tiles < 2 * kNoSplitBlocks ? 64 : 128;
@@ -766,33 +955,103 @@ int gemm_tile_cols(int dtype, int rows_ub, int N, int K) {
   return 128;
 }
 
-hipError_t launch_gemm(int dtype, const void* A, int lda, int64_t a_plane, const void* W, int ldw, const int* d_rows,
-                       int rows_ub, int N, int K, int splits, int k_per_split, const GemmEpi& ep, hipStream_t st) {
+// Widths of the direct-to-LDS tiles and the time of one 64-wide K step of a
+// 128-row tile with every CU busy (us, measured at 16384 x 37888 x 3584).
+constexpr int kDmaCols[4] = {128, 192, 256, 320};
+constexpr double kDmaStep[4] = {1.09, 1.40, 1.61, 1.97};
+
+// Tile width and split of a direct-to-LDS launch: the cheapest by rounds of
+// 256 blocks x (steps x step time + 4 us), plus, when K is split, 4 us and the
+// partials' write and read at 8 TB/s for the reduction.  Against measured
+// times (us, model / measured): 512 x 1536 x 8960 256 columns split 10 38 /
+// 38, 192 split 8 40 / 40, 128 split 5 42 / 45; 256 x 3584 x 18944 256 split 9
+// 70 / 74, 192 split 6 84 / 88, 128 split 4 96 / 99; and it ranks the widths
+// as measured at every shape tried unsplit (512 x 17920 x 1536: 320 columns
+// 56 us, 256 79; 256 rows: 192 39, 256 43; 8191 x 1536 x 8960: 192 416, 256
+// 432; 4096 x 768 x 3072: 128 47, 256 69).
+GemmPlan dma_plan(int rows_ub, int N, int K, int max_splits) {
+  GemmPlan best{128, 0, true, 1, K};
+  double best_t = 0.0;
+  const int64_t gy = ceil_div(rows_ub, 128);
+  for (int c = 0; c < 4; ++c) {
+    const int64_t tiles = gy * ceil_div(N, kDmaCols[c]);
+    for (int want = 1; want <= std::max(1, std::min(max_splits, K / 256)); ++want) {
+      const int kps = (int)(ceil_div(ceil_div(K, want), 64) * 64), S = (int)ceil_div(K, kps);
+      double t = (double)ceil_div(tiles * S, 256) * (kps / 64 * kDmaStep[c] + 4.0);
+      if (S > 1) t += 4.0 + (double)S * rows_ub * N / 1e6;
+      if (best.bn == 0 || t < best_t) {
+        best_t = t;
+        best.bn = kDmaCols[c];
+        best.splits = S;
+        best.k_per_split = kps;
+      }
+    }
+  }
+  return best;
+}
+
+}  // namespace
+
+// Which tiles.  Direct-to-LDS tiles (128 rows) above 1024 rows, and below that
+// where a launch has the MFMA work to fill the chip: 10 GFLOP issued above 128
+// rows, 30 at 65-128 (us, direct / staged, reductions included: 512 x 1536 x
+// 8960 38 / 57; 256 rows 27 / 31; 256 x 4608 x 3584 31 / 55; 128 x 3584 x
+// 18944 49 / 81; but 512 x 1536 x 1536 20 / 19 and 128 x 17920 x 1536 35 / 32).
+// Staged tiles split K only while their output tiles leave the chip short of
+// blocks, to about 384 blocks (768 for narrow outputs, whose partials are
+// small), and only as far as the fp32 partials (written once, read once: 8
+// bytes per output element and split) stay within twice the weight bytes or
+// 24 MiB.
+GemmPlan gemm_plan(int dtype, int rows_ub, int N, int K, int max_splits) {
+  if (dtype != 1) return GemmPlan{16, 32, false, 1, K};
+  max_splits = std::max(1, std::min(max_splits, GEMM_MAX_SPLITS));
+  const int bm = staged_tile_rows(rows_ub, N);
+  const double work = 4.0 * rows_ub * N * K;   // both planes
+  if (rows_ub > 1024 || bm == 0 || work >= (rows_ub > 128 ? 10e9 : rows_ub > 64 ? 30e9 : 1e300))
+    return dma_plan(rows_ub, N, K, max_splits);
+  const int bn = staged_tile_cols(bm, rows_ub, N, K);
+  const int64_t blocks = ceil_div(N, bn) * ceil_div(rows_ub, bm);
+  int64_t S = 1;
+  if (blocks < kNoSplitBlocks) S = ceil_div(N >= 8192 ? 384 : 768, blocks);
+  const int64_t budget = std::max<int64_t>(4LL * N * K, 24LL << 20);
+  S = std::max<int64_t>(1, std::min<int64_t>({S, K / 128, budget / (8LL * rows_ub * N), max_splits}));
+  GemmPlan p{bm, bn, false, 1, K};
+  p.k_per_split = (int)(ceil_div(ceil_div(K, S), 64) * 64);
+  p.splits = (int)ceil_div(K, p.k_per_split);
+  return p;
+}
+
+hipError_t launch_gemm(int dtype, const GemmPlan& p, const void* A, int lda, int64_t a_plane, const void* W, int ldw,
+                       const int* d_rows, int rows_ub, int N, int K, const GemmEpi& ep, hipStream_t st) {
   if (rows_ub <= 0) return hipSuccess;
-  if (splits > 1 && !ep.part) return hipErrorInvalidValue;
-  if (splits > GEMM_MAX_SPLITS) return hipErrorInvalidValue;
+  const int S = p.splits, kps = p.k_per_split;
+  if (S < 1 || S > GEMM_MAX_SPLITS || (S > 1 && !ep.part)) return hipErrorInvalidValue;
   if ((ep.mode == GEMM_EPI_SWIGLU || ep.mode == GEMM_EPI_QKV) && N % 32) return hipErrorInvalidValue;
   if (ep.mode == GEMM_EPI_QKV && (ep.hd % 32 || 128 % ep.hd)) return hipErrorInvalidValue;
-  hipError_t e;
   if (dtype == 1) {
-    if (K % BK_MAX || k_per_split % BK_MAX || N % 16) return hipErrorInvalidValue;
-    switch (gemm_tile_rows(dtype, rows_ub, N)) {
-      case 16: e = launch_tiled<16, 128, 1, 2, 1>(A, lda, a_plane, W, ldw, d_rows, rows_ub, N, K, splits, k_per_split, ep, st); break;
-      case 32:
-        if (gemm_tile_cols(dtype, rows_ub, N, K) == 64)
-          e = launch_tiled<32, 64, 1, 2, 1>(A, lda, a_plane, W, ldw, d_rows, rows_ub, N, K, splits, k_per_split, ep, st);
-        else
-          e = launch_tiled<32, 128, 1, 4, 1>(A, lda, a_plane, W, ldw, d_rows, rows_ub, N, K, splits, k_per_split, ep, st);
-        break;
-      case 64: e = launch_tiled<64, 128, 2, 4, 1>(A, lda, a_plane, W, ldw, d_rows, rows_ub, N, K, splits, k_per_split, ep, st); break;
-      case 128: e = launch_tiled<128, 128, 4, 4, 1>(A, lda, a_plane, W, ldw, d_rows, rows_ub, N, K, splits, k_per_split, ep, st); break;
-      default: e = launch_tiled<256, 256, 4, 8, 1>(A, lda, a_plane, W, ldw, d_rows, rows_ub, N, K, splits, k_per_split, ep, st); break;
+    if (K % BK_MAX || kps % BK_MAX || N % 16) return hipErrorInvalidValue;
+    hipError_t e = hipErrorInvalidValue;
+#define RG_TILE(F, ...) e = F<__VA_ARGS__>(A, lda, a_plane, W, ldw, d_rows, rows_ub, N, K, S, kps, ep, st)
+    if (p.dma) {
+      if (p.bn == 128) RG_TILE(launch_dma, 128, 128, 2, 4);
+      else if (p.bn == 192) RG_TILE(launch_dma, 128, 192, 2, 6);
+      else if (p.bn == 256) RG_TILE(launch_dma, 128, 256, 4, 4);
+      else if (p.bn == 320) RG_TILE(launch_dma, 128, 320, 2, 10);
+    } else if (p.bm == 16 && p.bn == 128) {
+      RG_TILE(launch_tiled, 16, 128, 1, 2, 1);
+    } else if (p.bm == 32 && p.bn == 64) {
+      RG_TILE(launch_tiled, 32, 64, 1, 2, 1);
+    } else if (p.bm == 32 && p.bn == 128) {
+      RG_TILE(launch_tiled, 32, 128, 1, 4, 1);
+    } else if (p.bm == 64 && p.bn == 128) {
+      RG_TILE(launch_tiled, 64, 128, 2, 4, 1);
     }
-    if (e != hipSuccess || splits == 1) return e;
-    return launch_split_epilogue(d_rows, rows_ub, N, splits, ep, st);
+#undef RG_TILE
+    if (e != hipSuccess || S == 1) return e;
+    return launch_split_epilogue(d_rows, rows_ub, N, S, ep, st);
   }
   // fp32: 64-row tiles once 16-row ones give every CU two blocks
-  if (splits != 1 || K % 16) return hipErrorInvalidValue;
+  if (S != 1 || K % 16) return hipErrorInvalidValue;
   if ((int64_t)((N + 31) / 32) * ((rows_ub + 15) / 16) > 512)
     return launch_f32<4>((const float*)A, lda, (const float*)W, ldw, d_rows, rows_ub, N, K, ep, st);
   return launch_f32<1>((const float*)A, lda, (const float*)W, ldw, d_rows, rows_ub, N, K, ep, st);

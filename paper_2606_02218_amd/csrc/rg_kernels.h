@@ -45,10 +45,6 @@ bool rg_launch_events_armed();
 // `a_plane`) follow ActOut in rg_device.h: fp32 for fp32 models, hi/lo bf16
 // planes a_plane elements apart for bf16 models.
 
-// Output tile rows / columns launch_gemm uses for a row bound and width N.
-int gemm_tile_rows(int dtype, int rows_ub, int N);
-int gemm_tile_cols(int dtype, int rows_ub, int N, int K);
-
 // Largest split-K factor of a projection.
 constexpr int GEMM_MAX_SPLITS = 32;
 
@@ -71,11 +67,20 @@ struct GemmEpi {
   float* part; int64_t part_stride;       // split partials [S][rows][N] (S > 1)
 };
 
-// y = A W^T over rows < *d_rows with K split `splits` ways (bf16 models: K
-// and k_per_split multiples of 64, N a multiple of 16; fp32 models: K a
-// multiple of 16, one split), then the epilogue ep.
-hipError_t launch_gemm(int dtype, const void* A, int lda, int64_t a_plane, const void* W, int ldw, const int* d_rows,
-                       int rows_ub, int N, int K, int splits, int k_per_split, const GemmEpi& ep, hipStream_t st);
+// Tiles and K split of a projection over at most rows_ub rows: bm x bn output
+// tiles (dma: the direct-to-LDS kernel), K in `splits` pieces of k_per_split.
+struct GemmPlan {
+  int bm, bn;
+  bool dma;
+  int splits, k_per_split;
+};
+GemmPlan gemm_plan(int dtype, int rows_ub, int N, int K, int max_splits);
+
+// y = A W^T over rows < *d_rows by plan p (bf16 models: K a multiple of 64, N
+// of 16; fp32 models: K a multiple of 16), then the epilogue ep.  A's buffer
+// holds rows_ub rows.
+hipError_t launch_gemm(int dtype, const GemmPlan& p, const void* A, int lda, int64_t a_plane, const void* W, int ldw,
+                       const int* d_rows, int rows_ub, int N, int K, const GemmEpi& ep, hipStream_t st);
 
 // x[r] = embed[tok[r]] (fp32), r < *d_rows.  Prefill: tok = prompts.  An id
 // outside [0, V) reads row 0 instead and sets *bad_token = 1.

@@ -1,0 +1,53 @@
+"""Direct-to-LDS projection tiles (more than 1024 rows: 128 rows x 128 to 320
+columns, K steps of 64 through two LDS buffers) against the oracle at their
+edges: row counts one over and one short of a tile, K of one step (64), two and
+many, with and without a K split, widths that end inside a column tile, and
+every epilogue (QKV + RoPE + KV append, SwiGLU, residual, the lm head's store
+through the recompute's row slices).
+
+Tolerance: activations carry 2^-17 relative in hi + lo planes and sums are
+fp32, so what shows is a key or value rounding the other way into the bf16
+cache (2^-8 of that element): about 1e-3 in a log-probability, bound 4e-3.
+"""
+import numpy as np
+import pytest
+
+from oracle.grpo import teacher_forced_logprobs
+from workload import ModelShape, make_weights
+from rg_helpers import make_policy, oracle_for, prompts_to_device
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [ModelShape(2, 64, 1, 1, 64, 64, 144, 1e4, dtype="bf16"),        # K = 64: one step
+          ModelShape(2, 128, 6, 2, 64, 320, 1040, 1e4, dtype="bf16"),     # K = 128, 384, 320
+          ModelShape(1, 512, 4, 1, 128, 1344, 2064, 1e4, dtype="bf16")]   # K split two to five ways
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("si", range(len(SHAPES)))
+@pytest.mark.parametrize("rows", [1025, 1151, 1152, 1153])
+def test_dma_tiles_match_oracle(si, rows):
+    import torch
+    assert torch.cuda.is_available()
+    shape = SHAPES[si]
+    w = make_weights(shape, 4)
+    rng = np.random.default_rng(rows + si)
+    P = 8
+    plens = np.full(P, rows // P)
+    plens[-1] += rows - plens.sum()
+    prompts = [rng.integers(0, shape.vocab - 1, size=int(n)).astype(np.int32) for n in plens]
+    G = [1] * P
+    # completions whose fed-back positions number `rows` in one chunk
+    lengths = (plens + 1).astype(np.int32)
+    max_new = int(lengths.max())
+    tok = rng.integers(0, shape.vocab - 1, size=(P, max_new)).astype(np.int32)
+    pol = make_policy(shape, w, max_seqs=P, max_prompts=P, max_prompt_tokens=rows, max_context=int(plens.max()) + max_new)
+    print(f"dma tiles: shape {si}, {rows} rows", flush=True)
+    got = pol.recompute_logprobs(prompts_to_device(prompts), G, torch.from_numpy(tok).cuda(),
+                                 torch.from_numpy(lengths).cuda()).cpu().numpy()
+    want = teacher_forced_logprobs(oracle_for(shape, w), prompts, G, tok, lengths)
+    valid = np.arange(max_new)[None, :] < lengths[:, None]
+    gap = float(np.max(np.abs(got[valid] - want[valid])))
+    print(f"gap {gap:.2e}", flush=True)
+    assert np.isfinite(got).all() and gap <= 4e-3
+    pol.close()
