@@ -268,7 +268,7 @@ int recompute_logprobs(rg_policy* pol, const int32_t* prompts, const int32_t* pr
  *                   counted tokens and the counted sequences.  All zero when
  *                   nothing is counted; NaN in all four if G is invalid or a
  *                   length lies outside [1, max_new].
- * Two kernels: one wave per sequence sums its terms (fp64) into a 16-byte
+ * Two kernels: one block per sequence sums its terms (fp64) into a 16-byte
  * record of device scratch, then one workgroup adds the records group by
  * group in sequence order; the summation order is fixed, so results are
  * reproducible.  The scratch (16*N bytes) is taken with hipMallocAsync on

@@ -203,81 +203,128 @@ __global__ __launch_bounds__(LP_THREADS) void k_token_logprob(const float* __res
   if (tid == 0) lp[out[r]] = z[tgt[r]] / T - (sm[0] + logf(ss[0]));
 }
 
-// Clipped surrogate, pass 1: one wave per sequence s < N.  Its lanes stride
-// over the sequence's L_s tokens and accumulate, in fp64,
-// min(rho * A_s, clip(rho, 1 - eps_lo, 1 + eps_hi) * A_s), rho = exp(new - old),
-// then the wave sums them (a butterfly: a fixed order).  rec[s] = (sum,
-// clipped tokens); a length outside [1, max_new] writes clipped = -1.
-__global__ __launch_bounds__(256) void k_surrogate_seq(SurrogateArgs a, SurrogateRec* __restrict__ rec) {
-  const int lane = threadIdx.x & 63;
-  const int s = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (s >= a.N) return;
+// Clipped surrogate, pass 1: one block of 256 threads per sequence s < N.  The
+// threads stride over the sequence's L_s tokens, four at a time, and
+// accumulate, in fp64, min(rho * A_s, clip(rho, 1 - eps_lo, 1 + eps_hi) * A_s),
+// rho = exp(new - old); a butterfly per wave and the waves in order make the
+// sum's order fixed.  rec[s] = (sum, or sum / L_s for the sequence mean;
+// clipped tokens; L_s); a length outside [1, max_new] writes clipped = -1.
+// Bound by latency: a sequence of 4096 tokens is 64 dependent trips for one
+// wave (36 us at 512 sequences), 4 for a block.
+constexpr int SURR_THREADS = 256;
+
+__global__ __launch_bounds__(SURR_THREADS) void k_surrogate_seq(SurrogateArgs a, SurrogateRec* __restrict__ rec) {
+  __shared__ double s_acc[SURR_THREADS / 64];
+  __shared__ int s_clip[SURR_THREADS / 64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int s = blockIdx.x;
   const int L = a.lengths[s];
+  const double A = (double)a.adv[s];
   if (L < 1 || L > a.max_new) {
-    if (lane == 0) rec[s] = SurrogateRec{0.0, -1, 0};
+    if (tid == 0) rec[s] = SurrogateRec{0.0, -1, 0};
     return;
   }
-  const double A = (double)a.adv[s];
-  const int64_t row = (int64_t)s * a.max_new;
+  const float* nw = a.new_lp + (int64_t)s * a.max_new;
+  const float* od = a.old_lp + (int64_t)s * a.max_new;
+  const double lo = 1.0 - a.eps_lo, hi = 1.0 + a.eps_hi;
   double acc = 0.0;
   int clips = 0;
-  for (int i = lane; i < L; i += 64) {
-    const double rho = exp((double)a.new_lp[row + i] - (double)a.old_lp[row + i]);
-    const double un = rho * A;
-    const double cl = fmin(fmax(rho, 1.0 - a.eps_lo), 1.0 + a.eps_hi) * A;
-    acc += fmin(un, cl);
-    clips += cl < un;
+  for (int i0 = tid; i0 < L; i0 += 4 * SURR_THREADS) {
+    float x[4], y[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {   // every load issued before the first use; past the end the first token again
+      const int i = i0 + u * SURR_THREADS < L ? i0 + u * SURR_THREADS : 0;
+      x[u] = nw[i];
+      y[u] = od[i];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (i0 + u * SURR_THREADS < L) {
+        const double rho = exp((double)x[u] - (double)y[u]);
+        const double un = rho * A;
+        const double cl = fmin(fmax(rho, lo), hi) * A;
+        acc += fmin(un, cl);
+        clips += cl < un;
+      }
+    }
   }
   acc = wave_sum_d(acc);
+#pragma unroll
   for (int o = 32; o > 0; o >>= 1) clips += __shfl_xor(clips, o, 64);
-  if (lane == 0) rec[s] = SurrogateRec{acc, clips, 0};
+  if (lane == 0) {
+    s_acc[tid >> 6] = acc;
+    s_clip[tid >> 6] = clips;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    acc = s_acc[0];
+    clips = s_clip[0];
+#pragma unroll
+    for (int w = 1; w < SURR_THREADS / 64; ++w) {
+      acc += s_acc[w];
+      clips += s_clip[w];
+    }
+    rec[s] = SurrogateRec{a.mode == 0 ? acc : acc / (double)L, clips, L};
+  }
 }
 
-// Pass 2, one block of 1024 threads: the group partition (each G[p] >= 1,
-// sum N), then thread t takes groups t, t + 1024, ... whose keep flag is set
-// and adds their members' records in sequence order; the per-thread totals
-// are combined by a butterfly within each wave and the wave totals in wave
-// order, so the result does not depend on timing.  out = (loss, clipped
+// Pass 2, one block: the group partition (each G[p] >= 1, sum N), then thread
+// t takes groups t, t + blockDim, ... whose keep flag is set and adds their
+// members' records in sequence order, eight loads at a time; the per-thread
+// totals are combined by a butterfly within each wave and the wave totals in
+// wave order, so the result does not depend on timing.  out = (loss, clipped
 // fraction, tokens, sequences); NaN in all four for an invalid partition or
 // a length outside [1, max_new], zeros when nothing is counted.
 __global__ __launch_bounds__(1024) void k_surrogate_reduce(SurrogateArgs a, const SurrogateRec* __restrict__ rec) {
   __shared__ int lds[17];
-  __shared__ double w_tok[16], w_seq[16];
+  __shared__ double w_sum[16];
   __shared__ long long w_ntok[16], w_nclip[16];
   __shared__ int w_nseq[16], w_bad[16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
-  if (!groups_valid(a.G, a.P, a.N)) {
+  const bool one = a.P <= (int)blockDim.x;
+  const int keep1 = one && tid < a.P && a.keep ? a.keep[tid] : 1;   // in flight beside G
+  int g1 = 0, o1 = 0;
+  const bool ok = one ? group_offsets(a.G, a.P, a.N, g1, o1) : groups_valid(a.G, a.P, a.N);
+  if (!ok) {
     if (tid < 4) a.out[tid] = __longlong_as_double(0x7FF8000000000000ll);
     return;
   }
-  double tok_sum = 0.0, seq_sum = 0.0;
+  double sum = 0.0;
   long long n_tok = 0, n_clip = 0;
   int n_seq = 0, bad = 0;
   int carry = 0;
   for (int base = 0; base < a.P; base += blockDim.x) {
     const int p = base + tid;
-    const int g = p < a.P ? a.G[p] : 0;
-    int t;
-    const int o = block_excl_scan(g, lds, &t) + carry;
-    if (p < a.P && (!a.keep || a.keep[p] != 0)) {
-      for (int s = o; s < o + g; ++s) {
-        const SurrogateRec r = rec[s];
-        if (r.clips < 0) {
-          bad = 1;
-          continue;
+    int g = g1, o = o1, kp = keep1;
+    if (!one) {
+      g = p < a.P ? a.G[p] : 0;
+      kp = p < a.P && a.keep ? a.keep[p] : 1;
+      int t;
+      o = block_excl_scan(g, lds, &t) + carry;
+      carry += t;
+    }
+    if (p < a.P && kp != 0) {
+      for (int s = o; s < o + g; s += 8) {
+        SurrogateRec r[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) r[j] = rec[min(s + j, o + g - 1)];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          if (s + j >= o + g) break;
+          if (r[j].clips < 0) {
+            bad = 1;
+            continue;
+          }
+          sum += r[j].acc;
+          n_tok += r[j].len;
+          n_clip += r[j].clips;
+          n_seq += 1;
         }
-        const int L = a.lengths[s];
-        tok_sum += r.acc;
-        seq_sum += r.acc / (double)L;
-        n_tok += L;
-        n_clip += r.clips;
-        n_seq += 1;
       }
     }
-    carry += t;
   }
-  tok_sum = wave_sum_d(tok_sum);
-  seq_sum = wave_sum_d(seq_sum);
+  sum = wave_sum_d(sum);
+#pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     n_tok += __shfl_xor(n_tok, o, 64);
     n_clip += __shfl_xor(n_clip, o, 64);
@@ -285,23 +332,22 @@ __global__ __launch_bounds__(1024) void k_surrogate_reduce(SurrogateArgs a, cons
     bad |= __shfl_xor(bad, o, 64);
   }
   if (lane == 0) {
-    w_tok[wave] = tok_sum; w_seq[wave] = seq_sum; w_ntok[wave] = n_tok; w_nclip[wave] = n_clip;
-    w_nseq[wave] = n_seq; w_bad[wave] = bad;
+    w_sum[wave] = sum; w_ntok[wave] = n_tok; w_nclip[wave] = n_clip; w_nseq[wave] = n_seq; w_bad[wave] = bad;
   }
   __syncthreads();
   if (tid == 0) {
-    double ts = 0.0, qs = 0.0;
+    double ts = 0.0;
     long long nt = 0, nc = 0;
     int ns = 0, nb = 0;
     for (int w = 0; w < nw; ++w) {
-      ts += w_tok[w]; qs += w_seq[w]; nt += w_ntok[w]; nc += w_nclip[w]; ns += w_nseq[w]; nb |= w_bad[w];
+      ts += w_sum[w]; nt += w_ntok[w]; nc += w_nclip[w]; ns += w_nseq[w]; nb |= w_bad[w];
     }
     if (nb) {
       for (int i = 0; i < 4; ++i) a.out[i] = __longlong_as_double(0x7FF8000000000000ll);
     } else if (ns == 0) {
       for (int i = 0; i < 4; ++i) a.out[i] = 0.0;
     } else {
-      const double agg = a.mode == 0 ? ts / (double)nt : qs / (double)ns;
+      const double agg = ts / (a.mode == 0 ? (double)nt : (double)ns);
       a.out[0] = -agg;
       a.out[1] = (double)nc / (double)nt;
       a.out[2] = (double)nt;
@@ -368,7 +414,8 @@ hipError_t surrogate_static_scratch(SurrogateRec** out) {
 
 hipError_t launch_surrogate(const SurrogateArgs& a, SurrogateRec* rec, hipStream_t st) {
   if (a.N < 1 || !rec) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_surrogate_seq, dim3((a.N + 3) / 4), dim3(256), 0, st, a, rec);
-  hipLaunchKernelGGL(k_surrogate_reduce, dim3(1), dim3(1024), 0, st, a, (const SurrogateRec*)rec);
+  hipLaunchKernelGGL(k_surrogate_seq, dim3(a.N), dim3(SURR_THREADS), 0, st, a, rec);
+  const int nt = a.P >= 1024 ? 1024 : (a.P + 63) / 64 * 64;   // a thread per group
+  hipLaunchKernelGGL(k_surrogate_reduce, dim3(1), dim3(nt), 0, st, a, (const SurrogateRec*)rec);
   return hipGetLastError();
 }

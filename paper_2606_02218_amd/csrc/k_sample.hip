@@ -337,17 +337,69 @@ __global__ void k_setup_out(int32_t* tokens, float* logprobs, int64_t n) {
 }
 
 // ------------------------------------------------------------------ advantage
-// One block of 1024 threads.  Pass 1 validates G (every entry >= 1, sum = N).
-// Pass 2 walks tiles of 1024 groups: the block scan gives each group its
-// offset, then each wave takes groups in turn and reduces them in fp64.
+// Small groups leave these kernels bound by the length of their load chain (G,
+// then rewards), not by work: segments of SW lanes take a group each, so that
+// groups of 16 run four to a wave, and up to a block's width of groups are
+// validated and placed by one load and one barrier (group_offsets).  Wider
+// sets of groups walk tiles of 1024.
+
+// Advantages of groups k = seg, seg + nseg, ... < ng whose offsets are offs[k]
+// .. offs[k + 1]: mean and deviation in fp64 over a segment of SW lanes.
+template <int SW>
+__device__ __forceinline__ void advantage_tile(const float* __restrict__ rewards, const int* offs, int ng, double eps,
+                                               int ddof, float* __restrict__ adv) {
+  const int tid = threadIdx.x, sl = tid % SW, nseg = blockDim.x / SW;
+  const uint64_t mask = SW == 64 ? ~0ull : ((1ull << SW) - 1) << ((tid & 63) / SW * SW);
+  for (int k0 = 0; k0 < ng; k0 += nseg) {
+    const int k = k0 + tid / SW;
+    const bool live = k < ng;   // whole segments; the others idle through the shuffles
+    const int o0 = live ? offs[k] : 0, gs = live ? offs[k + 1] - o0 : 0;
+    const float r0 = live ? rewards[o0] : 0.f;
+    const float v0 = sl < gs ? rewards[o0 + sl] : 0.f;   // the lane's first member stays in a register
+    double sum = 0.0;
+    int diff = 0;
+    for (int i = sl; i < gs; i += SW) {
+      const float v = i == sl ? v0 : rewards[o0 + i];
+      sum += (double)v;
+      diff |= (v != r0);
+    }
+#pragma unroll
+    for (int o = SW / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    const bool varies = (__ballot(diff) & mask) != 0;
+    const double mu = sum / (double)max(gs, 1);
+    double sq = 0.0;
+    for (int i = sl; i < gs; i += SW) {
+      const double dv = (double)(i == sl ? v0 : rewards[o0 + i]) - mu;
+      sq += dv * dv;
+    }
+#pragma unroll
+    for (int o = SW / 2; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
+    const bool flat = !varies || gs - ddof <= 0;
+    const double sigma = flat ? 0.0 : sqrt(sq / (double)(gs - ddof));
+    for (int i = sl; i < gs; i += SW)
+      adv[o0 + i] = flat ? 0.f : (float)(((double)(i == sl ? v0 : rewards[o0 + i]) - mu) / (sigma + eps));
+  }
+}
+
+template <int SW>
 __global__ __launch_bounds__(1024) void k_group_advantage(const float* __restrict__ rewards,
                                                           const int32_t* __restrict__ G, int P, int N, double eps,
                                                           int ddof, float* __restrict__ adv) {
   __shared__ int lds[17];
   __shared__ int offs[1025];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
-  if (!groups_valid(G, P, N)) {
+  const int tid = threadIdx.x;
+  const bool one = P <= (int)blockDim.x;
+  int g1 = 0, o1 = 0;
+  const bool ok = one ? group_offsets(G, P, N, g1, o1) : groups_valid(G, P, N);
+  if (!ok) {
     for (int i = tid; i < N; i += blockDim.x) adv[i] = __int_as_float(0x7FC00000);
+    return;
+  }
+  if (one) {
+    if (tid < P) offs[tid] = o1;
+    if (tid == 0) offs[P] = N;
+    __syncthreads();
+    advantage_tile<SW>(rewards, offs, P, eps, ddof, adv);
     return;
   }
   int carry = 0;
@@ -357,35 +409,9 @@ __global__ __launch_bounds__(1024) void k_group_advantage(const float* __restric
     int t;
     const int o = block_excl_scan(g, lds, &t) + carry;
     offs[tid] = o;
-    if (tid == blockDim.x - 1) offs[blockDim.x] = o + g;
+    if (tid == (int)blockDim.x - 1) offs[blockDim.x] = o + g;
     __syncthreads();
-    const int ng = min((int)blockDim.x, P - base);
-    for (int k = wave; k < ng; k += nw) {
-      const int o0 = offs[k], gs = offs[k + 1] - offs[k];
-      const float r0 = rewards[o0];
-      double sum = 0.0;
-      int diff = 0;
-      for (int i = lane; i < gs; i += 64) {
-        const float v = rewards[o0 + i];
-        sum += (double)v;
-        diff |= (v != r0);
-      }
-      sum = wave_sum_d(sum);
-      const bool varies = __any(diff);
-      if (!varies || gs - ddof <= 0) {
-        for (int i = lane; i < gs; i += 64) adv[o0 + i] = 0.f;
-        continue;
-      }
-      const double mu = sum / (double)gs;
-      double sq = 0.0;
-      for (int i = lane; i < gs; i += 64) {
-        const double dv = (double)rewards[o0 + i] - mu;
-        sq += dv * dv;
-      }
-      sq = wave_sum_d(sq);
-      const double sigma = sqrt(sq / (double)(gs - ddof));
-      for (int i = lane; i < gs; i += 64) adv[o0 + i] = (float)(((double)rewards[o0 + i] - mu) / (sigma + eps));
-    }
+    advantage_tile<SW>(rewards, offs, min((int)blockDim.x, P - base), eps, ddof, adv);
     carry += t;
     __syncthreads();
   }
@@ -428,33 +454,37 @@ hipError_t launch_setup(const SetupArgs& a, hipStream_t st) {
 }
 
 // ------------------------------------------------------------------ group length statistics
-// One 256-thread block per group: the group's offset is the sum of the sizes
-// before it; its lengths are ranked in LDS (rank = smaller values plus equal
-// values earlier in the group) and placed in sorted order.
+// One block per group: the group's offset is the sum of the sizes before it;
+// its lengths are ranked in LDS (rank = smaller values plus equal values
+// earlier in the group) and placed in sorted order.  One wave per group while
+// groups average at most 64 (no barrier leaves the wave: 7.1 -> 4 us at 8 to 32
+// groups), else four.
 __global__ __launch_bounds__(256) void k_group_stats(const int32_t* __restrict__ lengths, const int32_t* __restrict__ G,
                                                      int P, int N, double tau, float* __restrict__ stats) {
   constexpr int GMAX = 1024;
   __shared__ int s_len[GMAX], s_sorted[GMAX];
-  __shared__ unsigned long long s_off;
-  const int p = blockIdx.x, tid = threadIdx.x;
-  if (tid == 0) s_off = 0;
-  __syncthreads();
-  unsigned long long part = 0;
-  for (int i = tid; i < p; i += blockDim.x) part += (unsigned long long)(long long)G[i];
-  atomicAdd(&s_off, part);   // integer sum modulo 2^64: order-independent, exact for int32 sizes
-  __syncthreads();
-  const long long off = (long long)s_off;
+  __shared__ long long s_off[4];
+  const int p = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
   const int g = G[p];
+  long long part = 0;   // integer sum: order-independent, exact for int32 sizes
+  for (int i = tid; i < p; i += nt) part += (long long)G[i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
+  if ((tid & 63) == 0) s_off[tid >> 6] = part;
+  __syncthreads();
+  long long off = 0;
+  for (int w = 0; w < nt >> 6; ++w) off += s_off[w];
   float* out = stats + 4 * (int64_t)p;
   if (g < 1 || g > GMAX || off < 0 || off + g > N) {
     if (tid < 4) out[tid] = NAN;
     return;
   }
-  for (int i = tid; i < g; i += blockDim.x) s_len[i] = lengths[off + i];
+  for (int i = tid; i < g; i += nt) s_len[i] = lengths[off + i];
   __syncthreads();
-  for (int i = tid; i < g; i += blockDim.x) {
+  for (int i = tid; i < g; i += nt) {
     const int v = s_len[i];
     int rank = 0;
+#pragma unroll 4
     for (int j = 0; j < g; ++j) {
       const int u = s_len[j];
       rank += (u < v) || (u == v && j < i);
@@ -480,53 +510,101 @@ __global__ __launch_bounds__(256) void k_group_stats(const int32_t* __restrict__
 hipError_t launch_group_stats(const int32_t* lengths, const int32_t* G, int P, int N, double tau, float* stats,
                               hipStream_t st) {
   if (P < 1) return hipSuccess;
-  hipLaunchKernelGGL(k_group_stats, dim3(P), dim3(256), 0, st, lengths, G, P, N, tau, stats);
+  hipLaunchKernelGGL(k_group_stats, dim3(P), dim3(N / P <= 64 ? 64 : 256), 0, st, lengths, G, P, N, tau, stats);
   return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ zero-variance filter
-// One block of 1024 threads.  Validates G as the advantage does; then, per
-// tile of 1024 groups, the block scan gives each group its offset, one thread
-// per group compares its rewards with the first one (exact fp32 equality),
-// and a second scan compacts the ids of the groups that vary.  n_kept[0] =
-// number of kept groups, or -1 when G is invalid (nothing else written).
+// One block.  Validates G as the advantage does; then a segment of SW lanes
+// per group compares its rewards with the first one (exact fp32 equality) and
+// a scan compacts the ids of the groups that vary.  n_kept[0] = number of kept
+// groups, or -1 when G is invalid (nothing else written).
+template <int SW>
+__device__ __forceinline__ void filter_tile(const float* __restrict__ rewards, const int* offs, int ng, int* var) {
+  const int tid = threadIdx.x, sl = tid % SW, nseg = blockDim.x / SW;
+  const uint64_t mask = SW == 64 ? ~0ull : ((1ull << SW) - 1) << ((tid & 63) / SW * SW);
+  for (int k0 = 0; k0 < ng; k0 += nseg) {
+    const int k = k0 + tid / SW;
+    const bool live = k < ng;
+    const int o0 = live ? offs[k] : 0, gs = live ? offs[k + 1] - o0 : 0;
+    const float r0 = live ? rewards[o0] : 0.f;
+    int diff = 0;
+    for (int i = sl; i < gs; i += SW) diff |= i > 0 && rewards[o0 + i] != r0;
+    const bool varies = (__ballot(diff) & mask) != 0;
+    if (live && sl == 0) var[k] = varies;
+  }
+}
+
+template <int SW>
 __global__ __launch_bounds__(1024) void k_group_filter(const float* __restrict__ rewards, const int32_t* __restrict__ G,
                                                       int P, int N, int32_t* __restrict__ keep,
                                                       int32_t* __restrict__ kept_ids, int32_t* __restrict__ n_kept) {
   __shared__ int lds[17];
+  __shared__ int offs[1025], var[1024];
   const int tid = threadIdx.x;
-  if (!groups_valid(G, P, N)) {
+  const bool one = P <= (int)blockDim.x;
+  int g1 = 0, o1 = 0;
+  const bool ok = one ? group_offsets(G, P, N, g1, o1) : groups_valid(G, P, N);
+  if (!ok) {
     if (tid == 0) n_kept[0] = -1;
     return;
   }
   int carry = 0, kcarry = 0;
   for (int base = 0; base < P; base += blockDim.x) {
     const int p = base + tid;
-    const int g = p < P ? G[p] : 0;
-    int t, kt;
-    const int o = block_excl_scan(g, lds, &t) + carry;
-    int varies = 0;
-    if (p < P) {
-      const float r0 = rewards[o];
-      for (int i = 1; i < g && !varies; ++i) varies = rewards[o + i] != r0;
-      keep[p] = varies;
+    if (one) {
+      if (tid < P) offs[tid] = o1;
+      if (tid == 0) offs[P] = N;
+    } else {
+      const int g = p < P ? G[p] : 0;
+      int t;
+      const int o = block_excl_scan(g, lds, &t) + carry;
+      offs[tid] = o;
+      if (tid == (int)blockDim.x - 1) offs[blockDim.x] = o + g;
+      carry += t;
     }
+    __syncthreads();
+    filter_tile<SW>(rewards, offs, min((int)blockDim.x, P - base), var);
+    __syncthreads();
+    const int varies = p < P ? var[tid] : 0;
+    int kt;
     const int k = block_excl_scan(varies, lds, &kt) + kcarry;
+    if (p < P) keep[p] = varies;
     if (varies) kept_ids[k] = p;
-    carry += t;
     kcarry += kt;
+    __syncthreads();
   }
   if (tid == 0) n_kept[0] = kcarry;
 }
 
+namespace {
+// Lanes per group (16 to 64, at least the average size) and block threads (a
+// segment per group up to 1024 threads, at least P so that one load covers G).
+int group_lanes(int P, int N) { return N / P <= 16 ? 16 : N / P <= 32 ? 32 : 64; }
+int group_threads(int P, int lanes) {
+  const int64_t t = (int64_t)P * lanes;
+  return (int)((t < 64 ? 64 : t > 1024 ? 1024 : t) + 63) / 64 * 64;
+}
+}  // namespace
+
+#define RG_GROUP_LAUNCH(K, ...)                                                                               \
+  do {                                                                                                        \
+    const int lanes = group_lanes(P, N);                                                                      \
+    const dim3 nt(group_threads(P, lanes));                                                                   \
+    if (lanes == 16) hipLaunchKernelGGL(K<16>, dim3(1), nt, 0, st, __VA_ARGS__);                              \
+    else if (lanes == 32) hipLaunchKernelGGL(K<32>, dim3(1), nt, 0, st, __VA_ARGS__);                         \
+    else hipLaunchKernelGGL(K<64>, dim3(1), nt, 0, st, __VA_ARGS__);                                          \
+  } while (0)
+
 hipError_t launch_group_filter(const float* rewards, const int32_t* G, int P, int N, int32_t* keep, int32_t* kept_ids,
                                int32_t* n_kept, hipStream_t st) {
-  hipLaunchKernelGGL(k_group_filter, dim3(1), dim3(1024), 0, st, rewards, G, P, N, keep, kept_ids, n_kept);
+  RG_GROUP_LAUNCH(k_group_filter, rewards, G, P, N, keep, kept_ids, n_kept);
   return hipGetLastError();
 }
 
 hipError_t launch_group_advantage(const float* rewards, const int32_t* G, int P, int N, float eps, int ddof,
                                   float* adv, hipStream_t st) {
-  hipLaunchKernelGGL(k_group_advantage, dim3(1), dim3(1024), 0, st, rewards, G, P, N, (double)eps, ddof, adv);
+  RG_GROUP_LAUNCH(k_group_advantage, rewards, G, P, N, (double)eps, ddof, adv);
   return hipGetLastError();
 }
+#undef RG_GROUP_LAUNCH

@@ -181,3 +181,36 @@ static __device__ bool groups_valid(const int32_t* __restrict__ G, int P, int N)
   __syncthreads();
   return ok;
 }
+
+// Group sizes of a block that covers them (P <= blockDim.x): thread p gets G[p]
+// (0 past P) and its group's offset; true when every G[p] >= 1 and sum(G) == N
+// (64-bit sums, as in groups_valid; offsets mean nothing otherwise).  One load
+// and one barrier, where groups_valid and a tile loop load G twice and take
+// eight.  Block-wide: every thread of the block calls it once.
+static __device__ bool group_offsets(const int32_t* __restrict__ G, int P, int N, int& g, int& off) {
+  __shared__ long long s_tot[16];
+  __shared__ int s_badw[16];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, nw = blockDim.x >> 6;
+  g = tid < P ? G[tid] : 0;
+  long long x = g;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const long long y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  const bool bad = __any(tid < P && g < 1);
+  if (lane == 63) {
+    s_tot[w] = x;
+    s_badw[w] = bad;
+  }
+  __syncthreads();
+  long long base = 0, total = 0;
+  int any_bad = 0;
+  for (int i = 0; i < nw; ++i) {
+    if (i < w) base += s_tot[i];
+    total += s_tot[i];
+    any_bad |= s_badw[i];
+  }
+  off = (int)(base + x - g);
+  return !any_bad && total == (long long)N;
+}

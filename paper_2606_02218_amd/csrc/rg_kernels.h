@@ -300,13 +300,13 @@ struct SurrogateArgs {
   double eps_lo, eps_hi;
   double* out;
 };
-// Per-sequence record of the clipped surrogate's first pass (16 bytes):
-// the fp64 sum of the sequence's terms and its clipped-token count (-1 for a
-// length outside [1, max_new]).
+// Per-sequence record of the clipped surrogate's first pass (16 bytes): the
+// fp64 sum of the sequence's terms (their mean in the sequence-mean mode), its
+// clipped-token count (-1 for a length outside [1, max_new]) and its length.
 struct SurrogateRec {
   double acc;
   int32_t clips;
-  int32_t pad;
+  int32_t len;
 };
 static_assert(sizeof(SurrogateRec) == 16, "surrogate record layout");
 // Two launches: per-sequence records into rec [N] (device scratch), then one
