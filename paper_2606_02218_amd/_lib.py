@@ -22,7 +22,7 @@ EXPORTS = ["rg_last_error", "rg_policy_create", "rg_policy_destroy", "rg_policy_
            "group_advantage", "rg_philox_blocks", "rg_gumbel_bits", "rg_hbm_probe", "rg_step_history", "rg_kernel_times",
            "sagc_init", "sagc_group_stats", "sagc_step", "sagc_beta_draw", "group_filter",
            "recompute_logprobs", "grpo_surrogate", "rg_decode_attention_chunks", "rg_phase_times",
-           "grpo_surrogate_noalloc"]
+           "grpo_surrogate_noalloc", "grpo_surrogate_scratch"]
 SAGC_MAX_SIZES = 8
 
 
@@ -133,6 +133,7 @@ def load_library():
     lib.rg_decode_attention_chunks.argtypes = [C.c_int32, C.c_int32, C.c_int32]
     lib.rg_decode_attention_chunks.restype = C.c_int32
     lib.grpo_surrogate_noalloc.argtypes = lib.grpo_surrogate.argtypes
+    lib.grpo_surrogate_scratch.argtypes = lib.grpo_surrogate.argtypes + [C.c_void_p]
     lib.sagc_init.argtypes = [C.POINTER(sagc_config), C.POINTER(sagc_state)]
     lib.sagc_group_stats.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_double, C.c_void_p,
                                      C.c_void_p]
@@ -155,8 +156,11 @@ def _check(rc: int):
 
 def _stream_ptr(stream=None) -> int:
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    # the current stream's handle without building a Stream object (2.7 us, as
+    # much as a kernel launch; four of them in the calls after a rollout)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t) -> int:
@@ -402,9 +406,17 @@ def grpo_surrogate(new_lp, old_lp, adv, lengths, G_dev, eps_lo: float = 0.2, eps
     _gpu(new_lp=new_lp, old_lp=old_lp, adv=adv, lengths=lengths, G=G_dev, keep=keep, out=out)
     if out is None:
         out = torch.empty(4, dtype=torch.float64, device=new_lp.device)
-    fn = lib.grpo_surrogate_noalloc if noalloc else lib.grpo_surrogate
-    _check(fn(_ptr(new_lp), _ptr(old_lp), _ptr(adv), _ptr(lengths), _ptr(G_dev), int(G_dev.numel()), N, max_new,
-              _ptr(keep), float(eps_lo), float(eps_hi), LOSS_MODES[mode], _ptr(out), _stream_ptr(stream)))
+    args = (_ptr(new_lp), _ptr(old_lp), _ptr(adv), _ptr(lengths), _ptr(G_dev), int(G_dev.numel()), N, max_new,
+            _ptr(keep), float(eps_lo), float(eps_hi), LOSS_MODES[mode], _ptr(out))
+    if noalloc:
+        _check(lib.grpo_surrogate_noalloc(*args, _stream_ptr(stream)))
+    elif stream is None and new_lp.device.index == torch.cuda.current_device():
+        # on the current stream the per-sequence records come from torch's
+        # allocator, which hands the block out again only behind these kernels
+        scratch = torch.empty(2 * N, dtype=torch.float64, device=new_lp.device)
+        _check(lib.grpo_surrogate_scratch(*args, _ptr(scratch), _stream_ptr()))
+    else:
+        _check(lib.grpo_surrogate(*args, _stream_ptr(stream)))
     return out
 
 

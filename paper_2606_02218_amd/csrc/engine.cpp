@@ -1061,6 +1061,20 @@ int grpo_surrogate(const float* new_lp, const float* old_lp, const float* adv, c
   return RG_OK;
 }
 
+int grpo_surrogate_scratch(const float* new_lp, const float* old_lp, const float* adv, const int32_t* lengths,
+                           const int32_t* G, int32_t P, int32_t N, int32_t max_new, const int32_t* keep,
+                           double eps_lo, double eps_hi, int32_t mode, double* out, void* scratch, void* stream) {
+  SurrogateArgs sa;
+  int rc = surrogate_args("grpo_surrogate_scratch", new_lp, old_lp, adv, lengths, G, P, N, max_new, keep, eps_lo,
+                          eps_hi, mode, out, &sa);
+  if (rc) return rc;
+  if (!scratch || (uintptr_t)scratch % 16)
+    return fail(RG_EINVAL, "grpo_surrogate_scratch: scratch is NULL or not 16-byte aligned");
+  const hipError_t e = launch_surrogate(sa, (SurrogateRec*)scratch, (hipStream_t)stream);
+  if (e != hipSuccess) return fail(RG_EHIP, std::string("grpo_surrogate_scratch launch: ") + hipGetErrorString(e));
+  return RG_OK;
+}
+
 int grpo_surrogate_noalloc(const float* new_lp, const float* old_lp, const float* adv, const int32_t* lengths,
                            const int32_t* G, int32_t P, int32_t N, int32_t max_new, const int32_t* keep,
                            double eps_lo, double eps_hi, int32_t mode, double* out, void* stream) {

@@ -1,0 +1,45 @@
+"""grpo_surrogate_scratch (per-sequence records in the caller's memory) equals
+grpo_surrogate bit for bit, refuses a missing or misaligned scratch on the
+host, and the binding gives the same result on the current stream (scratch from
+torch's allocator), and on a given stream."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N,T,mode", [(1, 1, "token"), (5, 255, "seq"), (64, 1025, "token"), (700, 9, "seq")])
+def test_scratch_surrogate_equals_the_allocating_one(N, T, mode):
+    import torch
+    import paper_2606_02218_amd as rg
+    from paper_2606_02218_amd import _lib
+    lib = rg.load_library()
+    rng = np.random.default_rng(N + T)
+    L = rng.integers(1, T + 1, size=N).astype(np.int32)
+    old = rng.normal(-3.0, 1.0, (N, T)).astype(np.float32)
+    new = (old + rng.normal(0, 0.2, (N, T))).astype(np.float32)
+    d = [torch.from_numpy(a).cuda() for a in (new, old, rng.normal(size=N).astype(np.float32), L)]
+    G = torch.tensor([N], dtype=torch.int32, device="cuda")
+    want = torch.empty(4, dtype=torch.float64, device="cuda")
+    print(f"surrogate scratch: N {N}, T {T}, {mode}", flush=True)
+    a = [t.data_ptr() for t in d] + [G.data_ptr(), 1, N, T, 0, 0.2, 0.28, _lib.LOSS_MODES[mode], want.data_ptr()]
+    assert lib.grpo_surrogate(*a, _lib._stream_ptr()) == _lib.RG_OK
+    got = rg.grpo_surrogate(*d, G, eps_lo=0.2, eps_hi=0.28, mode=mode)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    other = rg.grpo_surrogate(*d, G, eps_lo=0.2, eps_hi=0.28, mode=mode, stream=side)
+    torch.cuda.synchronize()
+    w = want.cpu().numpy()
+    assert np.array_equal(got.cpu().numpy(), w) and np.array_equal(other.cpu().numpy(), w)
+
+
+def test_scratch_surrogate_refuses_bad_scratch():
+    import paper_2606_02218_amd as rg
+    from paper_2606_02218_amd import _lib
+    lib = rg.load_library()
+    p = [C.c_void_p(256 * (i + 1)) for i in range(6)]
+    for bad in (None, C.c_void_p(8)):
+        rc = lib.grpo_surrogate_scratch(p[0], p[1], p[2], p[3], p[4], 1, 4, 8, None, 0.2, 0.2, 0, p[5], bad, None)
+        assert rc == _lib.RG_EINVAL and b"scratch" in lib.rg_last_error()
