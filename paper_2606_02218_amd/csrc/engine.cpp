@@ -381,6 +381,11 @@ int sample_slices(int rows_ub) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(RG_SAMPLE_SLICES_MAX, ceil_div(4096, std::max(1, rows_ub))));
 }
 
+// The first layer's attention norm, into abuf.
+NormArgs first_norm(const rg_policy* pol) {
+  return NormArgs{pol->g_attn[0], pol->cfg.rms_eps, ActOut{pol->abuf, pol->a_plane}};
+}
+
 // Every kernel of one decode step (t >= 1, read on the device from state[8]).
 int enqueue_step(rg_policy* pol, hipStream_t st, int rows_ub, int ctx_max, SampleArgs sm, const CompactArgs& ca,
                  const PrefixPass* pre) {
@@ -388,13 +393,12 @@ int enqueue_step(rg_policy* pol, hipStream_t st, int rows_ub, int ctx_max, Sampl
   int rc;
   LAUNCH(RG_K_EMBED, launch_decode_rows(pol->dtype, pol->w_embed, pol->d, pol->act_seq, pol->act_tok, pol->seq_grp,
                                         pol->plen, pol->state + 8, pre ? 1 : 0, pol->row_tab, pol->row_pos,
-                                        pol->row_beg, pol->x, pol->state, rows_ub, st));
-  LAUNCH(RG_K_RMSNORM, launch_rmsnorm(pol->dtype, pol->x, pol->g_attn[0], pol->d, pol->cfg.rms_eps, pol->abuf,
-                                       pol->a_plane, nullptr, pol->state, rows_ub, st));
+                                        pol->row_beg, pol->x, first_norm(pol), pol->state, rows_ub, st));
   if ((rc = run_layers(pol, st, pol->state, rows_ub, ctx_max, true, pre))) return rc;
   if ((rc = run_head(pol, st, pol->state, rows_ub, nullptr))) return rc;
-  LAUNCH(RG_K_SAMPLE, launch_sample(sm, rows_ub, st));
-  LAUNCH(RG_K_COMPACT, launch_compact(ca, st));
+  const bool pick = rows_ub > COMPACT_PICK_ROWS;   // small batches: the retirement block picks
+  LAUNCH(RG_K_SAMPLE, launch_sample(sm, rows_ub, pick, st));
+  LAUNCH(RG_K_COMPACT, launch_compact(ca, pick ? nullptr : &sm, st));
   return RG_OK;
 }
 
@@ -503,10 +507,8 @@ int prefill_and_fork(rg_policy* pol, hipStream_t st, const GroupRun& gr, const i
   const int* d_pre = pol->state + 5;
   LAUNCH(RG_K_SETUP, launch_prefill_rows(pol->prompt_off, P, N, pol->row_tab, pol->row_pos, pol->row_beg, gr.T_pre,
                                          st));
-  LAUNCH(RG_K_EMBED, launch_embed(pol->dtype, pol->w_embed, pol->d, pol->V, prompts, pol->x, pol->state + 7, d_pre,
-                                  gr.T_pre, st));
-  LAUNCH(RG_K_RMSNORM, launch_rmsnorm(pol->dtype, pol->x, pol->g_attn[0], pol->d, pol->cfg.rms_eps, pol->abuf,
-                                       pol->a_plane, nullptr, d_pre, gr.T_pre, st));
+  LAUNCH(RG_K_EMBED, launch_embed(pol->dtype, pol->w_embed, pol->d, pol->V, prompts, pol->x, first_norm(pol),
+                                  pol->state + 7, d_pre, gr.T_pre, st));
   // bf16 models: attention by row tiles, which stage each K/V block once for
   // all positions and heads of a tile (the row-by-row pass reads a row's whole
   // context per row: 2.5 ms against 0.47 ms a layer for one 8191-token prompt,
@@ -850,6 +852,7 @@ int rollout_group(rg_policy* pol, const int32_t* prompts, const int32_t* prompt_
   ca.free_stack = pol->free_stack; ca.state = pol->state; ca.lengths = lengths; ca.hist_active = pol->hist_active;
   ca.hist_groups = pol->hist_groups; ca.hist_ctx = pol->hist_ctx; ca.hist_cap = pol->hist_cap;
   ca.P = P; ca.grp_row0 = pol->grp_row0; ca.grp_row1 = pol->grp_row1;
+  ca.ring = pol->h_ring; ca.ring_slots = RG_RING;
 
   // shared-prefix attention pass of the decode steps
   PrefixPass pp{};
@@ -863,9 +866,8 @@ int rollout_group(rg_policy* pol, const int32_t* prompts, const int32_t* prompt_
       pol->dtype == RG_DTYPE_BF16 && (o.flags & RG_FLAG_GROUP_PREFIX) && pp.max_pref > 0 ? &pp : nullptr;
 
   auto snapshot = [&](int t) -> int {
-    const int slot = t % RG_RING;
-    HIPTRY(hipMemcpyAsync(pol->h_ring + 8 * slot, pol->state, 8 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HIPTRY(hipEventRecord(pol->ring_ev[slot], st));
+    // the retirement kernel has written the step's state to its ring slot
+    HIPTRY(hipEventRecord(pol->ring_ev[t % RG_RING], st));
     return RG_OK;
   };
 
@@ -874,8 +876,8 @@ int rollout_group(rg_policy* pol, const int32_t* prompts, const int32_t* prompt_
   sm.logits_by_group = 1;
   sm.part = pol->sample_part;
   sm.n_slices = sample_slices(Ni);
-  LAUNCH(RG_K_SAMPLE, launch_sample(sm, Ni, st));
-  LAUNCH(RG_K_COMPACT, launch_compact(ca, st));
+  LAUNCH(RG_K_SAMPLE, launch_sample(sm, Ni, true, st));
+  LAUNCH(RG_K_COMPACT, launch_compact(ca, nullptr, st));
   if ((rc = snapshot(0))) return rc;
   HIPTRY(hipEventSynchronize(pol->ring_ev[0]));
   int known_t = 0, last_t = 0;
@@ -994,6 +996,7 @@ int recompute_logprobs(rg_policy* pol, const int32_t* prompts, const int32_t* pr
   rr.plen = pol->plen; rr.seq_grp = pol->seq_grp; rr.row_tab = pol->row_tab; rr.row_pos = pol->row_pos;
   rr.row_beg = pol->row_beg; rr.row_tgt = pol->row_tgt; rr.row_out = pol->row_out; rr.x = pol->x;
   rr.bad_token = pol->state + 7;
+  rr.norm = first_norm(pol);
   GemmEpi store{};
   store.mode = GEMM_EPI_STORE; store.C = pol->logits; store.ldc = pol->V;
   for (int64_t r0 = 0; r0 < R; r0 += chunk) {
@@ -1001,8 +1004,6 @@ int recompute_logprobs(rg_policy* pol, const int32_t* prompts, const int32_t* pr
     rr.row0 = (int)r0;
     LAUNCH(RG_K_EMBED, launch_recompute_rows(pol->dtype, pol->w_embed, rr, n, st));
     LAUNCH(RG_K_SETUP, launch_fill_i32(d_chunk, 1, n, st));
-    LAUNCH(RG_K_RMSNORM, launch_rmsnorm(pol->dtype, pol->x, pol->g_attn[0], pol->d, pol->cfg.rms_eps, pol->abuf,
-                                         pol->a_plane, nullptr, d_chunk, n, st));
     RowTiles rt{d_tiles, (int)ceil_div(n, tile_rows) + std::min(n, N)};
     if (use_tiles) LAUNCH(RG_K_SETUP, launch_row_tiles(pol->coff, N, (int)r0, n, tile_rows, d_chunk, pol->tile_r0,
                                                        pol->tile_nr, d_tiles, st));

@@ -73,8 +73,9 @@ __global__ __launch_bounds__(1024) void k_reserve(ReserveArgs a) {
 // g belongs to the sequence s with coff[s] <= g < coff[s + 1] and feeds token
 // y_t, t = g - coff[s], at position plen + t; it predicts y_{t+1}, whose
 // log-probability lands in logprobs[s * max_new + t + 1].
-template <typename T>
+template <typename T, int SPLIT>
 __global__ __launch_bounds__(256) void k_recompute_rows(RecomputeRows a, const T* __restrict__ embed) {
+  __shared__ float red[16];
   const int r = blockIdx.x;
   const int g = a.row0 + r;
   int lo = 0, hi = a.n_seq - 1;   // last s with coff[s] <= g: never an empty sequence
@@ -102,8 +103,7 @@ __global__ __launch_bounds__(256) void k_recompute_rows(RecomputeRows a, const T
     a.row_tgt[r] = tgt;
     a.row_out[r] = (int32_t)(o + 1);
   }
-  const T* e = embed + (int64_t)tok * a.d;
-  for (int i = threadIdx.x; i < a.d; i += blockDim.x) a.x[(int64_t)r * a.d + i] = ld_f32<T>(e + i);
+  embed_norm<T, SPLIT>(embed + (int64_t)tok * a.d, a.d, a.x + (int64_t)r * a.d, a.norm, r, red);
 }
 
 // Tiles of a run of prefill-style rows for the row-tile attention: sequence
@@ -366,9 +366,9 @@ hipError_t launch_reserve(const ReserveArgs& a, hipStream_t st) {
 hipError_t launch_recompute_rows(int dtype, const void* embed, const RecomputeRows& a, int rows, hipStream_t st) {
   if (rows <= 0) return hipSuccess;
   if (dtype == 1)
-    hipLaunchKernelGGL(k_recompute_rows<bf16_t>, dim3(rows), dim3(256), 0, st, a, (const bf16_t*)embed);
+    hipLaunchKernelGGL((k_recompute_rows<bf16_t, 1>), dim3(rows), dim3(256), 0, st, a, (const bf16_t*)embed);
   else
-    hipLaunchKernelGGL(k_recompute_rows<float>, dim3(rows), dim3(256), 0, st, a, (const float*)embed);
+    hipLaunchKernelGGL((k_recompute_rows<float, 0>), dim3(rows), dim3(256), 0, st, a, (const float*)embed);
   return hipGetLastError();
 }
 

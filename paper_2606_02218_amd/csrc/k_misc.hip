@@ -5,9 +5,11 @@
 
 namespace {
 
-template <typename T>
-__global__ void k_embed(const T* __restrict__ embed, int d, int V, const int32_t* __restrict__ tok,
-                        float* __restrict__ x, int32_t* __restrict__ bad_token, const int* __restrict__ d_rows) {
+template <typename T, int SPLIT>
+__global__ __launch_bounds__(256) void k_embed(const T* __restrict__ embed, int d, int V,
+                                               const int32_t* __restrict__ tok, float* __restrict__ x, NormArgs n,
+                                               int32_t* __restrict__ bad_token, const int* __restrict__ d_rows) {
+  __shared__ float red[16];
   const int r = blockIdx.x;
   if (r >= *d_rows) return;
   int id = tok[r];
@@ -15,27 +17,30 @@ __global__ void k_embed(const T* __restrict__ embed, int d, int V, const int32_t
     if (threadIdx.x == 0) bad_token[0] = 1;
     id = 0;
   }
-  const T* e = embed + (int64_t)id * d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) x[(int64_t)r * d + i] = ld_f32<T>(e + i);
+  embed_norm<T, SPLIT>(embed + (int64_t)id * d, d, x + (int64_t)r * d, n, r, red);
 }
 
-template <typename T>
-__global__ void k_decode_rows(const T* __restrict__ embed, int d, const int32_t* __restrict__ act_seq,
-                              const int32_t* __restrict__ act_tok, const int32_t* __restrict__ seq_grp,
-                              const int32_t* __restrict__ plen, const int* __restrict__ d_t, int prefix_split,
-                              int32_t* __restrict__ row_tab, int32_t* __restrict__ row_pos,
-                              int32_t* __restrict__ row_beg, float* __restrict__ x, const int* __restrict__ d_rows) {
+template <typename T, int SPLIT>
+__global__ __launch_bounds__(256) void k_decode_rows(const T* __restrict__ embed, int d,
+                                                     const int32_t* __restrict__ act_seq,
+                                                     const int32_t* __restrict__ act_tok,
+                                                     const int32_t* __restrict__ seq_grp,
+                                                     const int32_t* __restrict__ plen, const int* __restrict__ d_t,
+                                                     int prefix_split, int32_t* __restrict__ row_tab,
+                                                     int32_t* __restrict__ row_pos, int32_t* __restrict__ row_beg,
+                                                     float* __restrict__ x, NormArgs n,
+                                                     const int* __restrict__ d_rows) {
+  __shared__ float red[16];
   const int r = blockIdx.x;
   if (r >= *d_rows) return;
-  const int s = act_seq[r];
   if (threadIdx.x == 0) {
+    const int s = act_seq[r];
     const int L = plen[seq_grp[s]];
     row_tab[r] = s;
     row_pos[r] = L + *d_t - 1;
     row_beg[r] = prefix_split ? (L >> 4) << 4 : 0;
   }
-  const T* e = embed + (int64_t)act_tok[r] * d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) x[(int64_t)r * d + i] = ld_f32<T>(e + i);
+  embed_norm<T, SPLIT>(embed + (int64_t)act_tok[r] * d, d, x + (int64_t)r * d, n, r, red);
 }
 
 __global__ void k_prefill_rows(const int32_t* __restrict__ prompt_off, int P, int tab_base,
@@ -148,29 +153,29 @@ __global__ void k_gumbel_bits(uint64_t seed, int t, int s, int vocab, uint32_t* 
 }  // namespace
 
 
-hipError_t launch_embed(int dtype, const void* embed, int d, int V, const int32_t* tok, float* x, int32_t* bad_token,
-                        const int* d_rows, int rows_ub, hipStream_t st) {
+hipError_t launch_embed(int dtype, const void* embed, int d, int V, const int32_t* tok, float* x, const NormArgs& n,
+                        int32_t* bad_token, const int* d_rows, int rows_ub, hipStream_t st) {
   if (rows_ub <= 0) return hipSuccess;
   if (dtype == 1)
-    hipLaunchKernelGGL(k_embed<bf16_t>, dim3(rows_ub), dim3(256), 0, st, (const bf16_t*)embed, d, V, tok, x, bad_token,
-                       d_rows);
+    hipLaunchKernelGGL((k_embed<bf16_t, 1>), dim3(rows_ub), dim3(256), 0, st, (const bf16_t*)embed, d, V, tok, x, n,
+                       bad_token, d_rows);
   else
-    hipLaunchKernelGGL(k_embed<float>, dim3(rows_ub), dim3(256), 0, st, (const float*)embed, d, V, tok, x, bad_token,
-                       d_rows);
+    hipLaunchKernelGGL((k_embed<float, 0>), dim3(rows_ub), dim3(256), 0, st, (const float*)embed, d, V, tok, x, n,
+                       bad_token, d_rows);
   return hipGetLastError();
 }
 
 hipError_t launch_decode_rows(int dtype, const void* embed, int d, const int32_t* act_seq, const int32_t* act_tok,
                               const int32_t* seq_grp, const int32_t* plen, const int* d_t, int prefix_split,
-                              int32_t* row_tab, int32_t* row_pos, int32_t* row_beg, float* x, const int* d_rows,
-                              int rows_ub, hipStream_t st) {
+                              int32_t* row_tab, int32_t* row_pos, int32_t* row_beg, float* x, const NormArgs& n,
+                              const int* d_rows, int rows_ub, hipStream_t st) {
   if (rows_ub <= 0) return hipSuccess;
   if (dtype == 1)
-    hipLaunchKernelGGL(k_decode_rows<bf16_t>, dim3(rows_ub), dim3(256), 0, st, (const bf16_t*)embed, d, act_seq, act_tok,
-                       seq_grp, plen, d_t, prefix_split, row_tab, row_pos, row_beg, x, d_rows);
+    hipLaunchKernelGGL((k_decode_rows<bf16_t, 1>), dim3(rows_ub), dim3(256), 0, st, (const bf16_t*)embed, d, act_seq,
+                       act_tok, seq_grp, plen, d_t, prefix_split, row_tab, row_pos, row_beg, x, n, d_rows);
   else
-    hipLaunchKernelGGL(k_decode_rows<float>, dim3(rows_ub), dim3(256), 0, st, (const float*)embed, d, act_seq, act_tok,
-                       seq_grp, plen, d_t, prefix_split, row_tab, row_pos, row_beg, x, d_rows);
+    hipLaunchKernelGGL((k_decode_rows<float, 0>), dim3(rows_ub), dim3(256), 0, st, (const float*)embed, d, act_seq,
+                       act_tok, seq_grp, plen, d_t, prefix_split, row_tab, row_pos, row_beg, x, n, d_rows);
   return hipGetLastError();
 }
 

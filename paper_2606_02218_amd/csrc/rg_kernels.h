@@ -82,19 +82,43 @@ GemmPlan gemm_plan(int dtype, int rows_ub, int N, int K, int max_splits);
 hipError_t launch_gemm(int dtype, const GemmPlan& p, const void* A, int lda, int64_t a_plane, const void* W, int ldw,
                        const int* d_rows, int rows_ub, int N, int K, const GemmEpi& ep, hipStream_t st);
 
-// x[r] = embed[tok[r]] (fp32), r < *d_rows.  Prefill: tok = prompts.  An id
-// outside [0, V) reads row 0 instead and sets *bad_token = 1.
-hipError_t launch_embed(int dtype, const void* embed, int d, int V, const int32_t* tok, float* x,
+// RMSNorm of a row into an activation operand.
+struct NormArgs {
+  const float* g;
+  float eps;
+  ActOut out;
+};
+
+// One row's embedding into the residual stream and its first RMSNorm (the
+// arithmetic of k_rmsnorm) into the activation operand: the two as one launch
+// save a decode step 2.5-5 us.  Block-wide (256 threads).
+template <typename T, int SPLIT>
+__device__ __forceinline__ void embed_norm(const T* __restrict__ e, int d, float* __restrict__ xr, const NormArgs& n,
+                                           int64_t r, float* red) {
+  float ss = 0.f;
+  for (int i = threadIdx.x; i < d; i += blockDim.x) {
+    const float v = ld_f32<T>(e + i);
+    xr[i] = v;
+    ss = fmaf(v, v, ss);
+  }
+  ss = block_sum(ss, red);
+  const float inv = 1.0f / sqrtf(ss / (float)d + n.eps);
+  for (int i = threadIdx.x; i < d; i += blockDim.x) act_store<SPLIT>(n.out, r * d + i, ld_f32<T>(e + i) * inv * n.g[i]);
+}
+
+// x[r] = embed[tok[r]] (fp32) and its norm n, r < *d_rows.  Prefill: tok =
+// prompts.  An id outside [0, V) reads row 0 instead and sets *bad_token = 1.
+hipError_t launch_embed(int dtype, const void* embed, int d, int V, const int32_t* tok, float* x, const NormArgs& n,
                         int32_t* bad_token, const int* d_rows, int rows_ub, hipStream_t st);
 
 // Decode row setup for step t = *d_t >= 1: row r (< *d_rows) feeds act_tok[r]
 // for sequence s = act_seq[r] at position plen[grp[s]] + t - 1; writes
 // row_tab, row_pos, row_beg (the prompt's full-page length when
-// prefix_split, else 0) and the embedded token into x.
+// prefix_split, else 0), the embedded token into x and its norm n.
 hipError_t launch_decode_rows(int dtype, const void* embed, int d, const int32_t* act_seq,
                               const int32_t* act_tok, const int32_t* seq_grp, const int32_t* plen, const int* d_t,
                               int prefix_split, int32_t* row_tab, int32_t* row_pos, int32_t* row_beg, float* x,
-                              const int* d_rows, int rows_ub, hipStream_t st);
+                              const NormArgs& n, const int* d_rows, int rows_ub, hipStream_t st);
 
 // Prefill row setup: row r belongs to prompt p with prompt_off[p] <= r <
 // prompt_off[p+1]; row_tab[r] = tab_base + p, row_pos[r] = r - prompt_off[p],
@@ -186,7 +210,9 @@ struct SampleArgs {
   float* part;              // [rows][n_slices][4] slice partials
   int n_slices;             // vocabulary slices per row
 };
-hipError_t launch_sample(const SampleArgs& a, int rows_ub, hipStream_t st);
+// Slice partials of every row (part), then, unless the step's retirement does
+// it (launch_compact with a pick), the token of each row.
+hipError_t launch_sample(const SampleArgs& a, int rows_ub, bool pick, hipStream_t st);
 
 // Retire/compact after the step whose index is state[8]; advances state[8].
 // Also publishes each prompt's range of rows among the surviving ones
@@ -201,8 +227,14 @@ struct CompactArgs {
   int32_t* state;     // [0] active rows, [1] free-stack top, [2] out-of-pages flag, [8] step
   int32_t* lengths;
   int32_t* hist_active; int32_t* hist_groups; int64_t* hist_ctx; int hist_cap;
+  int32_t* ring; int ring_slots;   // pinned host memory [ring_slots][8]: state[0..7] after step t in slot t % ring_slots
 };
-hipError_t launch_compact(const CompactArgs& a, hipStream_t st);
+// Most rows (bound) whose tokens the retirement block picks itself, and most
+// vocabulary slices a row may then have.
+constexpr int COMPACT_PICK_ROWS = 32, COMPACT_PICK_SLICES = 32;
+// pick != NULL: the block first picks the token of each of at most
+// COMPACT_PICK_ROWS rows (as launch_sample would).
+hipError_t launch_compact(const CompactArgs& a, const SampleArgs* pick, hipStream_t st);
 
 struct ForkArgs {
   int P, n_seq, page_tok, max_pages, share;
@@ -266,13 +298,14 @@ struct ReserveArgs {
 hipError_t launch_reserve(const ReserveArgs& a, hipStream_t st);
 
 // Rows row0 .. row0 + rows - 1 of the teacher-forced forward: row set-up
-// (row_tab, row_pos, row_beg), embeddings into x, and for each row the token
+// (row_tab, row_pos, row_beg), embeddings into x and their norm, and for each row the token
 // it predicts (row_tgt) and where that token's log-probability goes (row_out).
 struct RecomputeRows {
   int row0, n_seq, max_new, V, d;
   const int32_t* coff; const int32_t* tokens; const int32_t* plen; const int32_t* seq_grp;
   int32_t* row_tab; int32_t* row_pos; int32_t* row_beg; int32_t* row_tgt; int32_t* row_out;
   float* x; int32_t* bad_token;
+  NormArgs norm;
 };
 hipError_t launch_recompute_rows(int dtype, const void* embed, const RecomputeRows& a, int rows, hipStream_t st);
 // Cuts rows 0..min(n, *d_rows)-1 of prefill-style rows (sequence s < n_seq
