@@ -1008,7 +1008,29 @@ int recompute_logprobs(rg_policy* pol, const int32_t* prompts, const int32_t* pr
     if (use_tiles) LAUNCH(RG_K_SETUP, launch_row_tiles(pol->coff, N, (int)r0, n, tile_rows, d_chunk, pol->tile_r0,
                                                        pol->tile_nr, d_tiles, st));
     if ((rc = run_layers(pol, st, d_chunk, n, ctx_all, true, nullptr, use_tiles ? &rt : nullptr))) return rc;
-    for (int h0 = 0; h0 < n; h0 += slice) {
+    // Direct-to-LDS plans take the log-probability in the lm head's epilogue:
+    // a row's logits (0.6 MB at 152k tokens) are neither written nor read back,
+    // and the rows need no slices (four-layer 1.5B widths, 4096 rows: lm head
+    // and log-probabilities 3.9 -> 3.3 ms).  The partials live in the idle
+    // logits buffer.
+    const GemmPlan lmp = gemm_plan(pol->dtype, n, pol->V, pol->d, 1);
+    if (lmp.dma) {
+      const int parts = gemm_lse_parts(lmp, pol->V);
+      const int64_t cap = std::min<int64_t>(n, pol->logit_rows * pol->V / (2 * parts + 1));
+      for (int h0 = 0; h0 < n; h0 += (int)cap) {
+        const int m = (int)std::min<int64_t>(cap, n - h0);
+        GemmEpi ep{};
+        ep.mode = GEMM_EPI_LOGPROB; ep.temperature = temperature; ep.row_tgt = pol->row_tgt + h0;
+        ep.lse_part = (float2*)pol->logits; ep.lse_ld = parts; ep.tgt_z = pol->logits + cap * 2 * parts;
+        LAUNCH(RG_K_SETUP, launch_fill_i32(d_slice, 1, m, st));
+        LAUNCH(RG_K_GEMM_LM, launch_gemm(pol->dtype, lmp, (const char*)pol->abuf + (size_t)h0 * row_bytes, pol->d,
+                                         pol->a_plane, pol->w_lm, pol->d, d_slice, m, pol->V, pol->d, ep, st));
+        LAUNCH(RG_K_LOGPROB, launch_lse_logprob(ep.lse_part, parts, parts, ep.tgt_z, pol->row_out + h0, logprobs, m,
+                                                st));
+      }
+      continue;
+    }
+    for (int h0 = 0; h0 < n; h0 += slice) {   // fp32 models and few rows
       const int m = std::min(slice, n - h0);
       LAUNCH(RG_K_SETUP, launch_fill_i32(d_slice, 1, m, st));
       if ((rc = gemm(pol, st, RG_K_GEMM_LM, (const char*)pol->abuf + (size_t)h0 * row_bytes, pol->d, pol->w_lm,

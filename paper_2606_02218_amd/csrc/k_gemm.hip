@@ -4,6 +4,8 @@
 //   RESIDUAL  x[r][n] += y                         (O and down projections)
 //   SWIGLU    act[r][f] = silu(gate) * up          (gate/up projection; packed
 //             columns come as [16 gate | 16 up] per 32)
+//   LOGPROB   the lm head of scored rows: no logits, but each row's logsumexp
+//             over the tile's columns and the logit of the token it predicts
 //   QKV       RoPE on the query and key heads; q -> fp32 buffer, k and v ->
 //             the row's KV page (keys as [slot][dim], values as [dim][slot]).
 //             Within each head the packed weight rows come in 16-row tiles
@@ -190,6 +192,36 @@ __device__ __forceinline__ void acc_epilogue(const f32x4_t (&acc)[WM][WN], const
   } else if constexpr (EPI == GEMM_EPI_QKV) {
     qkv_tile_store<WM, WN>(acc, ep, m0, n0, M, N, wm, wn, lane, ep.row_pos, ep.row_tab, ep.page_tab, ep.rope_cos,
                            ep.rope_sin, ep.q_out, (bf16_t*)ep.kv_pool);
+  } else if constexpr (EPI == GEMM_EPI_LOGPROB) {
+    // one (max, sum of exp(z/T - max)) per row and wave column, over the wave's
+    // columns below N: a lane folds its WN columns, the 16 lanes of a row the
+    // rest.  Past N the logit counts as -inf.
+    const float T = ep.temperature;
+    const bool unit_T = T == 1.0f;               // z / 1 == z exactly
+    const int part = (n0 / (16 * WN)) + wn;      // this wave's column range
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = m0 + (wm * WM + i) * 16 + (lane >> 4) * 4 + e;
+        const int tgt = r < M ? ep.row_tgt[r] : -1;
+        float z[WN], m = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < WN; ++j) {
+          const int col = n0 + (wn * WN + j) * 16 + lr;
+          z[j] = col < N ? (unit_T ? acc[i][j][e] : acc[i][j][e] / T) : -INFINITY;
+          if (col == tgt) ep.tgt_z[r] = z[j];    // one lane of the launch per row
+          m = fmaxf(m, z[j]);
+        }
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < WN; ++j) s += z[j] == -INFINITY ? 0.f : z[j] == m ? 1.f : __expf(z[j] - m);
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if (lr == 0 && r < M) ep.lse_part[(int64_t)r * ep.lse_ld + part] = float2{m, s};
+      }
   } else if constexpr (EPI == GEMM_EPI_SWIGLU) {
     // tiles 2m and 2m+1 of a wave pair up: (gate, up)
 #pragma unroll
@@ -859,6 +891,10 @@ hipError_t launch_dma(const void* A, int lda, int64_t a_plane, const void* W, in
       case GEMM_EPI_RESIDUAL: RG_DMA(GEMM_EPI_RESIDUAL); break;
       case GEMM_EPI_SWIGLU: RG_DMA(GEMM_EPI_SWIGLU); break;
       case GEMM_EPI_QKV: RG_DMA(GEMM_EPI_QKV); break;
+      case GEMM_EPI_LOGPROB:
+        if (ep.lse_ld < gx * (BN / (16 * WN))) return hipErrorInvalidValue;
+        RG_DMA(GEMM_EPI_LOGPROB);
+        break;
       default: return hipErrorInvalidValue;
     }
   }
@@ -1020,6 +1056,8 @@ GemmPlan gemm_plan(int dtype, int rows_ub, int N, int K, int max_splits) {
   p.splits = (int)ceil_div(K, p.k_per_split);
   return p;
 }
+
+int gemm_lse_parts(const GemmPlan& p, int N) { return (int)ceil_div(N, p.bn) * (p.bn == 256 ? 4 : 2); }
 
 hipError_t launch_gemm(int dtype, const GemmPlan& p, const void* A, int lda, int64_t a_plane, const void* W, int ldw,
                        const int* d_rows, int rows_ub, int N, int K, const GemmEpi& ep, hipStream_t st) {

@@ -203,6 +203,34 @@ __global__ __launch_bounds__(LP_THREADS) void k_token_logprob(const float* __res
   if (tid == 0) lp[out[r]] = z[tgt[r]] / T - (sm[0] + logf(ss[0]));
 }
 
+// The same from the partial logsumexps that the lm head's epilogue left: one
+// wave per row.
+__global__ __launch_bounds__(256) void k_lse_logprob(const float2* __restrict__ part, int ld, int n_part,
+                                                     const float* __restrict__ tgt_z, const int32_t* __restrict__ out,
+                                                     float* __restrict__ lp, int rows) {
+  const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (r >= rows) return;
+  const float2* p = part + (int64_t)r * ld;
+  // weight of a partial with max a under the joint max mm (an infinite max
+  // weighs 1 against itself)
+  auto weight = [](float a, float mm) { return a == -INFINITY ? 0.f : a == mm ? 1.f : expf(a - mm); };
+  float m = -INFINITY, sum = 0.f;
+  for (int k = lane; k < n_part; k += 64) {
+    const float2 v = p[k];
+    const float mm = fmaxf(m, v.x);
+    sum = sum * weight(m, mm) + v.y * weight(v.x, mm);
+    m = mm;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const float m2 = __shfl_xor(m, o, 64), s2 = __shfl_xor(sum, o, 64);
+    const float mm = fmaxf(m, m2);
+    sum = sum * weight(m, mm) + s2 * weight(m2, mm);
+    m = mm;
+  }
+  if (lane == 0) lp[out[r]] = tgt_z[r] - (m + logf(sum));
+}
+
 // Clipped surrogate, pass 1: one block of 256 threads per sequence s < N.  The
 // threads stride over the sequence's L_s tokens, four at a time, and
 // accumulate, in fp64, min(rho * A_s, clip(rho, 1 - eps_lo, 1 + eps_hi) * A_s),
@@ -390,6 +418,13 @@ hipError_t launch_token_logprob(const float* logits, int V, float T, const int32
                                 const int32_t* out, float* lp, int rows, hipStream_t st) {
   if (rows <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_token_logprob, dim3(rows), dim3(LP_THREADS), 0, st, logits, V, T, lrow, tgt, out, lp);
+  return hipGetLastError();
+}
+
+hipError_t launch_lse_logprob(const float2* part, int ld, int n_part, const float* tgt_z, const int32_t* out,
+                              float* lp, int rows, hipStream_t st) {
+  if (rows <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_lse_logprob, dim3((rows + 3) / 4), dim3(256), 0, st, part, ld, n_part, tgt_z, out, lp, rows);
   return hipGetLastError();
 }
 

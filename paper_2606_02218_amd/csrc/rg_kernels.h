@@ -53,7 +53,8 @@ enum { GEMM_EPI_STORE = 0,      // C[r][n] = y
        GEMM_EPI_RESIDUAL = 1,   // x[r][n] += y
        GEMM_EPI_SWIGLU = 2,     // columns packed [16 gate | 16 up] per 32; act[r][f] = silu(g) * u
        GEMM_EPI_QKV = 3,        // RoPE; q -> q_out, k and v -> the row's KV page
-       GEMM_EPI_PARTIAL = 4 };  // (internal) split partial to part[s]
+       GEMM_EPI_PARTIAL = 4,    // (internal) split partial to part[s]
+       GEMM_EPI_LOGPROB = 5 };  // direct-to-LDS plans: partial logsumexps and the predicted token's logit
 struct GemmEpi {
   int mode;
   float* C; int ldc;                      // STORE
@@ -64,6 +65,8 @@ struct GemmEpi {
   float* q_out; void* kv_pool; KvGeom geom; int layer;      // QKV
   const int32_t* page_tab; int tab_stride; const int32_t* row_tab; const int32_t* row_pos;
   const float* rope_cos; const float* rope_sin; int n_q, n_kv, hd;
+  float temperature; const int32_t* row_tgt; float* tgt_z;  // LOGPROB: z/T, the token each row predicts, its z/T
+  float2* lse_part; int lse_ld;           // LOGPROB: (max, sum) [rows][gemm_lse_parts]
   float* part; int64_t part_stride;       // split partials [S][rows][N] (S > 1)
 };
 
@@ -75,6 +78,8 @@ struct GemmPlan {
   int splits, k_per_split;
 };
 GemmPlan gemm_plan(int dtype, int rows_ub, int N, int K, int max_splits);
+// Partial logsumexps per row of a LOGPROB launch by plan p.
+int gemm_lse_parts(const GemmPlan& p, int N);
 
 // y = A W^T over rows < *d_rows by plan p (bf16 models: K a multiple of 64, N
 // of 16; fp32 models: K a multiple of 16), then the epilogue ep.  A's buffer
@@ -325,6 +330,10 @@ hipError_t launch_first_rows(const int32_t* tokens, const int32_t* seq_grp, int 
 // lp[out[r]] = z[tgt[r]]/T - logsumexp(z/T), z = logits row lrow[r] (lrow NULL: r).
 hipError_t launch_token_logprob(const float* logits, int V, float T, const int32_t* lrow, const int32_t* tgt,
                                 const int32_t* out, float* lp, int rows, hipStream_t st);
+
+// lp[out[r]] = tgt_z[r] - logsumexp over the row's n_part (max, sum) partials.
+hipError_t launch_lse_logprob(const float2* part, int ld, int n_part, const float* tgt_z, const int32_t* out,
+                              float* lp, int rows, hipStream_t st);
 
 struct SurrogateArgs {
   const float* new_lp; const float* old_lp; const float* adv; const int32_t* lengths;

@@ -43,9 +43,10 @@ def test_dma_tiles_match_oracle(si, rows):
     tok = rng.integers(0, shape.vocab - 1, size=(P, max_new)).astype(np.int32)
     pol = make_policy(shape, w, max_seqs=P, max_prompts=P, max_prompt_tokens=rows, max_context=int(plens.max()) + max_new)
     print(f"dma tiles: shape {si}, {rows} rows", flush=True)
+    T = 0.7 if rows == 1152 else 1.0
     got = pol.recompute_logprobs(prompts_to_device(prompts), G, torch.from_numpy(tok).cuda(),
-                                 torch.from_numpy(lengths).cuda()).cpu().numpy()
-    want = teacher_forced_logprobs(oracle_for(shape, w), prompts, G, tok, lengths)
+                                 torch.from_numpy(lengths).cuda(), temperature=T).cpu().numpy()
+    want = teacher_forced_logprobs(oracle_for(shape, w), prompts, G, tok, lengths, temperature=T)
     valid = np.arange(max_new)[None, :] < lengths[:, None]
     gap = float(np.max(np.abs(got[valid] - want[valid])))
     print(f"gap {gap:.2e}", flush=True)
