@@ -2,8 +2,8 @@
 columns, K steps of 64 through two LDS buffers) against the oracle at their
 edges: row counts one over and one short of a tile, K of one step (64), two and
 many, with and without a K split, widths that end inside a column tile, and
-every epilogue (QKV + RoPE + KV append, SwiGLU, residual, the lm head's store
-through the recompute's row slices).
+every epilogue (QKV + RoPE + KV append, SwiGLU, residual, the lm head's partial
+logsumexps and predicted-token logits, at temperatures 1 and 0.7).
 
 Tolerance: activations carry 2^-17 relative in hi + lo planes and sums are
 fp32, so what shows is a key or value rounding the other way into the bf16
