@@ -1080,14 +1080,19 @@ hipError_t launch_attention_tile(const float* q, int n_q, int n_kv, int head_dim
 int att_tile_rows(int n_q, int n_kv) { return ATT_TILE_QROWS / (n_q / n_kv); }
 
 // About ATT_ITEMS_TARGET work items (fewer, longer chunks measured faster than
-// filling every wave slot: less partial traffic and per-item set-up), at least
-// ~256 tokens each for the longest context, at most 16000 tokens each.  From
-// 512 to 2048 (row, kv head) pairs, where the chunks of a row are merged
-// inside the attention kernel, rows take at least two chunks: twice the waves
-// per CU and no merge launch (1.5B at 384-512 rows: 64.5 -> 60.1 us a launch).
+// filling every wave slot: less partial traffic and per-item set-up), at most
+// 16000 tokens each and at least ~256 for the longest context, or ~128 where
+// that still leaves half the target: a lone wave's chain of blocks is then what
+// the launch waits for (8 rows of the 1.5B shape at up to 2560 tokens, whole
+// steps 1.1 % faster).  From 512 to 2048 (row, kv head) pairs, where the chunks
+// of a row are merged inside the attention kernel, rows take at least two
+// chunks from 512 tokens (256 below 1024 pairs): twice the waves per CU and no
+// merge launch (1.5B at 384-512 rows: 64.5 -> 60.1 us a launch; gpt2s at 64 rows
+// and 256-416 tokens, one chunk before: whole steps 1.8 % faster).
 int att_row_chunks(int rows_ub, int n_kv, int ctx_max) {
   const int64_t items = (int64_t)rows_ub * n_kv;
-  int n = (int)std::min<int64_t>((ATT_ITEMS_TARGET + items / 2) / items, (ctx_max + 255) / 256);
-  if (items >= 512 && items <= 2048 && ctx_max >= 512) n = std::max(n, 2);
+  const int least = items * ((ctx_max + 255) / 256) < ATT_ITEMS_TARGET / 2 ? 128 : 256;
+  int n = (int)std::min<int64_t>((ATT_ITEMS_TARGET + items / 2) / items, (ctx_max + least - 1) / least);
+  if (items >= 512 && items <= 2048 && ctx_max >= (items < 1024 ? 256 : 512)) n = std::max(n, 2);
   return std::max<int>({1, n, (ctx_max + 15999) / 16000});
 }
