@@ -82,6 +82,8 @@ struct rg_policy {
   int64_t a_plane = 0;   // elements between the hi and lo planes of abuf (bf16 models)
   float* cpart = nullptr;
   int64_t cpart_elems = 0;
+  float* ssq = nullptr;   // [m_act][ssq_ld] partial sums of squares of x, for the next RMSNorm
+  int ssq_ld = 0, ssq_n = 0;
   float* qbuf = nullptr;
   float* att_o = nullptr;
   float* att_ml = nullptr;
@@ -227,14 +229,27 @@ struct ProfScope {
 // single-kernel launchers that time their dispatch with armed events
 #define LAUNCH_TIMED(kind, call) LAUNCH_(kind, call, true)
 
+// The row factor of an operand x * gain of width K whose rows start at row0 of
+// the policy's partial sums of squares (ssq_n of them per row; 0: none).
+void set_row_scale(const rg_policy* pol, GemmEpi* ep, int ssq_n, int K, int row0) {
+  ep->ssq_in = ssq_n ? pol->ssq + (int64_t)row0 * pol->ssq_ld : nullptr;
+  ep->ssq_n = ssq_n; ep->ssq_ld = pol->ssq_ld; ep->norm_dim = K; ep->norm_eps = pol->cfg.rms_eps;
+}
+
 // One projection with its epilogue; the split plan and workspace are filled in here.
+// ssq_n: partial sums of squares per row behind the operand (0: normalised already); a RESIDUAL with a next norm sets it to
+// the ones it leaves.
 int gemm(rg_policy* pol, hipStream_t st, int kind, const void* A, int K, const void* W, int N, const int* d_rows,
-         int rows_ub, GemmEpi ep, bool allow_split = true, int* splits_out = nullptr) {
+         int rows_ub, GemmEpi ep, int* ssq_n, bool allow_split = true) {
   const int64_t fit = pol->cpart_elems / ((int64_t)rows_ub * N);   // splits the workspace holds
-  // the reduction that normalises the row holds at most 8192 columns
-  if (ep.mode == GEMM_EPI_RESIDUAL && ep.norm_g && N > 8192) allow_split = false;
   const GemmPlan p = gemm_plan(pol->dtype, rows_ub, N, K, allow_split ? (int)std::min<int64_t>(fit, RG_SPLIT_MAX) : 1);
-  if (splits_out) *splits_out = p.splits;
+  ep.ssq_ld = pol->ssq_ld;
+  if (ep.mode == GEMM_EPI_RESIDUAL) {
+    ep.ssq_out = pol->ssq;
+    *ssq_n = gemm_ssq_parts(pol->dtype, p, N);
+  } else {
+    set_row_scale(pol, &ep, *ssq_n, K, 0);
+  }
   ep.part = pol->cpart;
   ep.part_stride = (int64_t)rows_ub * N;
   LAUNCH(kind, launch_gemm(pol->dtype, p, A, K, pol->a_plane, W, K, d_rows, rows_ub, N, K, ep, st));
@@ -262,7 +277,8 @@ struct RowTiles {
 // row_tab / row_pos / row_beg are set and whose first attention norm is in
 // pol->abuf; ctx_max bounds every row's context length.  pre != NULL runs the
 // prefix pass (row_beg then holds each row's prefix length).  On return
-// pol->abuf holds the final norm of every row (final_norm_rows) or x the
+// pol->abuf holds the final norm's operand x * gain of every row, with pol->ssq_n partial sums of squares behind it
+// (final_norm_rows), or x the
 // residual stream after the last block.
 int run_layers(rg_policy* pol, hipStream_t st, const int* d_rows, int rows_ub, int ctx_max, bool final_norm_rows,
                const PrefixPass* pre, const RowTiles* tiles = nullptr) {
@@ -282,7 +298,6 @@ int run_layers(rg_policy* pol, hipStream_t st, const int* d_rows, int rows_ub, i
   }
   if (!tiles && (int64_t)rows_ub * plan.n_slots > pol->att_rowchunks)
     return fail(RG_ENOMEM, "attention workspace too small");
-  const float eps = pol->cfg.rms_eps;
   GemmEpi qkv{};
   qkv.mode = GEMM_EPI_QKV;
   qkv.q_out = pol->qbuf; qkv.kv_pool = pol->kv_pool; qkv.geom = pol->geom;
@@ -290,14 +305,16 @@ int run_layers(rg_policy* pol, hipStream_t st, const int* d_rows, int rows_ub, i
   qkv.rope_cos = pol->rope_cos; qkv.rope_sin = pol->rope_sin; qkv.n_q = pol->nq; qkv.n_kv = pol->nkv; qkv.hd = pol->hd;
   GemmEpi resid{};
   resid.mode = GEMM_EPI_RESIDUAL; resid.x = pol->x; resid.ldx = pol->d;
-  resid.norm_eps = eps; resid.norm_out = ActOut{pol->abuf, pol->a_plane};
+  resid.norm_out = ActOut{pol->abuf, pol->a_plane};
   GemmEpi swig{};
   swig.mode = GEMM_EPI_SWIGLU; swig.act = ActOut{pol->abuf2, pol->a_plane}; swig.act_ld = pol->F;
   int rc;
+  int ssq_n = 0;   // layer 0's operand is normalised (by the embedding kernels)
 
   for (int l = 0; l < pol->L; ++l) {
     qkv.layer = l;
-    if ((rc = gemm(pol, st, RG_K_GEMM_QKV, pol->abuf, pol->d, pol->w_qkv[l], pol->qkv_n, d_rows, rows_ub, qkv)))
+    if ((rc = gemm(pol, st, RG_K_GEMM_QKV, pol->abuf, pol->d, pol->w_qkv[l], pol->qkv_n, d_rows, rows_ub, qkv,
+                   &ssq_n)))
       return rc;
     if (tiles) {
       LAUNCH_TIMED(RG_K_ATTN, launch_attention_tile(pol->qbuf, pol->nq, pol->nkv, pol->hd, pol->kv_pool, pol->geom, l,
@@ -318,38 +335,32 @@ int run_layers(rg_policy* pol, hipStream_t st, const int* d_rows, int rows_ub, i
       LAUNCH(RG_K_ATTN_MERGE, launch_attn_merge(pol->dtype, pol->att_o, pol->att_ml, pol->nq, pol->hd, pol->row_pos,
                                                 pol->row_beg, plan, pol->abuf2, pol->a_plane, d_rows, rows_ub, st));
     }
-    // O projection + residual, then the MLP norm into abuf (fused into the
-    // split epilogue when K is split)
-    int S;
+    // O projection + residual, the MLP norm's operand into abuf
     resid.norm_g = pol->g_ffn[l];
-    if ((rc = gemm(pol, st, RG_K_GEMM_O, pol->abuf2, pol->q_dim, pol->w_o[l], pol->d, d_rows, rows_ub, resid, true, &S)))
+    if ((rc = gemm(pol, st, RG_K_GEMM_O, pol->abuf2, pol->q_dim, pol->w_o[l], pol->d, d_rows, rows_ub, resid, &ssq_n)))
       return rc;
-    if (S == 1)
-      LAUNCH(RG_K_RMSNORM, launch_rmsnorm(pol->dtype, pol->x, pol->g_ffn[l], pol->d, eps, pol->abuf, pol->a_plane,
-                                           nullptr, d_rows, rows_ub, st));
-    if ((rc = gemm(pol, st, RG_K_GEMM_GU, pol->abuf, pol->d, pol->w_gu[l], 2 * pol->F, d_rows, rows_ub, swig)))
+    if ((rc = gemm(pol, st, RG_K_GEMM_GU, pol->abuf, pol->d, pol->w_gu[l], 2 * pol->F, d_rows, rows_ub, swig, &ssq_n)))
       return rc;
-    const float* gnext = l + 1 < pol->L ? pol->g_attn[l + 1] : (final_norm_rows ? pol->w_final : nullptr);
-    resid.norm_g = gnext;
-    if ((rc = gemm(pol, st, RG_K_GEMM_DOWN, pol->abuf2, pol->F, pol->w_down[l], pol->d, d_rows, rows_ub, resid, true,
-                   &S)))
+    resid.norm_g = l + 1 < pol->L ? pol->g_attn[l + 1] : (final_norm_rows ? pol->w_final : nullptr);
+    if ((rc = gemm(pol, st, RG_K_GEMM_DOWN, pol->abuf2, pol->F, pol->w_down[l], pol->d, d_rows, rows_ub, resid,
+                   &ssq_n)))
       return rc;
-    if (gnext && S == 1)
-      LAUNCH(RG_K_RMSNORM, launch_rmsnorm(pol->dtype, pol->x, gnext, pol->d, eps, pol->abuf, pol->a_plane, nullptr,
-                                           d_rows, rows_ub, st));
   }
+  pol->ssq_n = ssq_n;
   return RG_OK;
 }
 
 // The lm head into pol->logits.  src_rows != NULL (prefill): final norm of the
-// listed rows first; otherwise pol->abuf already holds the final norm.
+// listed rows first; otherwise pol->abuf holds the final norm's operand
+// (run_layers with final_norm_rows).
 int run_head(rg_policy* pol, hipStream_t st, const int* d_rows, int rows_ub, const int32_t* src_rows) {
   if (src_rows)
     LAUNCH(RG_K_RMSNORM, launch_rmsnorm(pol->dtype, pol->x, pol->w_final, pol->d, pol->cfg.rms_eps, pol->abuf,
                                          pol->a_plane, src_rows, d_rows, rows_ub, st));
   GemmEpi store{};
   store.mode = GEMM_EPI_STORE; store.C = pol->logits; store.ldc = pol->V;
-  return gemm(pol, st, RG_K_GEMM_LM, pol->abuf, pol->d, pol->w_lm, pol->V, d_rows, rows_ub, store, false);
+  int ssq_n = src_rows ? 0 : pol->ssq_n;
+  return gemm(pol, st, RG_K_GEMM_LM, pol->abuf, pol->d, pol->w_lm, pol->V, d_rows, rows_ub, store, &ssq_n, false);
 }
 
 // Row bound used for a decode step: the host's bound rounded up, so that the
@@ -725,6 +736,7 @@ int rg_policy_create(const rg_config* cfg, const rg_weights* w, const rg_limits*
           S * (RG_PRE_MAX_SLOTS + ceil_div(lim.max_context, 1024)),
       M * att_row_chunks((int)std::min<int64_t>(M, INT32_MAX), pol->nkv, lim.max_context));
   pol->hist_cap = lim.max_context;
+  pol->ssq_ld = (int)ceil_div(d, 32);   // the narrowest column tiles
   struct Piece { void** p; size_t bytes; };
   const int64_t kmax = std::max<int64_t>({d, pol->q_dim, pol->F});
   pol->a_plane = pol->dtype == RG_DTYPE_BF16 ? M * kmax : 0;
@@ -734,6 +746,7 @@ int rg_policy_create(const rg_config* cfg, const rg_weights* w, const rg_limits*
       {&pol->abuf2, (size_t)(M * kmax * 4)},
       {(void**)&pol->cpart, (size_t)(pol->cpart_elems * 4)},
       {(void**)&pol->qbuf, (size_t)(M * pol->q_dim * 4)},
+      {(void**)&pol->ssq, (size_t)(M * pol->ssq_ld * 4)},
       {(void**)&pol->att_o, (size_t)(pol->att_rowchunks * pol->nq * pol->hd * 4)},
       {(void**)&pol->att_ml, (size_t)(pol->att_rowchunks * pol->nq * 2 * 4)},
       {(void**)&pol->logits, (size_t)(pol->logit_rows * pol->V * 4)},
@@ -1021,6 +1034,7 @@ int recompute_logprobs(rg_policy* pol, const int32_t* prompts, const int32_t* pr
         const int m = (int)std::min<int64_t>(cap, n - h0);
         GemmEpi ep{};
         ep.mode = GEMM_EPI_LOGPROB; ep.temperature = temperature; ep.row_tgt = pol->row_tgt + h0;
+        set_row_scale(pol, &ep, pol->ssq_n, pol->d, h0);
         ep.lse_part = (float2*)pol->logits; ep.lse_ld = parts; ep.tgt_z = pol->logits + cap * 2 * parts;
         LAUNCH(RG_K_SETUP, launch_fill_i32(d_slice, 1, m, st));
         LAUNCH(RG_K_GEMM_LM, launch_gemm(pol->dtype, lmp, (const char*)pol->abuf + (size_t)h0 * row_bytes, pol->d,
@@ -1033,9 +1047,10 @@ int recompute_logprobs(rg_policy* pol, const int32_t* prompts, const int32_t* pr
     for (int h0 = 0; h0 < n; h0 += slice) {   // fp32 models and few rows
       const int m = std::min(slice, n - h0);
       LAUNCH(RG_K_SETUP, launch_fill_i32(d_slice, 1, m, st));
-      if ((rc = gemm(pol, st, RG_K_GEMM_LM, (const char*)pol->abuf + (size_t)h0 * row_bytes, pol->d, pol->w_lm,
-                     pol->V, d_slice, m, store, false)))
-        return rc;
+      set_row_scale(pol, &store, pol->ssq_n, pol->d, h0);
+      LAUNCH(RG_K_GEMM_LM, launch_gemm(pol->dtype, gemm_plan(pol->dtype, m, pol->V, pol->d, 1),
+                                       (const char*)pol->abuf + (size_t)h0 * row_bytes, pol->d, pol->a_plane,
+                                       pol->w_lm, pol->d, d_slice, m, pol->V, pol->d, store, st));
       LAUNCH(RG_K_LOGPROB, launch_token_logprob(pol->logits, pol->V, temperature, nullptr, pol->row_tgt + h0,
                                                 pol->row_out + h0, logprobs, m, st));
     }

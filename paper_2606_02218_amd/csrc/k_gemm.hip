@@ -1,7 +1,9 @@
 // Matrix products of the decoder, y = x W^T with activations [rows, K] and
 // weights W [N, K] (both K-contiguous), each with a fused epilogue:
 //   STORE     C[r][n] = y                          (lm head logits)
-//   RESIDUAL  x[r][n] += y                         (O and down projections)
+//   RESIDUAL  x[r][n] += y                         (O and down projections),
+//             and for the next RMSNorm the operand x * gain and partial sums of
+//             x^2 per row
 //   SWIGLU    act[r][f] = silu(gate) * up          (gate/up projection; packed
 //             columns come as [16 gate | 16 up] per 32)
 //   LOGPROB   the lm head of scored rows: no logits, but each row's logsumexp
@@ -11,6 +13,12 @@
 //             Within each head the packed weight rows come in 16-row tiles
 //             ordered (dims 0-15, dims h/2..h/2+15, dims 16-31, ...) so that
 //             a rotated pair (d, d + h/2) lies in adjacent column tiles.
+//
+// RMSNorm has no launch of its own: the producer of x leaves x * gain as the
+// next operand and, per row and column tile, the sum of x^2; the consumer's
+// products are scaled by the row's 1 / rms in its epilogue (the factor is the
+// same for the whole row, and the hi/lo split is relative, so the precision is
+// that of splitting the normalised value).
 //
 // bf16 models: LDS-tiled gfx950 MFMA (v_mfma_f32_16x16x32_bf16).  A block
 // owns a BM x BN output tile and walks its K range in steps of 64.  The
@@ -43,6 +51,47 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ bf16x8_t lds_frag(const bf16_t* p) {
   return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(p));
+}
+
+// 1 / rms of a block's BM rows from the ep.ssq_n partial sums of squares of each
+// (NULL ep.ssq_in: the operand is already normalised, factor 1).  NT / BM
+// threads share a row; load() issues the first eight partials of a thread,
+// finish() adds them up once the K loop is over.
+template <int BM, int NT>
+struct RowScale {
+  static constexpr int TPR = NT / BM, U = 8;
+  static_assert(NT % BM == 0 && TPR <= 64 && (TPR & (TPR - 1)) == 0, "threads per row");
+  float v[U];
+  __device__ __forceinline__ void load(const GemmEpi& ep, int m0, int rows_cap, int tid) {
+    const float* p = ep.ssq_in + (int64_t)min(m0 + tid / TPR, rows_cap - 1) * ep.ssq_ld;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = tid % TPR + u * TPR;
+      v[u] = ep.ssq_in && k < ep.ssq_n ? p[k] : 0.f;
+    }
+  }
+  __device__ __forceinline__ void finish(const GemmEpi& ep, int m0, int rows_cap, int tid, float* s_inv) {
+    float s = 0.f;
+#pragma unroll
+    for (int u = 0; u < U; ++u) s += v[u];
+    if (ep.ssq_in) {
+      const float* p = ep.ssq_in + (int64_t)min(m0 + tid / TPR, rows_cap - 1) * ep.ssq_ld;
+      for (int k = tid % TPR + U * TPR; k < ep.ssq_n; k += TPR) s += p[k];
+    }
+#pragma unroll
+    for (int o = TPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (tid % TPR == 0) s_inv[tid / TPR] = ep.ssq_in ? 1.0f / sqrtf(s / (float)ep.norm_dim + ep.norm_eps) : 1.f;
+    __syncthreads();
+  }
+};
+
+// The same factor for row r, the same for every lane of a wave.
+__device__ __forceinline__ float wave_row_scale(const GemmEpi& ep, int r, int lane) {
+  if (!ep.ssq_in) return 1.f;
+  const float* p = ep.ssq_in + (int64_t)r * ep.ssq_ld;
+  float s = 0.f;
+  for (int k = lane; k < ep.ssq_n; k += 64) s += p[k];
+  return 1.0f / sqrtf(wave_sum(s) / (float)ep.norm_dim + ep.norm_eps);
 }
 
 // Sum of the split partials of element (r, c), in split order.  The loads
@@ -168,13 +217,84 @@ __device__ __forceinline__ void qkv_tile_store(const f32x4_t (&acc)[WM][WN], con
   }
 }
 
+// Epilogues whose operand may be an unnormalised x * gain.
+template <int EPI>
+constexpr bool kScaled = EPI == GEMM_EPI_STORE || EPI == GEMM_EPI_SWIGLU || EPI == GEMM_EPI_QKV || EPI == GEMM_EPI_LOGPROB;
+
+template <int WM, int WN>
+__device__ __forceinline__ void scale_rows(f32x4_t (&acc)[WM][WN], const float* s_inv, int wm, int lane) {
+#pragma unroll
+  for (int i = 0; i < WM; ++i) {
+    const f32x4_t f = *reinterpret_cast<const f32x4_t*>(s_inv + (wm * WM + i) * 16 + (lane >> 4) * 4);
+#pragma unroll
+    for (int j = 0; j < WN; ++j) acc[i][j] *= f;
+  }
+}
+
+// RESIDUAL epilogue of one wave.  Through restrict-qualified pointers (each
+// element of x is read once, then written by the same lane) the four rows of a
+// block of accumulators are loaded at once and the next block's loads do not
+// wait on the stores: read-modify-write one element after the other paid a
+// load latency per element, about as long as the tile's K loop at K = 1536.
+template <int WM, int WN, int WAVES_N>
+__device__ __forceinline__ void residual_tile(const f32x4_t (&acc)[WM][WN], const GemmEpi& ep, bool norm, int m0,
+                                              int n0, int M, int N, int wm, int wn, int lane,
+                                              const float* __restrict__ x_in, float* __restrict__ x_out,
+                                              const float* __restrict__ gain, bf16_t* __restrict__ act,
+                                              float* s_ssq) {
+  const int lr = lane & 15;
+  int col[WN];
+  float g[WN];
+#pragma unroll
+  for (int j = 0; j < WN; ++j) {
+    const int c = n0 + (wn * WN + j) * 16 + lr;
+    col[j] = min(c, N - 1);
+    g[j] = norm ? gain[col[j]] : 0.f;
+  }
+#pragma unroll
+  for (int i = 0; i < WM; ++i) {
+    const int rl = (wm * WM + i) * 16 + (lane >> 4) * 4;
+    float xv[4][WN];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) xv[e][j] = x_in[(int64_t)min(m0 + rl + e, M - 1) * ep.ldx + col[j]];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = m0 + rl + e;
+      float ss = 0.f;
+#pragma unroll
+      for (int j = 0; j < WN; ++j) {
+        const bool on = r < M && n0 + (wn * WN + j) * 16 + lr < N;
+        const float v = xv[e][j] + acc[i][j][e];
+        if (!on) continue;
+        ss = fmaf(v, v, ss);
+        x_out[(int64_t)r * ep.ldx + col[j]] = v;
+        if (norm) {
+          const float a = v * g[j];
+          const bf16_t h = f32_to_bf16(a);
+          bf16_t* o = act + (int64_t)r * N + col[j];
+          o[0] = h;
+          o[ep.norm_out.plane] = f32_to_bf16(a - bf16_to_f32(h));
+        }
+      }
+      if (norm) {
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+        if (lr == 0) s_ssq[(rl + e) * WAVES_N + wn] = ss;
+      }
+    }
+  }
+}
+
 // Epilogue of one wave straight from its accumulators: rows m0 + (wm*WM + i)*16
 // + 4*(lane/16) + e, columns n0 + (wn*WN + j)*16 + lane%16; only rows below M
 // and columns below N are stored.
-template <int EPI, int WM, int WN>
-__device__ __forceinline__ void acc_epilogue(const f32x4_t (&acc)[WM][WN], const GemmEpi& ep, int tz, int m0, int n0,
-                                             int M, int N, int wm, int wn, int lane) {
-  const int lr = lane & 15;
+// Every thread of the block calls it; s_ssq holds BM x WAVES_N floats.
+template <int EPI, int BM, int WM, int WN, int WAVES_N>
+__device__ __forceinline__ void acc_epilogue(const f32x4_t (&acc)[WM][WN], const GemmEpi& ep, int tz, int tx, int m0,
+                                             int n0, int M, int N, int wm, int wn, int tid, float* s_ssq) {
+  const int lane = tid & 63, lr = lane & 15;
   if constexpr (EPI == GEMM_EPI_PARTIAL) {
     float* pp = ep.part + tz * ep.part_stride;
 #pragma unroll
@@ -238,9 +358,20 @@ __device__ __forceinline__ void acc_epilogue(const f32x4_t (&acc)[WM][WN], const
           act_store<1>(ep.act, (int64_t)r * ep.act_ld + (c >> 5) * 16 + lr, a / (1.0f + expf(-a)) * b);
         }
       }
+  } else if constexpr (EPI == GEMM_EPI_RESIDUAL) {
+    const bool norm = ep.norm_g != nullptr;
+    residual_tile<WM, WN, WAVES_N>(acc, ep, norm, m0, n0, M, N, wm, wn, lane, ep.x, ep.x, ep.norm_g,
+                                   (bf16_t*)ep.norm_out.base, s_ssq);
+    if (norm) {
+      __syncthreads();
+      if (tid < BM && m0 + tid < M) {
+        float s = s_ssq[tid * WAVES_N];
+#pragma unroll
+        for (int w = 1; w < WAVES_N; ++w) s += s_ssq[tid * WAVES_N + w];
+        ep.ssq_out[(int64_t)(m0 + tid) * ep.ssq_ld + tx] = s;
+      }
+    }
   } else {
-    float* cp = EPI == GEMM_EPI_RESIDUAL ? ep.x : ep.C;
-    const int ld = EPI == GEMM_EPI_RESIDUAL ? ep.ldx : ep.ldc;
 #pragma unroll
     for (int i = 0; i < WM; ++i)
 #pragma unroll
@@ -250,10 +381,7 @@ __device__ __forceinline__ void acc_epilogue(const f32x4_t (&acc)[WM][WN], const
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int r = m0 + (wm * WM + i) * 16 + (lane >> 4) * 4 + e;
-          if (r < M) {
-            if constexpr (EPI == GEMM_EPI_RESIDUAL) cp[(int64_t)r * ld + col] += acc[i][j][e];
-            else cp[(int64_t)r * ld + col] = acc[i][j][e];
-          }
+          if (r < M) ep.C[(int64_t)r * ep.ldc + col] = acc[i][j][e];
         }
       }
   }
@@ -364,6 +492,9 @@ __global__ __launch_bounds__((BM / (16 * WM)) * (BN / (16 * WN)) * 64) void k_ge
   __asm__ volatile("" ::: "memory");
   const int M = min(rows_now, rows_cap);
   if (m0 >= M) return;
+  __shared__ __attribute__((aligned(16))) float s_inv[BM], s_ssq[EPI == GEMM_EPI_RESIDUAL ? BM * WAVES_N : 1];
+  RowScale<BM, NT> scale;
+  if constexpr (kScaled<EPI>) scale.load(ep, m0, rows_cap, tid);
   for (int k = kb0; k < ke; k += STAGES * BK) {
 #pragma unroll
     for (int s = 0; s < STAGES; ++s) {
@@ -396,7 +527,11 @@ __global__ __launch_bounds__((BM / (16 * WM)) * (BN / (16 * WN)) * 64) void k_ge
 #undef RG_FETCH
 #undef RG_STASH
 
-  acc_epilogue<EPI, WM, WN>(acc, ep, tz, m0, n0, M, N, wm, wn, lane);
+  if constexpr (kScaled<EPI>) {
+    scale.finish(ep, m0, rows_cap, tid, s_inv);
+    scale_rows<WM, WN>(acc, s_inv, wm, lane);
+  }
+  acc_epilogue<EPI, BM, WM, WN, WAVES_N>(acc, ep, tz, tx, m0, n0, M, N, wm, wn, tid, s_ssq);
 }
 
 // 16 bytes per lane from global memory straight into LDS: lane l's piece lands
@@ -523,6 +658,9 @@ __global__ __launch_bounds__(512, 2) void k_gemm_dma(const int* __restrict__ d_r
     __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                                                        \
   }                                                                                                           \
   __builtin_amdgcn_sched_group_barrier(0x008, 2 * WM * WN, 0);
+  __shared__ __attribute__((aligned(16))) float s_inv[BM], s_ssq[EPI == GEMM_EPI_RESIDUAL ? BM * WAVES_N : 1];
+  RowScale<BM, NT> scale;
+  if constexpr (kScaled<EPI>) scale.load(ep, m0, rows_cap, tid);   // older than the tiles: covered by their waits
   issue(0);
   if (nk > 1) {
     issue(1);
@@ -554,68 +692,41 @@ __global__ __launch_bounds__(512, 2) void k_gemm_dma(const int* __restrict__ d_r
 #undef RG_READ
 #undef RG_MULTIPLY
 #undef RG_MIX
-  acc_epilogue<EPI, WM, WN>(acc, ep, tz, m0, n0, M, N, wm, wn, lane);
+  if constexpr (kScaled<EPI>) {
+    scale.finish(ep, m0, rows_cap, tid, s_inv);
+    scale_rows<WM, WN>(acc, s_inv, wm, lane);
+  }
+  acc_epilogue<EPI, BM, WM, WN, WAVES_N>(acc, ep, tz, tx, m0, n0, M, N, wm, wn, tid, s_ssq);
 }
 
-// Residual add of the split partials followed by the next RMSNorm of the row
-// (x += sum_s part_s; act = x / sqrt(mean(x^2) + eps) * g): one 1024-thread
-// block per row, thread t owning columns t + 1024 k (k < CPT).  A thread issues
-// its x and g loads and a batch of its split partials before the first add,
-// and the row stays in registers between the sum of squares and the store.
-// The sums run in split order, as in split_sum.
-template <int CPT>
-__global__ __launch_bounds__(1024) void k_split_residual_norm(const int* __restrict__ d_rows,
-                                                               const float* __restrict__ part, int64_t pst,
-                                                               float* __restrict__ x, const float* __restrict__ norm_g,
-                                                               int N, int S, int ldx, GemmEpi ep) {
-  constexpr int NT = 1024;
-  constexpr int BATCH = CPT <= 2 ? 16 : 32 / CPT;   // splits loaded per batch
-  const int r = blockIdx.x;
-  // Blocks of rows past the count (r < the launch's row bound, inside every
-  // buffer) run the same loads and sums but store nothing, so no load waits
-  // for the count.
+// Residual add of the split partials, the next norm's operand x * gain and the
+// row's partial sum of squares: one block of 256 threads per (256 columns,
+// row), a column per thread.  A thread issues its x and gain loads and a batch
+// of its split partials before the first add; blocks of rows past the count (r
+// < the launch's row bound, inside every buffer) run the same loads and sums
+// but store nothing, so no load waits for the count.  The sums run in split
+// order, as in split_sum.
+__global__ __launch_bounds__(256) void k_split_residual(const int* __restrict__ d_rows, float* __restrict__ part,
+                                                        int64_t pst, float* __restrict__ x,
+                                                        const float* __restrict__ norm_g, int N, int S, int ldx,
+                                                        GemmEpi ep) {
+  __shared__ float red[4];
+  const int r = blockIdx.y, c = blockIdx.x * 256 + threadIdx.x, cl = min(c, N - 1);
   const int rows_now = *d_rows;
-  __shared__ float red[16];
-  float* xr = x + (int64_t)r * ldx;
-  const float* pr = part + (int64_t)r * N;
-  float xv[CPT], gv[CPT], acc[CPT];
-#pragma unroll
-  for (int k = 0; k < CPT; ++k) {
-    const int c = threadIdx.x + k * NT;
-    xv[k] = c < N ? xr[c] : 0.f;
-    gv[k] = c < N ? norm_g[c] : 0.f;
-    acc[k] = 0.f;
+  const float x0 = x[(int64_t)r * ldx + cl], g = norm_g[cl];
+  ep.part = part;          // the preloaded copies
+  ep.part_stride = pst;
+  const float xv = x0 + split_sum(ep, S, (int64_t)r * N + cl);
+  const bool live = r < rows_now && c < N;
+  if (live) {
+    x[(int64_t)r * ldx + c] = xv;
+    act_store<1>(ep.norm_out, (int64_t)r * N + c, xv * g);
   }
-  for (int s0 = 0; s0 < S; s0 += BATCH) {
-    float t[BATCH][CPT];
-#pragma unroll
-    for (int j = 0; j < BATCH; ++j)
-#pragma unroll
-      for (int k = 0; k < CPT; ++k) {
-        const int c = threadIdx.x + k * NT;
-        t[j][k] = (s0 + j < S && c < N) ? pr[(s0 + j) * pst + c] : 0.f;
-      }
-#pragma unroll
-    for (int j = 0; j < BATCH; ++j)
-#pragma unroll
-      for (int k = 0; k < CPT; ++k) acc[k] += t[j][k];
-  }
-  float ss = 0.f;
-#pragma unroll
-  for (int k = 0; k < CPT; ++k) {
-    xv[k] += acc[k];
-    ss = fmaf(xv[k], xv[k], ss);
-  }
-  ss = block_sum(ss, red);
-  const float inv = 1.0f / sqrtf(ss / (float)N + ep.norm_eps);
-#pragma unroll
-  for (int k = 0; k < CPT; ++k) {
-    const int c = threadIdx.x + k * NT;
-    if (c < N && r < rows_now) {
-      xr[c] = xv[k];
-      act_store<1>(ep.norm_out, (int64_t)r * N + c, xv[k] * inv * gv[k]);
-    }
-  }
+  const float ss = wave_sum(c < N ? xv * xv : 0.f);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  if (threadIdx.x == 0 && r < rows_now)
+    ep.ssq_out[(int64_t)r * ep.ssq_ld + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 // QKV epilogue of split partials for bf16 models, 16 bytes at a time: thread
@@ -638,6 +749,7 @@ __global__ __launch_bounds__(64) void k_qkv_epilogue4(const int* __restrict__ d_
   const int head = c / hd, p = c % hd, d = (p >> 5) * 16 + (p & 15);
   const f4* pr = reinterpret_cast<const f4*>(part + (int64_t)r * N + c);
   const int64_t pst4 = pst / 4;
+  const float inv = wave_row_scale(ep, r, threadIdx.x);
   f4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
   for (int s0 = 0; s0 < S; s0 += BATCH) {
     f4 ta[BATCH], tb[BATCH];
@@ -654,6 +766,8 @@ __global__ __launch_bounds__(64) void k_qkv_epilogue4(const int* __restrict__ d_
   }
   // a row past the count has no position or page yet
   if (r >= rows_now || u >= N / 8) return;
+  a *= inv;
+  b *= inv;
   const int pos = ep.row_pos[r];
   bf16_t* pool = (bf16_t*)ep.kv_pool;
   const int n_rot = ep.n_q + ep.n_kv;
@@ -710,15 +824,17 @@ __global__ __launch_bounds__(128) void k_split_epilogue(const int* __restrict__ 
     const int q = threadIdx.x;                                     // 64 threads: a pair of columns each
     const int gc = blockIdx.x * 128 + (q >> 4) * 32 + (q & 15);   // gate column; up is 16 further
     const int gl = min(gc, N - 17);                                // gc itself while in range (N % 32 == 0)
-    const float gt = split_sum(ep, S, (int64_t)r * N + gl);
-    const float up = split_sum(ep, S, (int64_t)r * N + gl + 16);
+    const float inv = wave_row_scale(ep, r, threadIdx.x);
+    const float gt = split_sum(ep, S, (int64_t)r * N + gl) * inv;
+    const float up = split_sum(ep, S, (int64_t)r * N + gl + 16) * inv;
     if (r >= rows_now || gc >= N) return;
     act_store<1>(ep.act, (int64_t)r * ep.act_ld + (gc >> 5) * 16 + (q & 15), gt / (1.0f + expf(-gt)) * up);
   } else {
     const int c = blockIdx.x * 128 + threadIdx.x;
+    const float inv = EPI == GEMM_EPI_STORE ? wave_row_scale(ep, r, threadIdx.x & 63) : 1.f;
     const float v = split_sum(ep, S, (int64_t)r * N + min(c, N - 1));
     if (r >= rows_now || c >= N) return;
-    if constexpr (EPI == GEMM_EPI_STORE) ep.C[(int64_t)r * ep.ldc + c] = v;
+    if constexpr (EPI == GEMM_EPI_STORE) ep.C[(int64_t)r * ep.ldc + c] = v * inv;
     else ep.x[(int64_t)r * ep.ldx + c] += v;
   }
 }
@@ -739,9 +855,12 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, c
                                                   int N, int K, GemmEpi ep) {
   constexpr int BM = 16 * WMT;
   __shared__ float red[4][BM][33];
+  __shared__ float s_inv[BM];
   const int rows_now = *d_rows;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lk = (lane >> 4) * 4;
   const int m0 = blockIdx.y * BM, n0 = blockIdx.x * 32;
+  RowScale<BM, 256> scale;
+  if constexpr (kScaled<EPI>) scale.load(ep, m0, rows_cap, tid);
   const float* wp[2];
   const float* ap[WMT];
 #pragma unroll
@@ -786,21 +905,33 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, c
       for (int e = 0; e < 4; ++e) red[wave][i * 16 + (lane >> 4) * 4 + e][j * 16 + lr] = acc[i][j][e];
   __syncthreads();
   const int M = min(rows_now, rows_cap);
-  for (int i = tid; i < BM * 16; i += 256) {   // columns c and c + 16 of a row
+  if constexpr (kScaled<EPI>) scale.finish(ep, m0, rows_cap, tid, s_inv);
+  for (int i = tid; i < BM * 16; i += 256) {   // columns c and c + 16 of a row: 16 neighbouring lanes a row
     const int rr = i >> 4, cc = i & 15, r = m0 + rr, c = n0 + cc;
-    if (r >= M || c >= N) continue;
-    const float v0 = (red[0][rr][cc] + red[1][rr][cc]) + (red[2][rr][cc] + red[3][rr][cc]);
-    const float v1 = (red[0][rr][cc + 16] + red[1][rr][cc + 16]) + (red[2][rr][cc + 16] + red[3][rr][cc + 16]);
+    const bool on0 = r < M && c < N, on1 = r < M && c + 16 < N;
+    const float inv = kScaled<EPI> ? s_inv[rr] : 1.f;
+    const float v0 = inv * ((red[0][rr][cc] + red[1][rr][cc]) + (red[2][rr][cc] + red[3][rr][cc]));
+    const float v1 = inv * ((red[0][rr][cc + 16] + red[1][rr][cc + 16]) + (red[2][rr][cc + 16] + red[3][rr][cc + 16]));
     if constexpr (EPI == GEMM_EPI_QKV) {
-      qkv_store_f32(ep, r, c, v0, v1);
+      if (on0) qkv_store_f32(ep, r, c, v0, v1);
     } else if constexpr (EPI == GEMM_EPI_SWIGLU) {
-      act_store<0>(ep.act, (int64_t)r * ep.act_ld + (n0 >> 1) + cc, v0 / (1.0f + expf(-v0)) * v1);
+      if (on0) act_store<0>(ep.act, (int64_t)r * ep.act_ld + (n0 >> 1) + cc, v0 / (1.0f + expf(-v0)) * v1);
     } else if constexpr (EPI == GEMM_EPI_RESIDUAL) {
-      ep.x[(int64_t)r * ep.ldx + c] += v0;
-      if (c + 16 < N) ep.x[(int64_t)r * ep.ldx + c + 16] += v1;
+      float* xp = ep.x + (int64_t)r * ep.ldx + c;
+      const float x0 = on0 ? xp[0] + v0 : 0.f, x1 = on1 ? xp[16] + v1 : 0.f;
+      if (on0) xp[0] = x0;
+      if (on1) xp[16] = x1;
+      if (ep.norm_g) {
+        if (on0) act_store<0>(ep.norm_out, (int64_t)r * N + c, x0 * ep.norm_g[c]);
+        if (on1) act_store<0>(ep.norm_out, (int64_t)r * N + c + 16, x1 * ep.norm_g[c + 16]);
+        float ss = fmaf(x0, x0, x1 * x1);
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+        if (cc == 0 && r < M) ep.ssq_out[(int64_t)r * ep.ssq_ld + blockIdx.x] = ss;
+      }
     } else {
-      ep.C[(int64_t)r * ep.ldc + c] = v0;
-      if (c + 16 < N) ep.C[(int64_t)r * ep.ldc + c + 16] = v1;
+      if (on0) ep.C[(int64_t)r * ep.ldc + c] = v0;
+      if (on1) ep.C[(int64_t)r * ep.ldc + c + 16] = v1;
     }
   }
 }
@@ -904,16 +1035,8 @@ hipError_t launch_dma(const void* A, int lda, int64_t a_plane, const void* W, in
 
 hipError_t launch_split_epilogue(const int* d_rows, int rows_ub, int N, int S, const GemmEpi& ep, hipStream_t st) {
   if (ep.mode == GEMM_EPI_RESIDUAL && ep.norm_g) {
-    const int cpt = (N + 1023) / 1024;
-#define RG_SRN(C)                                                                                             \
-  hipLaunchKernelGGL((k_split_residual_norm<C>), dim3(rows_ub), dim3(1024), 0, st, d_rows, ep.part, ep.part_stride,   \
-                     ep.x, ep.norm_g, N, S, ep.ldx, ep)
-    if (cpt <= 1) RG_SRN(1);
-    else if (cpt <= 2) RG_SRN(2);
-    else if (cpt <= 4) RG_SRN(4);
-    else if (cpt <= 8) RG_SRN(8);
-    else return hipErrorInvalidValue;   // rows wider than 8192
-#undef RG_SRN
+    hipLaunchKernelGGL(k_split_residual, dim3((N + 255) / 256, rows_ub), dim3(256), 0, st, d_rows, ep.part,
+                       ep.part_stride, ep.x, ep.norm_g, N, S, ep.ldx, ep);
     return hipGetLastError();
   }
   dim3 grid((N + 127) / 128, rows_ub);
@@ -1055,6 +1178,10 @@ GemmPlan gemm_plan(int dtype, int rows_ub, int N, int K, int max_splits) {
   p.k_per_split = (int)(ceil_div(ceil_div(K, S), 64) * 64);
   p.splits = (int)ceil_div(K, p.k_per_split);
   return p;
+}
+
+int gemm_ssq_parts(int dtype, const GemmPlan& p, int N) {
+  return (int)ceil_div(N, dtype != 1 ? 32 : p.splits > 1 ? 256 : p.bn);
 }
 
 int gemm_lse_parts(const GemmPlan& p, int N) { return (int)ceil_div(N, p.bn) * (p.bn == 256 ? 4 : 2); }

@@ -59,8 +59,10 @@ struct GemmEpi {
   int mode;
   float* C; int ldc;                      // STORE
   float* x; int ldx;                      // RESIDUAL
-  const float* norm_g; float norm_eps; ActOut norm_out;   // RESIDUAL with K split: then RMSNorm the row
-                                                          // into norm_out (ignored without a split)
+  const float* norm_g; ActOut norm_out; float* ssq_out;   // RESIDUAL: the next RMSNorm's gain (or NULL), its operand
+                                          // x * gain, and gemm_ssq_parts partial sums of x^2 per row
+  const float* ssq_in; int ssq_n;         // STORE, SWIGLU, QKV, LOGPROB: scale row r's products by 1 / sqrt(sum of its
+  int ssq_ld; int norm_dim; float norm_eps;   // ssq_n partials / norm_dim + norm_eps) (NULL: 1); row stride of ssq_in, ssq_out
   ActOut act; int act_ld;                 // SWIGLU
   float* q_out; void* kv_pool; KvGeom geom; int layer;      // QKV
   const int32_t* page_tab; int tab_stride; const int32_t* row_tab; const int32_t* row_pos;
@@ -78,6 +80,8 @@ struct GemmPlan {
   int splits, k_per_split;
 };
 GemmPlan gemm_plan(int dtype, int rows_ub, int N, int K, int max_splits);
+// Partial sums of squares per row that a RESIDUAL launch by plan p leaves.
+int gemm_ssq_parts(int dtype, const GemmPlan& p, int N);
 // Partial logsumexps per row of a LOGPROB launch by plan p.
 int gemm_lse_parts(const GemmPlan& p, int N);
 
