@@ -49,7 +49,11 @@ constexpr int RG_RING = 64;            // async active-count slots
 constexpr int RG_LOOKAHEAD = 4;        // decode steps enqueued beyond the last seen count
 constexpr int RG_PROF_RING = 8192;     // event pairs in flight when profiling
 constexpr int RG_SAMPLE_SLICES_MAX = 32;  // vocabulary slices per sampled row
-constexpr int RG_LM_SLICE_ROWS = 2048;    // recompute: lm-head rows per slice (when the activations hold them)
+constexpr int RG_LM_SLICE_ROWS = 1024;    // recompute: lm-head rows per slice where logits are written (few rows, fp32)
+// Rows of a recompute chunk, if the policy's completions can number that many.
+// With the prompts' 1100 tokens as the bound a gpt2s chunk gave each projection
+// 27 to 216 tiles of 128 rows; at 4096 rows the chip is full.
+constexpr int RG_CHUNK_ROWS = 4096;
 constexpr int RG_PROF_PHASES = 2 + 8;     // prefill, decode, decode by row bucket (16 .. 512, larger)
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -62,7 +66,9 @@ struct rg_policy {
   int dtype = 0;
   size_t eb = 4;
   int d = 0, V = 0, L = 0, F = 0, hd = 0, nq = 0, nkv = 0, q_dim = 0, kv_dim = 0, qkv_n = 0;
-  int page_tok = RG_PAGE_TOK, max_pages = 0, m_act = 0;
+  int page_tok = RG_PAGE_TOK, max_pages = 0;
+  int m_step = 0;   // rows of the largest prefill or decode step
+  int m_act = 0;    // rows the activations hold: m_step, or a recompute chunk
   KvGeom geom{};
 
   void* w_embed = nullptr;
@@ -629,7 +635,8 @@ int rg_policy_create(const rg_config* cfg, const rg_weights* w, const rg_limits*
   pol->kv_dim = c.n_kv_heads * c.head_dim;
   pol->qkv_n = pol->q_dim + 2 * pol->kv_dim;
   pol->max_pages = (int)ceil_div(lim.max_context, pol->page_tok) + 1;
-  pol->m_act = std::max(lim.max_prompt_tokens, lim.max_seqs);
+  pol->m_step = std::max(lim.max_prompt_tokens, lim.max_seqs);
+  pol->m_act = std::max<int64_t>(pol->m_step, std::min<int64_t>(RG_CHUNK_ROWS, (int64_t)lim.max_seqs * lim.max_context));
   KvGeom& g = pol->geom;
   g.page_tok = pol->page_tok; g.n_layers = pol->L; g.n_kv = pol->nkv; g.head_dim = pol->hd;
   g.slab_elems = 2LL * pol->nkv * pol->page_tok * pol->hd;
@@ -729,12 +736,15 @@ int rg_policy_create(const rg_config* cfg, const rg_weights* w, const rg_limits*
   // split-K partials (bf16 models; fp32 projections are not split)
   pol->cpart_elems = pol->dtype == RG_DTYPE_BF16 ? std::max(M * maxN, (int64_t)RG_SPLIT_MAX * S * maxN) : 0;
   // (row, context chunk) slots of one attention launch: decode steps (rows <=
-  // S, prefix slots and chunks), and a full activation chunk of prefill or
-  // recompute rows, which splits contexts longer than one chunk's span
+  // S, prefix slots and chunks); a full activation chunk of prefill or recompute
+  // rows, which splits contexts longer than one chunk's span; and fewer rows
+  // (the last of a recompute), which take more chunks each, up to two of 2048
+  // rows and about ATT_ITEMS_TARGET + rows / 2 work items in all
   pol->att_rowchunks = std::max<int64_t>(
-      std::max<int64_t>(lim.max_prompt_tokens, S) + ATT_ITEMS_TARGET +
-          S * (RG_PRE_MAX_SLOTS + ceil_div(lim.max_context, 1024)),
-      M * att_row_chunks((int)std::min<int64_t>(M, INT32_MAX), pol->nkv, lim.max_context));
+      {std::max<int64_t>(lim.max_prompt_tokens, S) + ATT_ITEMS_TARGET +
+           S * (RG_PRE_MAX_SLOTS + ceil_div(lim.max_context, 1024)),
+       M * att_row_chunks((int)std::min<int64_t>(M, INT32_MAX), pol->nkv, lim.max_context),
+       2 * std::min<int64_t>(M, 2048) + ATT_ITEMS_TARGET});
   pol->hist_cap = lim.max_context;
   pol->ssq_ld = (int)ceil_div(d, 32);   // the narrowest column tiles
   struct Piece { void** p; size_t bytes; };
@@ -918,7 +928,7 @@ int rollout_group(rg_policy* pol, const int32_t* prompts, const int32_t* prompt_
       if (m_ub == 0) { n_steps = known_t + 1; break; }
     }
     if (n_steps || oom) break;
-    const int rows_ub = std::min(row_bucket(m_ub), pol->m_act);
+    const int rows_ub = std::min(row_bucket(m_ub), pol->m_step);
     if (graphs_on) {
       hipGraphExec_t exec;
       if ((rc = step_graph(pol, graphs, rows_ub, ctx_all, sm, ca, pre, &exec))) return rc;

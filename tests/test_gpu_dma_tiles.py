@@ -52,3 +52,35 @@ def test_dma_tiles_match_oracle(si, rows):
     print(f"gap {gap:.2e}", flush=True)
     assert np.isfinite(got).all() and gap <= 4e-3
     pol.close()
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("dtype,hd", [("bf16", 64), ("f32", 32)])
+def test_recompute_across_chunks(dtype, hd):
+    """More completion positions than a recompute chunk holds (4096 rows): a
+    sequence split over the boundary attends to its own earlier positions from
+    the first chunk and scores like any other.  The prompts alone (60 tokens)
+    no longer bound the chunk.  Tolerance as above; fp32 models 5e-5."""
+    import torch
+    assert torch.cuda.is_available()
+    shape = ModelShape(2, 64, 2, 1, hd, 128, 144, 1e4, dtype=dtype)
+    w = make_weights(shape, 6)
+    rng = np.random.default_rng(11)
+    P, G, max_new = 3, [9, 8, 8], 190
+    N = sum(G)
+    prompts = [rng.integers(0, shape.vocab - 1, size=20).astype(np.int32) for _ in range(P)]
+    lengths = rng.integers(160, max_new + 1, size=N).astype(np.int32)
+    rows = int(lengths.sum()) - N
+    starts = np.concatenate([[0], np.cumsum(lengths - 1)])
+    assert 4096 < rows and 4096 not in starts          # the boundary falls inside a sequence
+    tok = rng.integers(0, shape.vocab - 1, size=(N, max_new)).astype(np.int32)
+    print(f"recompute chunks: {dtype}, {rows} rows", flush=True)
+    pol = make_policy(shape, w, max_seqs=N, max_prompts=P, max_prompt_tokens=60, max_context=20 + max_new)
+    got = pol.recompute_logprobs(prompts_to_device(prompts), G, torch.from_numpy(tok).cuda(),
+                                 torch.from_numpy(lengths).cuda()).cpu().numpy()
+    want = teacher_forced_logprobs(oracle_for(shape, w), prompts, G, tok, lengths)
+    valid = np.arange(max_new)[None, :] < lengths[:, None]
+    gap = float(np.max(np.abs(got[valid] - want[valid])))
+    print(f"gap {gap:.2e}", flush=True)
+    assert np.isfinite(got).all() and gap <= (5e-5 if dtype == "f32" else 4e-3)
+    pol.close()
