@@ -12,6 +12,7 @@ namespace {
 // row combines the slices in order (ties to the lowest id), decides the
 // token and writes the outputs.
 constexpr int SAMPLE_THREADS = 256;
+constexpr float LN2 = 0.693147180559945309f;
 
 __global__ __launch_bounds__(SAMPLE_THREADS) void k_sample_slice(SampleArgs a) {
   const int r = blockIdx.y;
@@ -56,12 +57,16 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void k_sample_slice(SampleArgs a) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const uint32_t bits = (uint32_t)(w.v[j >> 1] >> (32 * (j & 1)));
-      const float u = rg_uniform_from_bits(bits);
-      // Gumbel noise -log(-log u): the inner log keeps full accuracy (for u
-      // near 1 its result is ~6e-8, where only a relative-error log is safe);
-      // the outer one takes an argument in [6e-8, 16.7] and needs ~1e-7
-      // absolute accuracy, which the hardware logarithm gives
-      float sc = zt[j] + (-__logf(-logf(u)));
+      // u = (2 (x >> 9) + 1) 2^-24, as 1 + (x >> 9) 2^-23 less 1 - 2^-24 (exact)
+      const float u = __uint_as_float((bits >> 9) | 0x3F800000u) - 0.999999940395355224609375f;
+      // Gumbel noise -ln(-ln u) = -ln 2 log2(-log2 u) - ln(ln 2); the constant,
+      // the same for every token, is left out.  The hardware logarithm's
+      // relative error is 1.2e-7 at most over all 2^23 values of u, also near
+      // u = 1 where -log2 u is ~8.6e-8, so the noise is within 1.8e-6 of its
+      // value in 64 bits (1.9e-6 with the library's logarithm inside, whose
+      // instructions bounded the kernel: 512 rows of 151,936 129 -> 102 us, of
+      // which reading the logits takes 63).
+      float sc = fmaf(-LN2, __builtin_amdgcn_logf(-__builtin_amdgcn_logf(u)), zt[j]);
       if (vb == eos_vb && j == eos_j) sc = -INFINITY;
       // a thread scans increasing ids, so a strict > keeps the lowest id of a tie
       if (sc > best) { best = sc; best_v = vb * 8 + j; }
