@@ -1163,7 +1163,8 @@ GemmPlan dma_plan(int rows_ub, int N, int K, int max_splits) {
 // 24 MiB.
 GemmPlan gemm_plan(int dtype, int rows_ub, int N, int K, int max_splits) {
   if (dtype != 1) return GemmPlan{16, 32, false, 1, K};
-  max_splits = std::max(1, std::min(max_splits, GEMM_MAX_SPLITS));
+  // the split reductions take a row per block in grid dimension y (at most 65535)
+  max_splits = rows_ub > 65535 ? 1 : std::max(1, std::min(max_splits, GEMM_MAX_SPLITS));
   const int bm = staged_tile_rows(rows_ub, N);
   const double work = 4.0 * rows_ub * N * K;   // both planes
   if (rows_ub > 1024 || bm == 0 || work >= (rows_ub > 128 ? 10e9 : rows_ub > 64 ? 30e9 : 1e300))
