@@ -96,7 +96,12 @@ typedef struct rg_weights {
 } rg_weights;
 
 /* Capacity of a policy, fixed at creation: the device workspace (activations,
- * logits, attention partials) and the KV page pool are allocated once. */
+ * logits, attention partials) and the KV page pool are allocated once.  The
+ * workspace holds the largest step (max(max_prompt_tokens, max_seqs) rows) and,
+ * for recompute_logprobs, up to 4096 rows of activations: as many as cost at
+ * most an eighth of the weights and the KV pool (or 32 MiB) more, and none
+ * where the device has no room for them (recompute_logprobs then takes
+ * smaller, slower chunks). */
 typedef struct rg_limits {
   int32_t max_seqs;           /* largest N = sum(G) of one rollout                        */
   int32_t max_prompts;        /* largest P                                                */

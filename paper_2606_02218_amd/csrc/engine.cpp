@@ -49,11 +49,15 @@ constexpr int RG_RING = 64;            // async active-count slots
 constexpr int RG_LOOKAHEAD = 4;        // decode steps enqueued beyond the last seen count
 constexpr int RG_PROF_RING = 8192;     // event pairs in flight when profiling
 constexpr int RG_SAMPLE_SLICES_MAX = 32;  // vocabulary slices per sampled row
-constexpr int RG_LM_SLICE_ROWS = 1024;    // recompute: lm-head rows per slice where logits are written (few rows, fp32)
+constexpr int RG_LM_SLICE_ROWS = 1024;    // recompute: most lm-head rows per slice where logits are written (few rows, fp32)
 // Rows of a recompute chunk, if the policy's completions can number that many.
 // With the prompts' 1100 tokens as the bound a gpt2s chunk gave each projection
 // 27 to 216 tiles of 128 rows; at 4096 rows the chip is full.
 constexpr int RG_CHUNK_ROWS = 4096;
+// What the workspace may grow by for rows beyond the largest step's (a policy
+// that only rolls out never uses them): an eighth of the weights and the KV
+// pool, or this where they are small.
+constexpr int64_t RG_CHUNK_BYTES = 32LL << 20;
 constexpr int RG_PROF_PHASES = 2 + 8;     // prefill, decode, decode by row bucket (16 .. 512, larger)
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -85,7 +89,7 @@ struct rg_policy {
   float* x = nullptr;
   void* abuf = nullptr;   // activation operand (ping)
   void* abuf2 = nullptr;  // activation operand (pong)
-  int64_t a_plane = 0;   // elements between the hi and lo planes of abuf (bf16 models)
+  int64_t a_plane = 0, a2_plane = 0;   // elements between the hi and lo planes of abuf, abuf2 (bf16 models)
   float* cpart = nullptr;
   int64_t cpart_elems = 0;
   float* ssq = nullptr;   // [m_act][ssq_ld] partial sums of squares of x, for the next RMSNorm
@@ -94,7 +98,8 @@ struct rg_policy {
   float* att_o = nullptr;
   float* att_ml = nullptr;
   int64_t att_rowchunks = 0;
-  int64_t logit_rows = 0;   // rows of the fp32 logits buffer
+  int64_t logit_rows = 0;    // rows of the fp32 logits buffer
+  int64_t logit_elems = 0;   // its elements (at least logit_rows * V)
   float* logits = nullptr;
   float* sample_part = nullptr;   // [rows][RG_SAMPLE_SLICES_MAX][4]
   int32_t *page_tab = nullptr, *seq_grp = nullptr, *seq_npages = nullptr, *seq_nshared = nullptr,
@@ -245,8 +250,8 @@ void set_row_scale(const rg_policy* pol, GemmEpi* ep, int ssq_n, int K, int row0
 // One projection with its epilogue; the split plan and workspace are filled in here.
 // ssq_n: partial sums of squares per row behind the operand (0: normalised already); a RESIDUAL with a next norm sets it to
 // the ones it leaves.
-int gemm(rg_policy* pol, hipStream_t st, int kind, const void* A, int K, const void* W, int N, const int* d_rows,
-         int rows_ub, GemmEpi ep, int* ssq_n, bool allow_split = true) {
+int gemm(rg_policy* pol, hipStream_t st, int kind, const void* A, int64_t a_plane, int K, const void* W, int N,
+         const int* d_rows, int rows_ub, GemmEpi ep, int* ssq_n, bool allow_split = true) {
   const int64_t fit = pol->cpart_elems / ((int64_t)rows_ub * N);   // splits the workspace holds
   const GemmPlan p = gemm_plan(pol->dtype, rows_ub, N, K, allow_split ? (int)std::min<int64_t>(fit, RG_SPLIT_MAX) : 1);
   ep.ssq_ld = pol->ssq_ld;
@@ -258,7 +263,7 @@ int gemm(rg_policy* pol, hipStream_t st, int kind, const void* A, int K, const v
   }
   ep.part = pol->cpart;
   ep.part_stride = (int64_t)rows_ub * N;
-  LAUNCH(kind, launch_gemm(pol->dtype, p, A, K, pol->a_plane, W, K, d_rows, rows_ub, N, K, ep, st));
+  LAUNCH(kind, launch_gemm(pol->dtype, p, A, K, a_plane, W, K, d_rows, rows_ub, N, K, ep, st));
   return RG_OK;
 }
 
@@ -313,20 +318,20 @@ int run_layers(rg_policy* pol, hipStream_t st, const int* d_rows, int rows_ub, i
   resid.mode = GEMM_EPI_RESIDUAL; resid.x = pol->x; resid.ldx = pol->d;
   resid.norm_out = ActOut{pol->abuf, pol->a_plane};
   GemmEpi swig{};
-  swig.mode = GEMM_EPI_SWIGLU; swig.act = ActOut{pol->abuf2, pol->a_plane}; swig.act_ld = pol->F;
+  swig.mode = GEMM_EPI_SWIGLU; swig.act = ActOut{pol->abuf2, pol->a2_plane}; swig.act_ld = pol->F;
   int rc;
   int ssq_n = 0;   // layer 0's operand is normalised (by the embedding kernels)
 
   for (int l = 0; l < pol->L; ++l) {
     qkv.layer = l;
-    if ((rc = gemm(pol, st, RG_K_GEMM_QKV, pol->abuf, pol->d, pol->w_qkv[l], pol->qkv_n, d_rows, rows_ub, qkv,
-                   &ssq_n)))
+    if ((rc = gemm(pol, st, RG_K_GEMM_QKV, pol->abuf, pol->a_plane, pol->d, pol->w_qkv[l], pol->qkv_n, d_rows, rows_ub,
+                   qkv, &ssq_n)))
       return rc;
     if (tiles) {
       LAUNCH_TIMED(RG_K_ATTN, launch_attention_tile(pol->qbuf, pol->nq, pol->nkv, pol->hd, pol->kv_pool, pol->geom, l,
                                                     pol->page_tab, tab_stride, pol->row_tab, pol->row_pos,
                                                     pol->tile_r0, pol->tile_nr, tiles->d_tiles, tiles->tiles_ub,
-                                                    ctx_max, pol->abuf2, pol->a_plane, st));
+                                                    ctx_max, pol->abuf2, pol->a2_plane, st));
     } else {
     if (plan.pre_slots)
       LAUNCH_TIMED(RG_K_ATTN, launch_attention_prefix(pol->qbuf, pol->nq, pol->nkv, pol->hd, pol->kv_pool, pol->geom, l,
@@ -335,21 +340,23 @@ int run_layers(rg_policy* pol, hipStream_t st, const int* d_rows, int rows_ub, i
                                                 pol->att_o, pol->att_ml, st));
     LAUNCH_TIMED(RG_K_ATTN, launch_attention(pol->dtype, pol->qbuf, pol->nq, pol->nkv, pol->hd, pol->kv_pool, pol->geom, l,
                                        pol->page_tab, tab_stride, pol->row_tab, pol->row_pos, pol->row_beg, ctx_max,
-                                       plan, pol->att_o, pol->att_ml, pol->abuf2, pol->a_plane, d_rows, rows_ub, st));
+                                       plan, pol->att_o, pol->att_ml, pol->abuf2, pol->a2_plane, d_rows, rows_ub, st));
     // one slot, or chunks merged inside the attention kernel: it wrote abuf2 itself
     if (plan.n_slots > 1 && !att_merges_in_kernel(pol->dtype, plan, rows_ub, pol->nkv))
       LAUNCH(RG_K_ATTN_MERGE, launch_attn_merge(pol->dtype, pol->att_o, pol->att_ml, pol->nq, pol->hd, pol->row_pos,
-                                                pol->row_beg, plan, pol->abuf2, pol->a_plane, d_rows, rows_ub, st));
+                                                pol->row_beg, plan, pol->abuf2, pol->a2_plane, d_rows, rows_ub, st));
     }
     // O projection + residual, the MLP norm's operand into abuf
     resid.norm_g = pol->g_ffn[l];
-    if ((rc = gemm(pol, st, RG_K_GEMM_O, pol->abuf2, pol->q_dim, pol->w_o[l], pol->d, d_rows, rows_ub, resid, &ssq_n)))
+    if ((rc = gemm(pol, st, RG_K_GEMM_O, pol->abuf2, pol->a2_plane, pol->q_dim, pol->w_o[l], pol->d, d_rows, rows_ub,
+                   resid, &ssq_n)))
       return rc;
-    if ((rc = gemm(pol, st, RG_K_GEMM_GU, pol->abuf, pol->d, pol->w_gu[l], 2 * pol->F, d_rows, rows_ub, swig, &ssq_n)))
+    if ((rc = gemm(pol, st, RG_K_GEMM_GU, pol->abuf, pol->a_plane, pol->d, pol->w_gu[l], 2 * pol->F, d_rows, rows_ub,
+                   swig, &ssq_n)))
       return rc;
     resid.norm_g = l + 1 < pol->L ? pol->g_attn[l + 1] : (final_norm_rows ? pol->w_final : nullptr);
-    if ((rc = gemm(pol, st, RG_K_GEMM_DOWN, pol->abuf2, pol->F, pol->w_down[l], pol->d, d_rows, rows_ub, resid,
-                   &ssq_n)))
+    if ((rc = gemm(pol, st, RG_K_GEMM_DOWN, pol->abuf2, pol->a2_plane, pol->F, pol->w_down[l], pol->d, d_rows, rows_ub,
+                   resid, &ssq_n)))
       return rc;
   }
   pol->ssq_n = ssq_n;
@@ -366,7 +373,7 @@ int run_head(rg_policy* pol, hipStream_t st, const int* d_rows, int rows_ub, con
   GemmEpi store{};
   store.mode = GEMM_EPI_STORE; store.C = pol->logits; store.ldc = pol->V;
   int ssq_n = src_rows ? 0 : pol->ssq_n;
-  return gemm(pol, st, RG_K_GEMM_LM, pol->abuf, pol->d, pol->w_lm, pol->V, d_rows, rows_ub, store, &ssq_n, false);
+  return gemm(pol, st, RG_K_GEMM_LM, pol->abuf, pol->a_plane, pol->d, pol->w_lm, pol->V, d_rows, rows_ub, store, &ssq_n, false);
 }
 
 // Row bound used for a decode step: the host's bound rounded up, so that the
@@ -636,7 +643,6 @@ int rg_policy_create(const rg_config* cfg, const rg_weights* w, const rg_limits*
   pol->qkv_n = pol->q_dim + 2 * pol->kv_dim;
   pol->max_pages = (int)ceil_div(lim.max_context, pol->page_tok) + 1;
   pol->m_step = std::max(lim.max_prompt_tokens, lim.max_seqs);
-  pol->m_act = std::max<int64_t>(pol->m_step, std::min<int64_t>(RG_CHUNK_ROWS, (int64_t)lim.max_seqs * lim.max_context));
   KvGeom& g = pol->geom;
   g.page_tok = pol->page_tok; g.n_layers = pol->L; g.n_kv = pol->nkv; g.head_dim = pol->hd;
   g.slab_elems = 2LL * pol->nkv * pol->page_tok * pol->hd;
@@ -728,74 +734,106 @@ int rg_policy_create(const rg_config* cfg, const rg_weights* w, const rg_limits*
   if ((rc = pol->alloc(&pol->kv_pool, (size_t)pol->pool_pages * g.slab_elems * pol->L * eb))) return bail(rc);
 
   // ---- workspace
-  const int64_t M = pol->m_act, S = lim.max_seqs, P = lim.max_prompts;
-  // the rollout needs max(S, P) rows of logits; the recompute's lm head runs
-  // in slices of this many rows
-  pol->logit_rows = std::max<int64_t>({S, P, std::min<int64_t>(M, RG_LM_SLICE_ROWS)});
+  const int64_t S = lim.max_seqs, P = lim.max_prompts;
   const int64_t maxN = std::max<int64_t>({pol->qkv_n, 2LL * pol->F, d});
-  // split-K partials (bf16 models; fp32 projections are not split)
-  pol->cpart_elems = pol->dtype == RG_DTYPE_BF16 ? std::max(M * maxN, (int64_t)RG_SPLIT_MAX * S * maxN) : 0;
-  // (row, context chunk) slots of one attention launch: decode steps (rows <=
-  // S, prefix slots and chunks); a full activation chunk of prefill or recompute
-  // rows, which splits contexts longer than one chunk's span; and fewer rows
-  // (the last of a recompute), which take more chunks each, up to two of 2048
-  // rows and about ATT_ITEMS_TARGET + rows / 2 work items in all
-  pol->att_rowchunks = std::max<int64_t>(
-      {std::max<int64_t>(lim.max_prompt_tokens, S) + ATT_ITEMS_TARGET +
-           S * (RG_PRE_MAX_SLOTS + ceil_div(lim.max_context, 1024)),
-       M * att_row_chunks((int)std::min<int64_t>(M, INT32_MAX), pol->nkv, lim.max_context),
-       2 * std::min<int64_t>(M, 2048) + ATT_ITEMS_TARGET});
+  const int64_t kmax = std::max(pol->q_dim, pol->F);
   pol->hist_cap = lim.max_context;
   pol->ssq_ld = (int)ceil_div(d, 32);   // the narrowest column tiles
+  // split-K partials (bf16 models; fp32 projections are not split): those of a
+  // step's rows.  A recompute chunk splits as far as they reach.
+  pol->cpart_elems = pol->dtype == RG_DTYPE_BF16 ? std::max(pol->m_step * maxN, (int64_t)RG_SPLIT_MAX * S * maxN) : 0;
+  // rows up to which the recompute's lm head writes logits (direct-to-LDS plans
+  // leave a row's partial logsumexps instead)
+  int64_t written = RG_LM_SLICE_ROWS;
+  while (written > 0 && gemm_plan(pol->dtype, (int)written, pol->V, pol->d, 1).dma) --written;
   struct Piece { void** p; size_t bytes; };
-  const int64_t kmax = std::max<int64_t>({d, pol->q_dim, pol->F});
-  pol->a_plane = pol->dtype == RG_DTYPE_BF16 ? M * kmax : 0;
-  std::vector<Piece> pieces = {
-      {(void**)&pol->x, (size_t)(M * d * 4)},
-      {&pol->abuf, (size_t)(M * kmax * 4)},   // fp32, or two bf16 planes
-      {&pol->abuf2, (size_t)(M * kmax * 4)},
-      {(void**)&pol->cpart, (size_t)(pol->cpart_elems * 4)},
-      {(void**)&pol->qbuf, (size_t)(M * pol->q_dim * 4)},
-      {(void**)&pol->ssq, (size_t)(M * pol->ssq_ld * 4)},
-      {(void**)&pol->att_o, (size_t)(pol->att_rowchunks * pol->nq * pol->hd * 4)},
-      {(void**)&pol->att_ml, (size_t)(pol->att_rowchunks * pol->nq * 2 * 4)},
-      {(void**)&pol->logits, (size_t)(pol->logit_rows * pol->V * 4)},
-      {(void**)&pol->sample_part, (size_t)(std::max(S, P) * RG_SAMPLE_SLICES_MAX * 4 * 4)},
-      {(void**)&pol->page_tab, (size_t)((S + P) * pol->max_pages * 4)},
-      {(void**)&pol->seq_grp, (size_t)(S * 4)},
-      {(void**)&pol->seq_npages, (size_t)(S * 4)},
-      {(void**)&pol->seq_nshared, (size_t)(S * 4)},
-      {(void**)&pol->seq_forced, (size_t)(S * 4)},
-      {(void**)&pol->grp_off, (size_t)((P + 1) * 4)},
-      {(void**)&pol->prompt_off, (size_t)((P + 1) * 4)},
-      {(void**)&pol->plen, (size_t)(P * 4)},
-      {(void**)&pol->G_dev, (size_t)(P * 4)},
-      {(void**)&pol->last_rows, (size_t)(P * 4)},
-      {(void**)&pol->act_seq, (size_t)(S * 4)},
-      {(void**)&pol->act_tok, (size_t)(S * 4)},
-      {(void**)&pol->done, (size_t)(S * 4)},
-      {(void**)&pol->row_tab, (size_t)(M * 4)},
-      {(void**)&pol->row_pos, (size_t)(M * 4)},
-      {(void**)&pol->row_beg, (size_t)(M * 4)},
-      {(void**)&pol->grp_row0, (size_t)(P * 4)},
-      {(void**)&pol->grp_row1, (size_t)(P * 4)},
-      {(void**)&pol->coff, (size_t)((S + 1) * 4)},
-      {(void**)&pol->row_tgt, (size_t)(M * 4)},
-      {(void**)&pol->row_out, (size_t)(M * 4)},
-      {(void**)&pol->row_lrow, (size_t)(S * 4)},
-      {(void**)&pol->tile_r0, (size_t)((M + S + 1) * 4)},
-      {(void**)&pol->tile_nr, (size_t)((M + S + 1) * 4)},
-      {(void**)&pol->free_stack, (size_t)(pol->pool_pages * 4)},
-      {(void**)&pol->state, 64},
-      {(void**)&pol->copy_pairs, (size_t)(2 * S * pol->max_pages * 4)},
-      {(void**)&pol->hist_active, (size_t)(pol->hist_cap * 4)},
-      {(void**)&pol->hist_groups, (size_t)(pol->hist_cap * 4)},
-      {(void**)&pol->hist_ctx, (size_t)(pol->hist_cap * 8)},
+  // The pieces for activations of M rows; sets the sizes that go with M.
+  auto pieces_for = [&](int64_t M) {
+    pol->m_act = (int)M;
+    // the rollout needs max(S, P) rows of logits, the recompute's lm head a
+    // slice of the rows it writes, or the partials of up to a chunk's rows
+    pol->logit_rows = std::max<int64_t>({S, P, std::min<int64_t>(M, written)});
+    const int lm_rows = (int)std::min<int64_t>(M, RG_CHUNK_ROWS);
+    const GemmPlan lmp = gemm_plan(pol->dtype, lm_rows, pol->V, pol->d, 1);
+    pol->logit_elems = std::max<int64_t>(pol->logit_rows * pol->V,
+                                         lmp.dma ? (int64_t)lm_rows * (2 * gemm_lse_parts(lmp, pol->V) + 1) : 0);
+    // (row, context chunk) slots of one attention launch: decode steps (rows <=
+    // S, prefix slots and chunks); a full activation chunk of prefill or recompute
+    // rows, which splits contexts longer than one chunk's span; and fewer rows
+    // (the last of a recompute), which take more chunks each, up to two of 2048
+    // rows and about ATT_ITEMS_TARGET + rows / 2 work items in all
+    pol->att_rowchunks = std::max<int64_t>(
+        {std::max<int64_t>(lim.max_prompt_tokens, S) + ATT_ITEMS_TARGET +
+             S * (RG_PRE_MAX_SLOTS + ceil_div(lim.max_context, 1024)),
+         M * att_row_chunks((int)std::min<int64_t>(M, INT32_MAX), pol->nkv, lim.max_context),
+         2 * std::min<int64_t>(M, 2048) + ATT_ITEMS_TARGET});
+    pol->a_plane = pol->dtype == RG_DTYPE_BF16 ? M * d : 0;
+    pol->a2_plane = pol->dtype == RG_DTYPE_BF16 ? M * kmax : 0;
+    return std::vector<Piece>{
+        {(void**)&pol->x, (size_t)(M * d * 4)},
+        {&pol->abuf, (size_t)(M * d * 4)},   // fp32, or two bf16 planes
+        {&pol->abuf2, (size_t)(M * kmax * 4)},
+        {(void**)&pol->cpart, (size_t)(pol->cpart_elems * 4)},
+        {(void**)&pol->qbuf, (size_t)(M * pol->q_dim * 4)},
+        {(void**)&pol->ssq, (size_t)(M * pol->ssq_ld * 4)},
+        {(void**)&pol->att_o, (size_t)(pol->att_rowchunks * pol->nq * pol->hd * 4)},
+        {(void**)&pol->att_ml, (size_t)(pol->att_rowchunks * pol->nq * 2 * 4)},
+        {(void**)&pol->logits, (size_t)(pol->logit_elems * 4)},
+        {(void**)&pol->sample_part, (size_t)(std::max(S, P) * RG_SAMPLE_SLICES_MAX * 4 * 4)},
+        {(void**)&pol->page_tab, (size_t)((S + P) * pol->max_pages * 4)},
+        {(void**)&pol->seq_grp, (size_t)(S * 4)},
+        {(void**)&pol->seq_npages, (size_t)(S * 4)},
+        {(void**)&pol->seq_nshared, (size_t)(S * 4)},
+        {(void**)&pol->seq_forced, (size_t)(S * 4)},
+        {(void**)&pol->grp_off, (size_t)((P + 1) * 4)},
+        {(void**)&pol->prompt_off, (size_t)((P + 1) * 4)},
+        {(void**)&pol->plen, (size_t)(P * 4)},
+        {(void**)&pol->G_dev, (size_t)(P * 4)},
+        {(void**)&pol->last_rows, (size_t)(P * 4)},
+        {(void**)&pol->act_seq, (size_t)(S * 4)},
+        {(void**)&pol->act_tok, (size_t)(S * 4)},
+        {(void**)&pol->done, (size_t)(S * 4)},
+        {(void**)&pol->row_tab, (size_t)(M * 4)},
+        {(void**)&pol->row_pos, (size_t)(M * 4)},
+        {(void**)&pol->row_beg, (size_t)(M * 4)},
+        {(void**)&pol->grp_row0, (size_t)(P * 4)},
+        {(void**)&pol->grp_row1, (size_t)(P * 4)},
+        {(void**)&pol->coff, (size_t)((S + 1) * 4)},
+        {(void**)&pol->row_tgt, (size_t)(M * 4)},
+        {(void**)&pol->row_out, (size_t)(M * 4)},
+        {(void**)&pol->row_lrow, (size_t)(S * 4)},
+        {(void**)&pol->tile_r0, (size_t)((M + S + 1) * 4)},
+        {(void**)&pol->tile_nr, (size_t)((M + S + 1) * 4)},
+        {(void**)&pol->free_stack, (size_t)(pol->pool_pages * 4)},
+        {(void**)&pol->state, 64},
+        {(void**)&pol->copy_pairs, (size_t)(2 * S * pol->max_pages * 4)},
+        {(void**)&pol->hist_active, (size_t)(pol->hist_cap * 4)},
+        {(void**)&pol->hist_groups, (size_t)(pol->hist_cap * 4)},
+        {(void**)&pol->hist_ctx, (size_t)(pol->hist_cap * 8)},
+    };
   };
-  size_t total = 0;
-  for (auto& pc : pieces) total += (pc.bytes + 255) & ~(size_t)255;
-  char* arena;
-  if ((rc = pol->alloc((void**)&arena, total))) return bail(rc);
+  auto bytes_of = [](const std::vector<Piece>& ps) {
+    size_t total = 0;
+    for (auto& pc : ps) total += (pc.bytes + 255) & ~(size_t)255;
+    return total;
+  };
+  // Rows of the activations: a recompute chunk's, as far as those beyond the
+  // largest step's cost at most the allowance; the step's alone where the
+  // device has no room for more.
+  const int64_t chunk = std::min<int64_t>(RG_CHUNK_ROWS, S * lim.max_context);
+  const size_t least = bytes_of(pieces_for(pol->m_step));
+  const size_t most = least + (size_t)std::max<int64_t>(RG_CHUNK_BYTES, pol->dev_bytes / 8);
+  int64_t rows = std::max<int64_t>(pol->m_step, chunk);
+  while (rows > pol->m_step && bytes_of(pieces_for(rows)) > most) rows = std::max<int64_t>(pol->m_step, rows - 128);
+  char* arena = nullptr;
+  std::vector<Piece> pieces = pieces_for(rows);
+  rc = pol->alloc((void**)&arena, bytes_of(pieces));
+  if (rc == RG_ENOMEM && rows > pol->m_step) {
+    (void)hipGetLastError();
+    pieces = pieces_for(pol->m_step);
+    rc = pol->alloc((void**)&arena, least);
+  }
+  if (rc) return bail(rc);
   for (auto& pc : pieces) {
     *pc.p = arena;
     arena += (pc.bytes + 255) & ~(size_t)255;
@@ -1039,7 +1077,7 @@ int recompute_logprobs(rg_policy* pol, const int32_t* prompts, const int32_t* pr
     const GemmPlan lmp = gemm_plan(pol->dtype, n, pol->V, pol->d, 1);
     if (lmp.dma) {
       const int parts = gemm_lse_parts(lmp, pol->V);
-      const int64_t cap = std::min<int64_t>(n, pol->logit_rows * pol->V / (2 * parts + 1));
+      const int64_t cap = std::min<int64_t>(n, pol->logit_elems / (2 * parts + 1));
       for (int h0 = 0; h0 < n; h0 += (int)cap) {
         const int m = (int)std::min<int64_t>(cap, n - h0);
         GemmEpi ep{};
