@@ -316,6 +316,9 @@ __device__ __forceinline__ void acc_epilogue(const f32x4_t (&acc)[WM][WN], const
     // one (max, sum of exp(z/T - max)) per row and wave column, over the wave's
     // columns below N: a lane folds its WN columns, the 16 lanes of a row the
     // rest.  Past N the logit counts as -inf.
+    // expf, as where the logits are written: 8.4e-8 relative at most over [-87,
+    // 0]; __expf, which rounds x log2(e) first, is off by 5e-7 from -8 and 1e-6
+    // from -20 (it takes 3 % off the four-layer 1.5B recompute).
     const float T = ep.temperature;
     const bool unit_T = T == 1.0f;               // z / 1 == z exactly
     const int part = (n0 / (16 * WN)) + wn;      // this wave's column range
@@ -337,7 +340,7 @@ __device__ __forceinline__ void acc_epilogue(const f32x4_t (&acc)[WM][WN], const
         for (int o = 8; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
         float s = 0.f;
 #pragma unroll
-        for (int j = 0; j < WN; ++j) s += z[j] == -INFINITY ? 0.f : z[j] == m ? 1.f : __expf(z[j] - m);
+        for (int j = 0; j < WN; ++j) s += z[j] == -INFINITY ? 0.f : z[j] == m ? 1.f : expf(z[j] - m);
 #pragma unroll
         for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
         if (lr == 0 && r < M) ep.lse_part[(int64_t)r * ep.lse_ld + part] = float2{m, s};
