@@ -543,7 +543,7 @@ __global__ __launch_bounds__((BM / (16 * WM)) * (BN / (16 * WN)) * 64) void k_ge
 // buffers apart); the kernel places the waits itself.  No register is written.
 __device__ __forceinline__ void dma16(uint32_t lds, uint32_t voff, const bf16_t* sbase) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(sbase)
-               : "memory");
+               : "memory", "m0");
 }
 
 // Large tiles: BM x BN output, eight waves, K steps of 64 through two LDS

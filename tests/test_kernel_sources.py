@@ -20,3 +20,17 @@ def test_scored_log_probabilities_use_the_library_exponential():
     largest terms hide most of it, so no log-probability tells the two apart."""
     for name in ("k_gemm.hip", "k_loss.hip"):
         assert not re.search(r"__expf|__builtin_amdgcn_exp2f|\bexp2f", _source(name)), name
+
+
+def test_assembly_lists_the_scalar_registers_it_writes():
+    """Inline assembly that sets m0 (the LDS address of a direct load) tells the
+    compiler so, which keeps values of its own there (LDS and message
+    instructions)."""
+    found = 0
+    for name in sorted(os.listdir(CSRC)):
+        for m in re.finditer(r"\basm\s*(?:volatile)?\s*\((.*?)\)\s*;", _source(name), flags=re.S):
+            body = m.group(1)
+            if re.search(r"s_mov_b32\s+m0", body):
+                found += 1
+                assert '"m0"' in body.rsplit(":", 1)[1], (name, body)
+    assert found
