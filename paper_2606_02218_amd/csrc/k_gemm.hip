@@ -231,17 +231,16 @@ __device__ __forceinline__ void scale_rows(f32x4_t (&acc)[WM][WN], const float* 
   }
 }
 
-// RESIDUAL epilogue of one wave.  Through restrict-qualified pointers (each
-// element of x is read once, then written by the same lane) the four rows of a
-// block of accumulators are loaded at once and the next block's loads do not
-// wait on the stores: read-modify-write one element after the other paid a
-// load latency per element, about as long as the tile's K loop at K = 1536.
+// RESIDUAL epilogue of one wave.  The four rows of a block of accumulators are
+// loaded at once, and the next block's before this one's stores (which the
+// compiler may not move them across): read-modify-write one element after the
+// other paid a load latency per element, about as long as the tile's K loop at
+// K = 1536.
 template <int WM, int WN, int WAVES_N>
 __device__ __forceinline__ void residual_tile(const f32x4_t (&acc)[WM][WN], const GemmEpi& ep, bool norm, int m0,
                                               int n0, int M, int N, int wm, int wn, int lane,
-                                              const float* __restrict__ x_in, float* __restrict__ x_out,
-                                              const float* __restrict__ gain, bf16_t* __restrict__ act,
-                                              float* s_ssq) {
+                                              float* __restrict__ x, const float* __restrict__ gain,
+                                              bf16_t* __restrict__ act, float* s_ssq) {
   const int lr = lane & 15;
   int col[WN];
   float g[WN];
@@ -251,14 +250,19 @@ __device__ __forceinline__ void residual_tile(const f32x4_t (&acc)[WM][WN], cons
     col[j] = min(c, N - 1);
     g[j] = norm ? gain[col[j]] : 0.f;
   }
-#pragma unroll
-  for (int i = 0; i < WM; ++i) {
+  float xv[2][4][WN];
+  auto fetch = [&](int i) {
     const int rl = (wm * WM + i) * 16 + (lane >> 4) * 4;
-    float xv[4][WN];
 #pragma unroll
     for (int e = 0; e < 4; ++e)
 #pragma unroll
-      for (int j = 0; j < WN; ++j) xv[e][j] = x_in[(int64_t)min(m0 + rl + e, M - 1) * ep.ldx + col[j]];
+      for (int j = 0; j < WN; ++j) xv[i & 1][e][j] = x[(int64_t)min(m0 + rl + e, M - 1) * ep.ldx + col[j]];
+  };
+  fetch(0);
+#pragma unroll
+  for (int i = 0; i < WM; ++i) {
+    const int rl = (wm * WM + i) * 16 + (lane >> 4) * 4;
+    if (i + 1 < WM) fetch(i + 1);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int r = m0 + rl + e;
@@ -266,10 +270,10 @@ __device__ __forceinline__ void residual_tile(const f32x4_t (&acc)[WM][WN], cons
 #pragma unroll
       for (int j = 0; j < WN; ++j) {
         const bool on = r < M && n0 + (wn * WN + j) * 16 + lr < N;
-        const float v = xv[e][j] + acc[i][j][e];
+        const float v = xv[i & 1][e][j] + acc[i][j][e];
         if (!on) continue;
         ss = fmaf(v, v, ss);
-        x_out[(int64_t)r * ep.ldx + col[j]] = v;
+        x[(int64_t)r * ep.ldx + col[j]] = v;
         if (norm) {
           const float a = v * g[j];
           const bf16_t h = f32_to_bf16(a);
@@ -363,7 +367,7 @@ __device__ __forceinline__ void acc_epilogue(const f32x4_t (&acc)[WM][WN], const
       }
   } else if constexpr (EPI == GEMM_EPI_RESIDUAL) {
     const bool norm = ep.norm_g != nullptr;
-    residual_tile<WM, WN, WAVES_N>(acc, ep, norm, m0, n0, M, N, wm, wn, lane, ep.x, ep.x, ep.norm_g,
+    residual_tile<WM, WN, WAVES_N>(acc, ep, norm, m0, n0, M, N, wm, wn, lane, ep.x, ep.norm_g,
                                    (bf16_t*)ep.norm_out.base, s_ssq);
     if (norm) {
       __syncthreads();

@@ -34,3 +34,16 @@ def test_assembly_lists_the_scalar_registers_it_writes():
                 found += 1
                 assert '"m0"' in body.rsplit(":", 1)[1], (name, body)
     assert found
+
+
+def test_restrict_pointers_of_a_call_are_distinct():
+    """No call hands one pointer expression to two parameters: the kernels'
+    helpers take restrict-qualified pointers, and memory that one of them
+    writes may not be read through another."""
+    for name in sorted(os.listdir(CSRC)):
+        if not name.endswith(".hip"):
+            continue
+        for m in re.finditer(r"\b(\w+)(?:<[^;{}()]*>)?\(([^;{}]*)\);", _source(name)):
+            args = re.findall(r"(?<![\w.>])(?:ep|a|sm|p)\.\w+(?![\w.\[(])", m.group(2))
+            ptrs = [x for x in args if x.split(".")[1] in ("x", "C", "q_out", "kv_pool", "part", "norm_g", "tgt_z")]
+            assert len(ptrs) == len(set(ptrs)), (name, m.group(0)[:120])
