@@ -511,44 +511,72 @@ hipError_t launch_setup(const SetupArgs& a, hipStream_t st) {
 }
 
 // ------------------------------------------------------------------ group length statistics
-// One block per group: the group's offset is the sum of the sizes before it;
-// its lengths are ranked in LDS (rank = smaller values plus equal values
-// earlier in the group) and placed in sorted order.  One wave per group while
-// groups average at most 64 (no barrier leaves the wave: 7.1 -> 4 us at 8 to 32
-// groups), else four.
+// One block of four waves per group: the group's offset is the sum of the sizes
+// before it; its lengths are ranked in LDS (rank = smaller values plus equal
+// values earlier in the group) and placed in sorted order.  The first wave
+// alone, without a barrier, takes a group of at most 64; the average says
+// nothing about a large group among small ones (1024 among 63 of 4 members, us a
+// launch: 463 on the one wave that the average asks for, 107 on four).
 __global__ __launch_bounds__(256) void k_group_stats(const int32_t* __restrict__ lengths, const int32_t* __restrict__ G,
                                                      int P, int N, double tau, float* __restrict__ stats) {
   constexpr int GMAX = 1024;
   __shared__ int s_len[GMAX], s_sorted[GMAX];
   __shared__ long long s_off[4];
-  const int p = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
+  const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int g = G[p];
-  long long part = 0;   // integer sum: order-independent, exact for int32 sizes
-  for (int i = tid; i < p; i += nt) part += (long long)G[i];
+  const bool small = g <= 64;
+  long long off = 0;   // integer sum: order-independent, exact for int32 sizes
+  if (P <= 256) {      // each wave sums all sizes itself
+    if (small && tid >= 64) return;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
-  if ((tid & 63) == 0) s_off[tid >> 6] = part;
-  __syncthreads();
-  long long off = 0;
-  for (int w = 0; w < nt >> 6; ++w) off += s_off[w];
+    for (int u = 0; u < 4; ++u) off += lane + 64 * u < p ? (long long)G[lane + 64 * u] : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) off += __shfl_xor(off, o, 64);
+  } else {
+    long long part = 0;
+    for (int i = tid; i < p; i += 256) part += (long long)G[i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
+    if (lane == 0) s_off[tid >> 6] = part;
+    __syncthreads();
+    off = (s_off[0] + s_off[1]) + (s_off[2] + s_off[3]);
+    if (small && tid >= 64) return;
+  }
   float* out = stats + 4 * (int64_t)p;
   if (g < 1 || g > GMAX || off < 0 || off + g > N) {
     if (tid < 4) out[tid] = NAN;
     return;
   }
+  // what the group's threads (nt of them) wrote to LDS is seen by all of them
+  auto sync = [&]() {
+    if (small) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    } else {
+      __syncthreads();
+    }
+  };
+  const int nt = small ? 64 : 256;
   for (int i = tid; i < g; i += nt) s_len[i] = lengths[off + i];
-  __syncthreads();
+  sync();
   for (int i = tid; i < g; i += nt) {
     const int v = s_len[i];
     int rank = 0;
+    if (small) {
 #pragma unroll 4
-    for (int j = 0; j < g; ++j) {
-      const int u = s_len[j];
-      rank += (u < v) || (u == v && j < i);
+      for (int j = 0; j < g; ++j) {
+        const int u = s_len[j];
+        rank += (u < v) || (u == v && j < i);
+      }
+    } else {
+      for (int j = 0; j < g; ++j) {
+        const int u = s_len[j];
+        rank += (u < v) || (u == v && j < i);
+      }
     }
     s_sorted[rank] = v;
   }
-  __syncthreads();
+  sync();
   if (tid == 0) {
     const int lmax = s_sorted[g - 1];
     const double med = (g & 1) ? (double)s_sorted[g / 2] : ((double)s_sorted[g / 2 - 1] + (double)s_sorted[g / 2]) / 2.0;
@@ -567,7 +595,7 @@ __global__ __launch_bounds__(256) void k_group_stats(const int32_t* __restrict__
 hipError_t launch_group_stats(const int32_t* lengths, const int32_t* G, int P, int N, double tau, float* stats,
                               hipStream_t st) {
   if (P < 1) return hipSuccess;
-  hipLaunchKernelGGL(k_group_stats, dim3(P), dim3(N / P <= 64 ? 64 : 256), 0, st, lengths, G, P, N, tau, stats);
+  hipLaunchKernelGGL(k_group_stats, dim3(P), dim3(256), 0, st, lengths, G, P, N, tau, stats);
   return hipGetLastError();
 }
 
