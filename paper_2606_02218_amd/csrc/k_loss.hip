@@ -1,6 +1,7 @@
 // GRPO loss forward: the row set-up of the teacher-forced log-probability
 // recompute over finished rollouts, the per-token log-probability gather
 // after the lm head, and the clipped surrogate reduction.
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -245,29 +246,31 @@ __global__ __launch_bounds__(SURR_THREADS) void k_surrogate_seq(SurrogateArgs a,
   __shared__ double s_acc[SURR_THREADS / 64];
   __shared__ int s_clip[SURR_THREADS / 64];
   const int tid = threadIdx.x, lane = tid & 63;
-  const int s = blockIdx.x;
+  const int64_t s = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  if (s >= a.N) return;
   const int L = a.lengths[s];
   const double A = (double)a.adv[s];
   if (L < 1 || L > a.max_new) {
     if (tid == 0) rec[s] = SurrogateRec{0.0, -1, 0};
     return;
   }
-  const float* nw = a.new_lp + (int64_t)s * a.max_new;
-  const float* od = a.old_lp + (int64_t)s * a.max_new;
+  const float* nw = a.new_lp + s * a.max_new;
+  const float* od = a.old_lp + s * a.max_new;
   const double lo = 1.0 - a.eps_lo, hi = 1.0 + a.eps_hi;
   double acc = 0.0;
   int clips = 0;
-  for (int i0 = tid; i0 < L; i0 += 4 * SURR_THREADS) {
+  const unsigned len = (unsigned)L;   // i0 may pass 2^31
+  for (unsigned i0 = tid; i0 < len; i0 += 4 * SURR_THREADS) {
     float x[4], y[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {   // every load issued before the first use; past the end the first token again
-      const int i = i0 + u * SURR_THREADS < L ? i0 + u * SURR_THREADS : 0;
+      const unsigned i = i0 + u * SURR_THREADS < len ? i0 + u * SURR_THREADS : 0;
       x[u] = nw[i];
       y[u] = od[i];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      if (i0 + u * SURR_THREADS < L) {
+      if (i0 + u * SURR_THREADS < len) {
         const double rho = exp((double)x[u] - (double)y[u]);
         const double un = rho * A;
         const double cl = fmin(fmax(rho, lo), hi) * A;
@@ -449,7 +452,10 @@ hipError_t surrogate_static_scratch(SurrogateRec** out) {
 
 hipError_t launch_surrogate(const SurrogateArgs& a, SurrogateRec* rec, hipStream_t st) {
   if (a.N < 1 || !rec) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_surrogate_seq, dim3(a.N), dim3(SURR_THREADS), 0, st, a, rec);
+  // a launch holds fewer than 2^32 threads in a dimension: past 2^20 sequences in rows of blocks
+  const int gx = std::min(a.N, 1 << 20);
+  hipLaunchKernelGGL(k_surrogate_seq, dim3(gx, (unsigned)(((int64_t)a.N + gx - 1) / gx)), dim3(SURR_THREADS), 0, st, a,
+                     rec);
   const int nt = a.P >= 1024 ? 1024 : (a.P + 63) / 64 * 64;   // a thread per group
   hipLaunchKernelGGL(k_surrogate_reduce, dim3(1), dim3(nt), 0, st, a, (const SurrogateRec*)rec);
   return hipGetLastError();

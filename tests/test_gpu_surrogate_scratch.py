@@ -43,3 +43,27 @@ def test_scratch_surrogate_refuses_bad_scratch():
     for bad in (None, C.c_void_p(8)):
         rc = lib.grpo_surrogate_scratch(p[0], p[1], p[2], p[3], p[4], 1, 4, 8, None, 0.2, 0.2, 0, p[5], bad, None)
         assert rc == _lib.RG_EINVAL and b"scratch" in lib.rg_last_error()
+
+
+@pytest.mark.timeout(120)
+@pytest.mark.parametrize("N", [(1 << 20) + 1, (1 << 24) + 1])
+def test_more_sequences_than_one_row_of_blocks(N):
+    """2^24 sequences of one token and one more: with 256 threads each they pass
+    the 2^32 threads that one dimension of a launch holds.  Terms of one sign, so
+    that sums of 1.7e7 of them agree to a few fp64 roundings (1e-12)."""
+    import torch
+    import paper_2606_02218_amd as rg
+    rng = np.random.default_rng(3)
+    old = rng.normal(-3.0, 1.0, (N, 1)).astype(np.float32)
+    new = (old + rng.normal(0, 0.2, (N, 1)).astype(np.float32)).astype(np.float32)
+    adv = rng.uniform(0.1, 2.0, N).astype(np.float32)
+    G = np.full(-(-N // 4096), 4096, np.int32)
+    G[-1] = N - 4096 * (len(G) - 1)
+    print(f"surrogate of {N} sequences", flush=True)
+    d = [torch.from_numpy(a).cuda() for a in (new, old, adv, np.ones(N, np.int32), G)]
+    got = rg.grpo_surrogate(*d, eps_lo=0.2, eps_hi=0.28, mode="token").cpu().numpy()
+    rho = np.exp(new[:, 0].astype(np.float64) - old[:, 0])
+    un, cl = rho * adv, np.clip(rho, 0.8, 1.28) * adv
+    assert got[2] == N and got[3] == N
+    assert got[0] == pytest.approx(-np.minimum(un, cl).mean(), rel=1e-12)
+    assert got[1] == pytest.approx((cl < un).mean(), abs=3.0 / N)   # a clip decided by the last bit of exp
