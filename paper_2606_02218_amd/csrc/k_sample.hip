@@ -1,5 +1,6 @@
 // Token sampling, retirement/compaction, sibling fork, rollout set-up and the
 // group-relative advantage.
+#include <algorithm>
 #include <type_traits>
 
 #include "rg_device.h"
@@ -522,7 +523,9 @@ __global__ __launch_bounds__(256) void k_group_stats(const int32_t* __restrict__
   constexpr int GMAX = 1024;
   __shared__ int s_len[GMAX], s_sorted[GMAX];
   __shared__ long long s_off[4];
-  const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int64_t pb = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+  if (pb >= P) return;
+  const int p = (int)pb, tid = threadIdx.x, lane = tid & 63;
   const int g = G[p];
   const bool small = g <= 64;
   long long off = 0;   // integer sum: order-independent, exact for int32 sizes
@@ -595,7 +598,10 @@ __global__ __launch_bounds__(256) void k_group_stats(const int32_t* __restrict__
 hipError_t launch_group_stats(const int32_t* lengths, const int32_t* G, int P, int N, double tau, float* stats,
                               hipStream_t st) {
   if (P < 1) return hipSuccess;
-  hipLaunchKernelGGL(k_group_stats, dim3(P), dim3(256), 0, st, lengths, G, P, N, tau, stats);
+  // a launch holds fewer than 2^32 threads in a dimension: past 2^20 groups in rows of blocks
+  const int gx = std::min(P, 1 << 20);
+  hipLaunchKernelGGL(k_group_stats, dim3(gx, (unsigned)(((int64_t)P + gx - 1) / gx)), dim3(256), 0, st, lengths, G, P, N,
+                     tau, stats);
   return hipGetLastError();
 }
 

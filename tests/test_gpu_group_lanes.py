@@ -77,3 +77,20 @@ def test_large_groups_among_small_ones(P, g, big):
     L = rng.integers(1, 50, size=N).astype(np.int32)
     st = rg.Sagc().group_stats(torch.from_numpy(L).cuda(), Gd).cpu().numpy()
     np.testing.assert_array_equal(st, np.asarray(oracle_stats(L, G, 1.25), np.float32))
+
+
+@pytest.mark.timeout(120)
+def test_statistics_of_more_groups_than_one_row_of_blocks():
+    """2^20 groups and one more: blocks come in rows of 2^20.  The last groups
+    of both rows and some between, against numpy."""
+    import torch
+    import paper_2606_02218_amd as rg
+    P = (1 << 20) + 1
+    rng = np.random.default_rng(8)
+    L = rng.integers(1, 5000, size=(P, 2)).astype(np.int32)
+    print(f"statistics of {P} groups", flush=True)
+    st = rg.Sagc().group_stats(torch.from_numpy(L.reshape(-1)).cuda(),
+                               torch.full((P,), 2, dtype=torch.int32, device="cuda")).cpu().numpy()
+    lmax, med = L.max(1).astype(np.float64), L.sum(1) / 2.0
+    want = np.stack([lmax, med, lmax / med, (lmax / med > 1.25)], 1).astype(np.float32)
+    np.testing.assert_array_equal(st, want)
