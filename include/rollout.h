@@ -133,9 +133,11 @@ typedef struct rg_policy rg_policy;  /* opaque: packed weights, KV pool, workspa
                                         block (a test and measurement aid)                 */
 
 /* Sampling options.  A NULL rg_sampling* means temperature 1, natural EOS, no
- * flags.  Token t of sequence s is argmax_v fp32(z_v/T) + g_v where g_v is the
- * fp32 Gumbel variate -log(-log(u)) of the stream documented at
- * rg_gumbel_bits() for (seed, t, s, v); ties go to the lowest id.  With
+ * flags.  Token t of sequence s is argmax_v fp32(fp32(z_v/T) + g_v) where g_v is
+ * the Gumbel variate -log(-log(u)), less the constant -log(log 2) that is the
+ * same for every token, of the stream documented at rg_gumbel_bits() for (seed,
+ * t, s, v); the variate is within 2e-6 of its value in 64 bits (see
+ * rg_gumbel_noise()) and ties of the scores go to the lowest id.  With
  * forced_len, EOS scores -inf while t < forced_len[s]-1 and token
  * forced_len[s]-1 is EOS (the synthetic stand-in for a policy's own stopping
  * time).  The reported log-probability is that of the emitted token under the
@@ -324,6 +326,12 @@ int rg_philox_blocks(uint64_t key0, uint64_t key1, const uint64_t* ctr, int64_t 
  * v < vocab, from block Philox((v>>3, t, s, 0), (seed, 1)), 32-bit half (v&1)
  * (low first) of 64-bit word ((v&7)>>1).  out is DEVICE uint32 [vocab]. */
 int rg_gumbel_bits(uint64_t seed, int32_t t, int32_t s, int32_t vocab, uint32_t* out, void* stream);
+
+/* The Gumbel variates that the sampler adds to fp32(z/T): out[i], i < n, is
+ * -log(-log u) + log(log 2) in fp32 for u = (2 (first + i) + 1) 2^-24, the
+ * uniform of every 32-bit value x with x >> 9 == first + i.  0 <= first, 1 <= n,
+ * first + n <= 2^23.  out is DEVICE fp32 [n].  Enqueue only. */
+int rg_gumbel_noise(int32_t first, int32_t n, float* out, void* stream);
 
 /* Measured streaming ceiling for the HBM rooflines (not a step of the path):
  * one launch of `blocks` workgroups of 256 threads that stream `bytes` (a

@@ -22,7 +22,7 @@ EXPORTS = ["rg_last_error", "rg_policy_create", "rg_policy_destroy", "rg_policy_
            "group_advantage", "rg_philox_blocks", "rg_gumbel_bits", "rg_hbm_probe", "rg_step_history", "rg_kernel_times",
            "sagc_init", "sagc_group_stats", "sagc_step", "sagc_beta_draw", "group_filter",
            "recompute_logprobs", "grpo_surrogate", "rg_decode_attention_chunks", "rg_phase_times",
-           "grpo_surrogate_noalloc", "grpo_surrogate_scratch"]
+           "grpo_surrogate_noalloc", "grpo_surrogate_scratch", "rg_gumbel_noise"]
 SAGC_MAX_SIZES = 8
 
 
@@ -120,6 +120,7 @@ def load_library():
                                     C.c_void_p]
     lib.rg_philox_blocks.argtypes = [C.c_uint64, C.c_uint64, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p]
     lib.rg_gumbel_bits.argtypes = [C.c_uint64, C.c_int32, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p]
+    lib.rg_gumbel_noise.argtypes = [C.c_int32, C.c_int32, C.c_void_p, C.c_void_p]
     lib.rg_hbm_probe.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_int32, C.c_int32, C.c_void_p]
     lib.rg_step_history.argtypes = [C.c_void_p, C.c_int32, C.POINTER(C.c_int32), C.c_void_p, C.c_void_p, C.c_void_p]
     lib.rg_kernel_times.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.POINTER(C.c_double), C.POINTER(C.c_int64)]

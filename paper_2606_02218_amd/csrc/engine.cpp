@@ -1214,6 +1214,14 @@ int rg_gumbel_bits(uint64_t seed, int32_t t, int32_t s, int32_t vocab, uint32_t*
   return RG_OK;
 }
 
+int rg_gumbel_noise(int32_t first, int32_t n, float* out, void* stream) {
+  if (!out || first < 0 || n < 1 || (int64_t)first + n > (1 << 23))
+    return fail(RG_EINVAL, "rg_gumbel_noise: bad argument");
+  hipError_t e = launch_gumbel_noise((uint32_t)first, n, out, (hipStream_t)stream);
+  if (e != hipSuccess) return fail(RG_EHIP, std::string("rg_gumbel_noise: ") + hipGetErrorString(e));
+  return RG_OK;
+}
+
 int rg_hbm_probe(const void* src, void* dst, int64_t bytes, int32_t mode, int32_t blocks, void* stream) {
   if (!src || !dst || bytes < 16 || bytes % 16 || (mode != 0 && mode != 1) || blocks < 1 || blocks > (1 << 20))
     return fail(RG_EINVAL, "rg_hbm_probe: bad argument");

@@ -17,6 +17,25 @@ namespace {
 constexpr int SAMPLE_THREADS = 256;
 constexpr float LN2 = 0.693147180559945309f;
 
+// log2(-log2 u) for the 32-bit value x of a token, u = (2 (x >> 9) + 1) 2^-24.
+// The Gumbel noise is -ln(-ln u) = -ln 2 log2(-log2 u) - ln(ln 2); the constant,
+// the same for every token, is left out of the scores.  Over all 2^23 values of u
+// the noise is within 1.81e-6 of its value in 64 bits, 7.3e-8 rms (1.88e-6 and
+// 9.6e-8 with the library's logarithm inside, whose instructions bounded the
+// slice kernel: 512 rows of 151,936 129 -> 102 us, of which reading the logits
+// takes 63): the hardware logarithm keeps its relative error near u = 1 too,
+// where -log2 u is ~8.6e-8.
+__device__ __forceinline__ float gumbel_log2(uint32_t x) {
+  // 1 + (x >> 9) 2^-23 less 1 - 2^-24: exact
+  const float u = __uint_as_float((x >> 9) | 0x3F800000u) - 0.999999940395355224609375f;
+  return __builtin_amdgcn_logf(-__builtin_amdgcn_logf(u));
+}
+
+__global__ void k_gumbel_noise(uint32_t first, int64_t n, float* __restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) out[i] = -LN2 * gumbel_log2((first + (uint32_t)i) << 9);
+}
+
 __global__ __launch_bounds__(SAMPLE_THREADS) void k_sample_slice(SampleArgs a) {
   const int r = blockIdx.y;
   if (r >= *a.d_rows) return;
@@ -60,16 +79,7 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void k_sample_slice(SampleArgs a) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const uint32_t bits = (uint32_t)(w.v[j >> 1] >> (32 * (j & 1)));
-      // u = (2 (x >> 9) + 1) 2^-24, as 1 + (x >> 9) 2^-23 less 1 - 2^-24 (exact)
-      const float u = __uint_as_float((bits >> 9) | 0x3F800000u) - 0.999999940395355224609375f;
-      // Gumbel noise -ln(-ln u) = -ln 2 log2(-log2 u) - ln(ln 2); the constant,
-      // the same for every token, is left out.  The hardware logarithm's
-      // relative error is 1.2e-7 at most over all 2^23 values of u, also near
-      // u = 1 where -log2 u is ~8.6e-8, so the noise is within 1.8e-6 of its
-      // value in 64 bits (1.9e-6 with the library's logarithm inside, whose
-      // instructions bounded the kernel: 512 rows of 151,936 129 -> 102 us, of
-      // which reading the logits takes 63).
-      float sc = fmaf(-LN2, __builtin_amdgcn_logf(-__builtin_amdgcn_logf(u)), zt[j]);
+      float sc = fmaf(-LN2, gumbel_log2(bits), zt[j]);
       if (vb == eos_vb && j == eos_j) sc = -INFINITY;
       // a thread scans increasing ids, so a strict > keeps the lowest id of a tie
       if (sc > best) { best = sc; best_v = vb * 8 + j; }
@@ -473,6 +483,12 @@ __global__ __launch_bounds__(1024) void k_group_advantage(const float* __restric
 }
 
 }  // namespace
+
+hipError_t launch_gumbel_noise(uint32_t first, int64_t n, float* out, hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_gumbel_noise, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, first, n, out);
+  return hipGetLastError();
+}
 
 hipError_t launch_sample(const SampleArgs& a, int rows_ub, bool pick, hipStream_t st) {
   if (rows_ub <= 0) return hipSuccess;

@@ -37,6 +37,29 @@ def test_gumbel_bits_bit_exact(rg, seed, t, s, V):
     np.testing.assert_array_equal(got, gumbel_uniform_bits(seed, t, s, V))
 
 
+def test_gumbel_noise_over_every_uniform(rg):
+    """The noise that the sampler adds, for each of the 2^23 uniforms its stream
+    can give, against 64 bits.  A relative error of 2^-23 in the inner logarithm
+    moves the noise by 1.2e-7; the outer one's value reaches 23.5 before the
+    product with ln 2, whose last bit is 1.9e-6: 2e-6 in all, also in the tail
+    near u = 1 that wins a draw, and 1e-7 rms (an ordinary value is below 4)."""
+    import torch
+    from paper_2606_02218_amd import _lib
+    n = 1 << 23
+    out = torch.empty(n, dtype=torch.float32, device="cuda")
+    print("Gumbel noise of 2^23 uniforms", flush=True)
+    assert rg.load_library().rg_gumbel_noise(0, n, out.data_ptr(), _lib._stream_ptr()) == _lib.RG_OK
+    u = (2.0 * np.arange(n) + 1.0) * 2.0 ** -24
+    err = out.cpu().numpy().astype(np.float64) - (-np.log(-np.log(u)) + np.log(np.log(2.0)))
+    print(f"max {np.abs(err).max():.3e}, rms {np.sqrt(np.mean(err * err)):.3e}", flush=True)
+    assert np.abs(err).max() <= 2e-6 and np.sqrt(np.mean(err * err)) <= 1e-7
+    part = torch.empty(1000, dtype=torch.float32, device="cuda")
+    assert rg.load_library().rg_gumbel_noise(n - 1000, 1000, part.data_ptr(), _lib._stream_ptr()) == _lib.RG_OK
+    assert torch.equal(part, out[-1000:])
+    for first, m in ((-1, 4), (0, 0), (n - 3, 4)):
+        assert rg.load_library().rg_gumbel_noise(first, m, out.data_ptr(), None) == _lib.RG_EINVAL
+
+
 def _adv_case(rg, rewards, G, ddof=1):
     import torch
     r = torch.from_numpy(np.asarray(rewards, np.float32)).cuda()
