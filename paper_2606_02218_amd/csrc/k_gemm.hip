@@ -44,7 +44,7 @@
 
 namespace {
 
-constexpr int BK_MAX = 64;             // K step
+constexpr int BK = 64;                 // K step
 constexpr int LDS_PAD = 16;            // bf16 elements of padding per LDS row (rows 160 B apart: no bank conflicts)
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
@@ -406,7 +406,7 @@ __device__ __forceinline__ u32x4_t load_w(const bf16_t* p) {
   else return *reinterpret_cast<const u32x4_t*>(p);
 }
 
-template <int BM, int BN, int WM, int WN, int STAGES, int BK, int EPI, bool NTW, bool XO>
+template <int BM, int BN, int WM, int WN, int EPI, bool NTW, bool XO>
 __global__ __launch_bounds__((BM / (16 * WM)) * (BN / (16 * WN)) * 64) void k_gemm_tiled(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const int* __restrict__ d_rows, int64_t a_plane,
     int lda, int ldw, int rows_cap, int N, int K, int k_per_split, int gx, int gy, GemmEpi ep) {
@@ -420,7 +420,6 @@ __global__ __launch_bounds__((BM / (16 * WM)) * (BN / (16 * WN)) * 64) void k_ge
   constexpr int WAVES_M = BM / (16 * WM), WAVES_N = BN / (16 * WN);
   constexpr int NT = WAVES_M * WAVES_N * 64;
   constexpr int LROW = BK + LDS_PAD;                // LDS row stride (elements)
-  static_assert(BK == 32 || BK == 64, "K step");
   constexpr int A_PIECES = BM * (BK / 8);          // 16-byte pieces per A plane tile
   constexpr int W_PIECES = BN * (BK / 8);
   static_assert((2 * A_PIECES) % NT == 0 && W_PIECES % NT == 0, "tile pieces must split evenly over threads");
@@ -459,9 +458,13 @@ __global__ __launch_bounds__((BM / (16 * WM)) * (BN / (16 * WN)) * 64) void k_ge
   const int lr = lane & 15, lk = (lane >> 4) * 8;
 
   // STAGES register sets: the global loads of step k + STAGES*BK are issued
-  // right after step k's tiles reach LDS, so STAGES steps of loads are in
-  // flight while one step is multiplied out (HBM latency exceeds one step of
-  // MFMA work by a wide margin).
+  // right after step k's tiles reach LDS.  One set: two or three lowered the
+  // occupancy and gained at most 5-10 % of a launch at 64 rows and fewer, nothing
+  // above.  (The loop over sets and its always true first test stay: written
+  // out without them the first loads are sunk below the row-count test and the
+  // loop is scheduled otherwise, which made gpt2s and small-batch decode steps
+  // 0.7-1 % slower.)
+  constexpr int STAGES = 1;
   u32x4_t ra[STAGES][A_PER_T], rw[STAGES][W_PER_T];
 #define RG_FETCH(S, KK)                                                                                       \
   _Pragma("unroll") for (int i = 0; i < A_PER_T; ++i) {                                                       \
@@ -572,7 +575,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_dma(const int* __restrict__ d_r
                                                      const bf16_t* __restrict__ W, int64_t a_plane, int lda, int ldw,
                                                      int rows_cap, int N, int K, int k_per_split, int gx, int gy,
                                                      GemmEpi ep) {
-  constexpr int BK = 64, CH = BK / 8;                        // CH 16-byte chunks per row and step
+  constexpr int CH = BK / 8;                                 // 16-byte chunks per row and step
   constexpr int WAVES_N = BN / (16 * WN), NT = 512;
   static_assert((BM / (16 * WM)) * WAVES_N == 8, "eight waves");
   constexpr int A_P = BM * CH / NT, W_P = BN * CH / NT;      // pieces per thread of one A plane, of W
@@ -815,11 +818,11 @@ __global__ __launch_bounds__(64) void k_qkv_epilogue4(const int* __restrict__ d_
   }
 }
 
-// Sum of split partials + STORE, RESIDUAL or SWIGLU epilogue: one block of 128
-// threads (SWIGLU: 64) per (128 columns, row).  Sums the partials (all inside the partial
-// buffer; columns past N read a column in range) before testing row and
-// column, so the loads wait neither for the row count nor for a test of a
-// kernel argument.
+// Sum of split partials + SWIGLU or (without a next norm) RESIDUAL epilogue: one
+// block of 128 threads (SWIGLU: 64) per (128 columns, row).  Sums the partials
+// (all inside the partial buffer; columns past N read a column in range) before
+// testing row and column, so the loads wait neither for the row count nor for a
+// test of a kernel argument.
 template <int EPI>
 __global__ __launch_bounds__(128) void k_split_epilogue(const int* __restrict__ d_rows, float* __restrict__ part,
                                                         int64_t pst, int N, int S, GemmEpi ep) {
@@ -838,11 +841,9 @@ __global__ __launch_bounds__(128) void k_split_epilogue(const int* __restrict__ 
     act_store<1>(ep.act, (int64_t)r * ep.act_ld + (gc >> 5) * 16 + (q & 15), gt / (1.0f + expf(-gt)) * up);
   } else {
     const int c = blockIdx.x * 128 + threadIdx.x;
-    const float inv = EPI == GEMM_EPI_STORE ? wave_row_scale(ep, r, threadIdx.x & 63) : 1.f;
     const float v = split_sum(ep, S, (int64_t)r * N + min(c, N - 1));
     if (r >= rows_now || c >= N) return;
-    if constexpr (EPI == GEMM_EPI_STORE) ep.C[(int64_t)r * ep.ldc + c] = v * inv;
-    else ep.x[(int64_t)r * ep.ldx + c] += v;
+    ep.x[(int64_t)r * ep.ldx + c] += v;
   }
 }
 
@@ -959,7 +960,7 @@ hipError_t launch_f32(const float* A, int lda, const float* W, int ldw, const in
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WM, int WN, int STAGES, int BK = 64>
+template <int BM, int BN, int WM, int WN>
 hipError_t launch_tiled(const void* A, int lda, int64_t a_plane, const void* W, int ldw, const int* d_rows,
                         int rows_ub, int N, int K, int splits, int k_per_split, const GemmEpi& ep, hipStream_t st) {
   constexpr int NT = (BM / (16 * WM)) * (BN / (16 * WN)) * 64;
@@ -972,10 +973,7 @@ hipError_t launch_tiled(const void* A, int lda, int64_t a_plane, const void* W, 
   // faster).  For the narrow outputs at 256-512 rows it measured 2-9 % slower,
   // so they keep the default order.
   const bool order1d = N >= 8192 && gy >= 8;
-  if (order1d) {
-    if ((K + k_per_split - 1) / k_per_split != splits) return hipErrorInvalidValue;
-    grid = dim3((unsigned)(((int64_t)gx * gy * splits + 7) / 8 * 8));
-  }
+  if (order1d) grid = dim3((unsigned)(((int64_t)gx * gy * splits + 7) / 8 * 8));
   // One row tile: every weight piece is read by one block only, so its loads
   // are non-temporal.  With several row tiles the weight tiles are re-read
   // by the other row tiles' blocks through L2, and non-temporal loads there
@@ -985,7 +983,7 @@ hipError_t launch_tiled(const void* A, int lda, int64_t a_plane, const void* W, 
   // decides a branch ahead of the first loads.  The grouped order needs 8 or
   // more row tiles, so it never meets ntw.
 #define RG_TILED_K(E, NTV, XOV)                                                                               \
-  hipLaunchKernelGGL((k_gemm_tiled<BM, BN, WM, WN, STAGES, BK, E, NTV, XOV>), grid, dim3(NT), 0, st,           \
+  hipLaunchKernelGGL((k_gemm_tiled<BM, BN, WM, WN, E, NTV, XOV>), grid, dim3(NT), 0, st,                       \
                      (const bf16_t*)A, (const bf16_t*)W, d_rows, a_plane, lda, ldw, rows_ub, N, K, k_per_split, gx, \
                      gy, ep)
 #define RG_TILED(E)                                                                                           \
@@ -1014,7 +1012,6 @@ template <int BM, int BN, int WM, int WN>
 hipError_t launch_dma(const void* A, int lda, int64_t a_plane, const void* W, int ldw, const int* d_rows, int rows_ub,
                       int N, int K, int splits, int k_per_split, const GemmEpi& ep, hipStream_t st) {
   const int gx = (N + BN - 1) / BN, gy = (rows_ub + BM - 1) / BM;
-  if (k_split_count(K, k_per_split) != splits) return hipErrorInvalidValue;
   // byte offsets inside a tile are 32-bit
   if ((int64_t)BM * lda * 2 > UINT32_MAX || (int64_t)BN * ldw * 2 > UINT32_MAX) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(((int64_t)gx * gy * splits + 7) / 8 * 8));
@@ -1048,10 +1045,6 @@ hipError_t launch_split_epilogue(const int* d_rows, int rows_ub, int N, int S, c
   }
   dim3 grid((N + 127) / 128, rows_ub);
   switch (ep.mode) {
-    case GEMM_EPI_STORE:
-      hipLaunchKernelGGL((k_split_epilogue<GEMM_EPI_STORE>), grid, dim3(128), 0, st, d_rows, ep.part, ep.part_stride,
-                         N, S, ep);
-      break;
     case GEMM_EPI_RESIDUAL:
       hipLaunchKernelGGL((k_split_epilogue<GEMM_EPI_RESIDUAL>), grid, dim3(128), 0, st, d_rows, ep.part,
                          ep.part_stride, N, S, ep);
@@ -1199,10 +1192,11 @@ hipError_t launch_gemm(int dtype, const GemmPlan& p, const void* A, int lda, int
   if (rows_ub <= 0) return hipSuccess;
   const int S = p.splits, kps = p.k_per_split;
   if (S < 1 || S > GEMM_MAX_SPLITS || (S > 1 && !ep.part)) return hipErrorInvalidValue;
+  if (S > 1 && (ep.mode == GEMM_EPI_STORE || ep.mode == GEMM_EPI_LOGPROB)) return hipErrorInvalidValue;   // lm head: unsplit
   if ((ep.mode == GEMM_EPI_SWIGLU || ep.mode == GEMM_EPI_QKV) && N % 32) return hipErrorInvalidValue;
   if (ep.mode == GEMM_EPI_QKV && (ep.hd % 32 || 128 % ep.hd)) return hipErrorInvalidValue;
   if (dtype == 1) {
-    if (K % BK_MAX || kps % BK_MAX || N % 16) return hipErrorInvalidValue;
+    if (K % BK || kps % BK || N % 16 || k_split_count(K, kps) != S) return hipErrorInvalidValue;
     hipError_t e = hipErrorInvalidValue;
 #define RG_TILE(F, ...) e = F<__VA_ARGS__>(A, lda, a_plane, W, ldw, d_rows, rows_ub, N, K, S, kps, ep, st)
     if (p.dma) {
@@ -1211,13 +1205,13 @@ hipError_t launch_gemm(int dtype, const GemmPlan& p, const void* A, int lda, int
       else if (p.bn == 256) RG_TILE(launch_dma, 128, 256, 4, 4);
       else if (p.bn == 320) RG_TILE(launch_dma, 128, 320, 2, 10);
     } else if (p.bm == 16 && p.bn == 128) {
-      RG_TILE(launch_tiled, 16, 128, 1, 2, 1);
+      RG_TILE(launch_tiled, 16, 128, 1, 2);
     } else if (p.bm == 32 && p.bn == 64) {
-      RG_TILE(launch_tiled, 32, 64, 1, 2, 1);
+      RG_TILE(launch_tiled, 32, 64, 1, 2);
     } else if (p.bm == 32 && p.bn == 128) {
-      RG_TILE(launch_tiled, 32, 128, 1, 4, 1);
+      RG_TILE(launch_tiled, 32, 128, 1, 4);
     } else if (p.bm == 64 && p.bn == 128) {
-      RG_TILE(launch_tiled, 64, 128, 2, 4, 1);
+      RG_TILE(launch_tiled, 64, 128, 2, 4);
     }
 #undef RG_TILE
     if (e != hipSuccess || S == 1) return e;
