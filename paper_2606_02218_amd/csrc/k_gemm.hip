@@ -406,10 +406,10 @@ __device__ __forceinline__ u32x4_t load_w(const bf16_t* p) {
   else return *reinterpret_cast<const u32x4_t*>(p);
 }
 
-template <int BM, int BN, int WM, int WN, int EPI, bool NTW, bool XO>
+template <int BM, int BN, int WM, int WN, int EPI, bool NTW>
 __global__ __launch_bounds__((BM / (16 * WM)) * (BN / (16 * WN)) * 64) void k_gemm_tiled(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const int* __restrict__ d_rows, int64_t a_plane,
-    int lda, int ldw, int rows_cap, int N, int K, int k_per_split, int gx, int gy, GemmEpi ep) {
+    int lda, int ldw, int rows_cap, int N, int K, int k_per_split, GemmEpi ep) {
   // The arguments the first loads need come first (14 dwords, which the
   // build preloads into scalar registers at dispatch).  The row count is
   // read first but waited for only after the first K step's loads are
@@ -429,26 +429,7 @@ __global__ __launch_bounds__((BM / (16 * WM)) * (BN / (16 * WN)) * 64) void k_ge
   __shared__ __attribute__((aligned(16))) bf16_t sA[2][BM * LROW];
   __shared__ __attribute__((aligned(16))) bf16_t sW[BN * LROW];
 
-  int tx = blockIdx.x, ty = blockIdx.y, tz = blockIdx.z;
-  if constexpr (XO) {
-    // A 1-D grid of a multiple of 8 blocks, dealt to the 8 XCDs in turn:
-    // XCD x = b % 8 takes the contiguous tile range [x*per, (x+1)*per)
-    // (split-major), walked in groups of TILE_GROUP row tiles.  Within a
-    // group the row tiles of one column tile are consecutive, so the blocks
-    // that an XCD runs at once share A rows and W columns in its L2.
-    constexpr int TILE_GROUP = 4;
-    const int per = gridDim.x / 8;
-    int w = (blockIdx.x % 8) * per + blockIdx.x / 8;
-    if (w >= gx * gy * (int)k_split_count(K, k_per_split)) return;
-    tz = w / (gx * gy);
-    w -= tz * gx * gy;
-    const int gsz = TILE_GROUP * gx;                    // tiles per full group
-    const int g = w / gsz, r0 = g * TILE_GROUP;
-    const int rows_g = min(TILE_GROUP, gy - r0);       // the last group may be short
-    const int wi = w - g * gsz;
-    ty = r0 + wi % rows_g;
-    tx = wi / rows_g;
-  }
+  const int tx = blockIdx.x, ty = blockIdx.y, tz = blockIdx.z;
   const int m0 = ty * BM;   // < rows_cap: the grid has ceil(rows_cap / BM) row tiles
   const int n0 = tx * BN;
   const int kb0 = tz * k_per_split;
@@ -585,7 +566,11 @@ __global__ __launch_bounds__(512, 2) void k_gemm_dma(const int* __restrict__ d_r
   __shared__ __attribute__((aligned(128))) bf16_t sm[2 * STAGE];
   const int rows_now = *d_rows;
 
-  // the XCD-aware grouped tile order of k_gemm_tiled, groups of 4 row tiles
+  // A 1-D grid of a multiple of 8 blocks, dealt to the 8 XCDs in turn: XCD x =
+  // b % 8 takes the contiguous tile range [x*per, (x+1)*per) (split-major),
+  // walked in groups of TILE_GROUP row tiles.  Within a group the row tiles of one
+  // column tile are consecutive, so the blocks that an XCD runs at once share A
+  // rows and W columns in its L2.
   constexpr int TILE_GROUP = 4;
   const int per = gridDim.x / 8;
   int w = (blockIdx.x % 8) * per + blockIdx.x / 8;
@@ -965,32 +950,19 @@ hipError_t launch_tiled(const void* A, int lda, int64_t a_plane, const void* W, 
                         int rows_ub, int N, int K, int splits, int k_per_split, const GemmEpi& ep, hipStream_t st) {
   constexpr int NT = (BM / (16 * WM)) * (BN / (16 * WN)) * 64;
   const int gx = (N + BN - 1) / BN, gy = (rows_ub + BM - 1) / BM;
-  dim3 grid(gx, gy, splits);
-  // The XCD-aware grouped tile order for wide outputs (gate/up) read by 8 or
-  // more row tiles: there the default order fetches each weight tile about 7
-  // times per launch from beyond L2 (gate/up at 512 rows on 64-row tiles: 418
-  // MB of L2 misses for 58 MB of operands, against 120 MB in this order, 7 %
-  // faster).  For the narrow outputs at 256-512 rows it measured 2-9 % slower,
-  // so they keep the default order.
-  const bool order1d = N >= 8192 && gy >= 8;
-  if (order1d) grid = dim3((unsigned)(((int64_t)gx * gy * splits + 7) / 8 * 8));
+  const dim3 grid(gx, gy, splits);
   // One row tile: every weight piece is read by one block only, so its loads
   // are non-temporal.  With several row tiles the weight tiles are re-read
   // by the other row tiles' blocks through L2, and non-temporal loads there
   // measured 12 % slower over the 1.5B group step.
   const bool ntw = gy == 1;
-  // The tile order is a template parameter, so that no kernel argument
-  // decides a branch ahead of the first loads.  The grouped order needs 8 or
-  // more row tiles, so it never meets ntw.
-#define RG_TILED_K(E, NTV, XOV)                                                                               \
-  hipLaunchKernelGGL((k_gemm_tiled<BM, BN, WM, WN, E, NTV, XOV>), grid, dim3(NT), 0, st,                       \
-                     (const bf16_t*)A, (const bf16_t*)W, d_rows, a_plane, lda, ldw, rows_ub, N, K, k_per_split, gx, \
-                     gy, ep)
+#define RG_TILED_K(E, NTV)                                                                                    \
+  hipLaunchKernelGGL((k_gemm_tiled<BM, BN, WM, WN, E, NTV>), grid, dim3(NT), 0, st, (const bf16_t*)A,          \
+                     (const bf16_t*)W, d_rows, a_plane, lda, ldw, rows_ub, N, K, k_per_split, ep)
 #define RG_TILED(E)                                                                                           \
   do {                                                                                                        \
-    if (order1d) RG_TILED_K(E, false, true);                                                                  \
-    else if (ntw) RG_TILED_K(E, true, false);                                                                 \
-    else RG_TILED_K(E, false, false);                                                                         \
+    if (ntw) RG_TILED_K(E, true);                                                                             \
+    else RG_TILED_K(E, false);                                                                                \
   } while (0)
   if (splits > 1) {
     RG_TILED(GEMM_EPI_PARTIAL);

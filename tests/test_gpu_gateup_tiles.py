@@ -52,3 +52,31 @@ def test_gateup_64_column_tiles_teacher_forced():
     print(f"worst teacher-forced logit gap {worst:.2e}", flush=True)
     assert worst <= LOGIT_TOL
     pol.close()
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("d,rows", [(256, 500), (128, 1000), (512, 449)])
+def test_wide_gateup_on_staged_tiles_by_many_rows(d, rows):
+    """Prompt rows whose gate/up product (8192 columns) has too little work for
+    the direct-to-LDS tiles and 8 or more row tiles: the recompute's scores of
+    the prompts' continuations against the oracle's (2e-2, as everywhere)."""
+    import torch
+    from oracle.grpo import teacher_forced_logprobs
+    assert torch.cuda.is_available()
+    shape = ModelShape(1, d, 4, 2, 64, 4096, 528, 1e4, dtype="bf16")
+    w = make_weights(shape, 7)
+    rng = np.random.default_rng(d + rows)
+    plens = np.array([rows // 3, rows // 3, rows - 2 * (rows // 3)])
+    prompts = [rng.integers(0, shape.vocab - 1, size=int(n)).astype(np.int32) for n in plens]
+    lengths = np.array([3, 1, 2], np.int32)
+    tok = rng.integers(0, shape.vocab - 1, size=(3, 3)).astype(np.int32)
+    print(f"wide gate/up on staged tiles: d {d}, {rows} prompt rows", flush=True)
+    pol = make_policy(shape, w, max_seqs=3, max_prompts=3, max_prompt_tokens=rows, max_context=int(plens.max()) + 3)
+    got = pol.recompute_logprobs(prompts_to_device(prompts), [1] * 3, torch.from_numpy(tok).cuda(),
+                                 torch.from_numpy(lengths).cuda()).cpu().numpy()
+    want = teacher_forced_logprobs(oracle_for(shape, w), prompts, [1] * 3, tok, lengths)
+    valid = np.arange(3)[None, :] < lengths[:, None]
+    gap = float(np.max(np.abs(got[valid] - want[valid])))
+    print(f"gap {gap:.2e}", flush=True)
+    assert np.isfinite(got).all() and gap <= 2 * LOGIT_TOL
+    pol.close()
