@@ -57,10 +57,10 @@ def test_dma_tiles_match_oracle(si, rows):
 @pytest.mark.timeout(300)
 @pytest.mark.parametrize("dtype,hd", [("bf16", 64), ("f32", 32)])
 def test_recompute_across_chunks(dtype, hd):
-    """More completion positions than a recompute chunk holds (4096 rows): a
-    sequence split over the boundary attends to its own earlier positions from
+    """More completion positions than a recompute chunk holds (at most 4096 rows):
+    a sequence split over the boundary attends to its own earlier positions from
     the first chunk and scores like any other.  The prompts alone (60 tokens)
-    no longer bound the chunk.  Tolerance as above; fp32 models 5e-5."""
+    do not bound the chunk.  Tolerance as above; fp32 models 5e-5."""
     import torch
     assert torch.cuda.is_available()
     shape = ModelShape(2, 64, 2, 1, hd, 128, 144, 1e4, dtype=dtype)
@@ -83,4 +83,35 @@ def test_recompute_across_chunks(dtype, hd):
     gap = float(np.max(np.abs(got[valid] - want[valid])))
     print(f"gap {gap:.2e}", flush=True)
     assert np.isfinite(got).all() and gap <= (5e-5 if dtype == "f32" else 4e-3)
+    pol.close()
+
+
+@pytest.mark.timeout(300)
+def test_lm_head_in_passes():
+    """A chunk of more rows (5003: as many as prompt tokens) than the lm head
+    scores in one pass (4096 at 16 tokens of vocabulary): the rows of the second
+    pass take their own norm factors, targets and outputs.  Tolerance as above."""
+    import torch
+    assert torch.cuda.is_available()
+    shape = ModelShape(1, 64, 1, 1, 64, 64, 16, 1e4, rms_eps=1e-6, dtype="bf16")
+    w = make_weights(shape, 12)
+    rng = np.random.default_rng(13)
+    w.final_norm[:] = rng.uniform(1.0, 5.0, shape.d_model)   # values apart, so that another row's would show
+    P = 25
+    plens = np.full(P, 200)
+    plens[-1] = 203
+    prompts = [rng.integers(0, shape.vocab - 1, size=int(n)).astype(np.int32) for n in plens]
+    lengths = (plens + 1).astype(np.int32)
+    max_new = int(lengths.max())
+    tok = rng.integers(0, shape.vocab - 1, size=(P, max_new)).astype(np.int32)
+    print(f"lm head in passes: {plens.sum()} rows", flush=True)
+    pol = make_policy(shape, w, max_seqs=P, max_prompts=P, max_prompt_tokens=int(plens.sum()), max_context=max_new + 203)
+    got = pol.recompute_logprobs(prompts_to_device(prompts), [1] * P, torch.from_numpy(tok).cuda(),
+                                 torch.from_numpy(lengths).cuda(), temperature=0.7, profile=True).cpu().numpy()
+    assert pol.kernel_times(1)["gemm_lm"][1] == 2            # passes over the one chunk
+    want = teacher_forced_logprobs(oracle_for(shape, w), prompts, [1] * P, tok, lengths, temperature=0.7)
+    valid = np.arange(max_new)[None, :] < lengths[:, None]
+    gap, spread = float(np.max(np.abs(got[valid] - want[valid]))), float(want[valid].std())
+    print(f"gap {gap:.2e}, spread of the values {spread:.2f}", flush=True)
+    assert np.isfinite(got).all() and gap <= 4e-3 < spread / 50
     pol.close()

@@ -3,9 +3,9 @@
 * recompute_logprobs against the oracle's teacher-forced log-probabilities:
   within 1e-4 for the fp32 tiny model, within 2e-2 (twice the logit
   tolerance) for bf16 decoders -- a GQA decoder with 6 query heads per kv head
-  and head_dim 128, and a gpt2s-shaped one with ragged prompts.  Limits are
-  chosen so the completion rows run in many chunks and the lm head in many
-  slices, each with a ragged tail.
+  and head_dim 128, and a gpt2s-shaped one with ragged prompts.  Completion
+  rows of these cases fit one chunk; test_recompute_in_three_chunks runs the
+  GQA heads over three, and test_gpu_dma_tiles.py the lm head in passes.
 * the recompute reproduces the library's own rollout logprobs (same
   temperature) on a free-running rollout, also at the 1.5B decoder shape,
   and private prompt pages give bit-identical results.
@@ -77,7 +77,6 @@ def test_recompute_tiny_fp32(torch):
     G = [4, 3, 2]
     L = rng.integers(1, 33, size=9).astype(np.int32)
     L[0], L[-1] = 1, 32
-    # max_prompt_tokens 48, max_seqs 9: chunks of 48 rows, lm head slices of 9 rows
     _, _, _, err = _recompute_case(torch, wl.shape, w, prompts, G, 32, L, 7, T=0.8, tol=1e-4)
     assert err < 1e-4
 
@@ -89,14 +88,42 @@ def test_recompute_gqa_bf16_many_chunks(torch):
     G = [6, 1, 3]
     L = rng.integers(1, 121, size=10).astype(np.int32)
     L[0], L[4] = 1, 120
-    # m_act = 63 rows per chunk (about 12 chunks), slices of 10 lm-head rows
     _recompute_case(torch, GQA, w, prompts, G, 120, L, 11)
 
 
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("row_tiles", [True, False])
+def test_recompute_in_three_chunks(torch, row_tiles):
+    """More completion rows than two chunks hold (at most 4096 each) at head_dim
+    128 with 6 query heads per kv head: sequences cut by both boundaries attend
+    to their positions of earlier chunks, by row tiles and row by row."""
+    shape = ModelShape(2, 64, 6, 1, 128, 64, 144, 1e6, dtype="bf16")
+    w = make_weights(shape, 9)
+    rng = np.random.default_rng(31)
+    G, max_new = [20, 17, 24], 170
+    N = sum(G)
+    prompts = [rng.integers(0, shape.vocab - 1, size=n).astype(np.int32) for n in (19, 33, 8)]
+    L = rng.integers(140, max_new + 1, size=N).astype(np.int32)
+    rows = int(L.sum()) - N
+    assert rows > 2 * 4096 and not {4096, 8192} & set(np.cumsum(L - 1).tolist())
+    tok = rng.integers(0, shape.vocab - 1, size=(N, max_new)).astype(np.int32)
+    print(f"recompute of {rows} rows, row tiles {row_tiles}", flush=True)
+    pol = make_policy(shape, w, N, len(G), 60, 33 + max_new)
+    got = _np(pol.recompute_logprobs(prompts_to_device(prompts), G, torch.from_numpy(tok).cuda(),
+                                     torch.from_numpy(L).cuda(), row_tiles=row_tiles, profile=True))
+    assert pol.kernel_times(1)["gemm_lm"][1] >= 3             # at least one launch a chunk
+    want = teacher_forced_logprobs(oracle_for(shape, w), prompts, G, tok, L)
+    valid = np.arange(max_new)[None, :] < L[:, None]
+    err = float(np.max(np.abs(got[valid] - want[valid])))
+    print(f"gap {err:.2e}", flush=True)
+    assert np.isfinite(got).all() and np.all(got[~valid] == 0) and err <= 2 * LOGIT_TOL
+    pol.close()
+
+
 def test_recompute_row_tiles_match_row_pass(torch):
-    """The row-tile attention (32 positions of a sequence per staged K/V
+    """The row-tile attention (21 positions of a sequence per staged K/V
     block at 6 query heads per kv head) against the per-row pass: both within the oracle tolerance and
-    within 2e-3 of each other; a long completion spans many tiles and chunks,
+    within 2e-3 of each other; a long completion spans many tiles,
     sequences of length 1 and 2 give empty and one-row tiles."""
     w = make_weights(GQA, 6)
     rng = np.random.default_rng(25)

@@ -1,7 +1,7 @@
 """grpo_surrogate_scratch (per-sequence records in the caller's memory) equals
-grpo_surrogate bit for bit, refuses a missing or misaligned scratch on the
-host, and the binding gives the same result on the current stream (scratch from
-torch's allocator), and on a given stream."""
+grpo_surrogate bit for bit inside 16 N bytes, refuses a missing or misaligned
+scratch on the host, and the binding gives the same result on the current stream
+(scratch from torch's allocator), and on a given stream."""
 import ctypes as C
 
 import numpy as np
@@ -33,6 +33,35 @@ def test_scratch_surrogate_equals_the_allocating_one(N, T, mode):
     torch.cuda.synchronize()
     w = want.cpu().numpy()
     assert np.array_equal(got.cpu().numpy(), w) and np.array_equal(other.cpu().numpy(), w)
+
+
+@pytest.mark.parametrize("N,T,mode", [(1, 1, "seq"), (129, 300, "token"), (1000, 17, "seq")])
+def test_scratch_surrogate_stays_in_its_scratch(N, T, mode):
+    """The entry point itself, on 16 N bytes between guard words: equal to
+    grpo_surrogate bit for bit, the records written, nothing beside them."""
+    import torch
+    import paper_2606_02218_amd as rg
+    from paper_2606_02218_amd import _lib
+    lib = rg.load_library()
+    rng = np.random.default_rng(7 * N + T)
+    L = rng.integers(1, T + 1, size=N).astype(np.int32)
+    old = rng.normal(-3.0, 1.0, (N, T)).astype(np.float32)
+    new = (old + rng.normal(0, 0.2, (N, T))).astype(np.float32)
+    d = [torch.from_numpy(a).cuda() for a in (new, old, rng.normal(size=N).astype(np.float32), L)]
+    G = torch.tensor([N], dtype=torch.int32, device="cuda")
+    print(f"surrogate scratch with guards: N {N}, T {T}, {mode}", flush=True)
+    out = [torch.empty(4, dtype=torch.float64, device="cuda") for _ in range(2)]
+    guard, word = 64, 0x5A5A5A5A5A5A5A5A
+    mem = torch.full((guard + 2 * N + guard,), word, dtype=torch.int64, device="cuda")
+    args = [t.data_ptr() for t in d] + [G.data_ptr(), 1, N, T, 0, 0.2, 0.28, _lib.LOSS_MODES[mode]]
+    assert lib.grpo_surrogate(*args, out[0].data_ptr(), _lib._stream_ptr()) == _lib.RG_OK
+    rc = lib.grpo_surrogate_scratch(*args, out[1].data_ptr(), mem.data_ptr() + 8 * guard, _lib._stream_ptr())
+    assert rc == _lib.RG_OK
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1])
+    m = mem.cpu().numpy()
+    assert (m[:guard] == word).all() and (m[-guard:] == word).all()
+    assert (m[guard:-guard].reshape(N, 2) != word).all()
 
 
 def test_scratch_surrogate_refuses_bad_scratch():
