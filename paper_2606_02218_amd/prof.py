@@ -121,10 +121,11 @@ def steps_table(d: str, full: bool = False) -> str:
 def phases_table(d: str, hist_path: str) -> str:
     """Decode attention of one rollout (the trace's only rollout) by phase:
     steps grouped by their active-row count.  HIST.npz is the step history
-    that `bench.py --history-out` writes.  The first n_layers per-row
-    attention launches attend the prompt rows; after them decode step t owns
-    launches (t-1)*n_layers .. t*n_layers-1, and a merge launch belongs to the
-    attention launch before it.  Algorithmic bytes count each active group's
+    that `bench.py --history-out` writes.  Per-row attention launches before
+    the first decode-row set-up attend prompt rows (none where the prefill
+    takes row tiles; n_layers in a trace without that launch); after them
+    decode step t owns launches (t-1)*n_layers .. t*n_layers-1, and a merge
+    launch belongs to the attention launch before it.  Algorithmic bytes count each active group's
     prompt once; wave-read bytes count it once per row (what the per-row
     pass's waves read, the repeats served by L2)."""
     import numpy as np
@@ -132,14 +133,17 @@ def phases_table(d: str, hist_path: str) -> str:
     A, Gr, C = h["active"], h["groups"], h["ctx"]
     L = int(h["n_layers"])
     kvb, qb = float(h["kv_bytes_per_token_layer"]), float(h["q_bytes_per_row"])
-    ev = []
+    ev, first_step = [], None
     for f in _find(d, "kernel_trace.csv"):
         for r in csv.DictReader(open(f)):
             n = _kname(r)
+            s0 = int(r["Start_Timestamp"])
             if n in ("k_attention_mfma", "k_attn_merge"):
-                s0 = int(r["Start_Timestamp"])
                 ev.append((s0, int(r["End_Timestamp"]) - s0, n == "k_attn_merge"))
+            elif n == "k_decode_rows" and (first_step is None or s0 < first_step):
+                first_step = s0
     ev.sort()
+    pre = L if first_step is None else sum(s0 < first_step and not is_merge for s0, _, is_merge in ev)
     att = []
     for _, dt, is_merge in ev:
         if is_merge:
@@ -150,7 +154,7 @@ def phases_table(d: str, hist_path: str) -> str:
     bins = [(257, 1 << 30), (129, 256), (65, 128), (33, 64), (17, 32), (1, 16)]
     acc = {b: [0, 0.0, 0.0, 0.0, 0.0] for b in bins}
     used = 0
-    for i, (dt, dm) in enumerate(att[L:]):
+    for i, (dt, dm) in enumerate(att[pre:]):
         t = 1 + i // L
         if t >= len(A) or int(A[t]) == 0:
             break
@@ -160,7 +164,7 @@ def phases_table(d: str, hist_path: str) -> str:
         a = acc[next(b for b in bins if b[0] <= M <= b[1])]
         a[0] += 1; a[1] += dt; a[2] += dm; a[3] += alg; a[4] += wave
         used += 1
-    out = [f"decode attention launches {len(att) - L} (after {L} prompt-row launches), {used} matched to steps",
+    out = [f"decode attention launches {len(att) - pre} (after {pre} prompt-row launches), {used} matched to steps",
            f"{'rows':>9s} {'launches':>9s} {'attn_ms':>8s} {'merge_ms':>9s} {'us/launch':>10s} {'alg_MB':>8s} "
            f"{'alg_TB/s':>9s} {'wave_TB/s':>10s}"]
     ta = tm = 0.0

@@ -56,6 +56,29 @@ def test_phases_table(tmp_path):
     assert out[-1] == "total: attention 28.0 ms, merge 2.0 ms"
 
 
+def test_phases_table_after_a_row_tile_prefill(tmp_path):
+    """Prompt rows attended by row tiles leave no per-row launch ahead of step 1:
+    the first decode-row set-up marks where the steps begin."""
+    L, ms = 2, 1000000
+    ns = "void (anonymous namespace)::"
+    ev, t = [], 1000
+    for _ in range(L):
+        ev.append((ns + "k_attention_tile<128>(x)", t, 5 * ms)); t += 10 * ms
+    for rows, dur in ((300, 10), (20, 4)):
+        ev.append((ns + "k_decode_rows<unsigned short, 1>(x)", t, 50)); t += 100
+        for _ in range(L):
+            ev.append((ns + "k_attention_mfma<128, 2, 1>(x)", t, dur * ms)); t += 20 * ms
+    os.makedirs(tmp_path / "tr")
+    _trace(tmp_path / "tr" / "run_kernel_trace.csv", ev)
+    np.savez(tmp_path / "h.npz", active=np.array([300, 300, 20, 0]), groups=np.array([30, 30, 4, 0]),
+             ctx=np.array([15000, 15000, 1000, 0]), n_layers=L, kv_bytes_per_token_layer=1e7, q_bytes_per_row=1e6)
+    out = phases_table(str(tmp_path / "tr"), str(tmp_path / "h.npz")).splitlines()
+    assert out[0].startswith(f"decode attention launches {2 * L} (after 0 prompt-row launches), {2 * L} matched")
+    big = next(l for l in out if l.lstrip().startswith("257+")).split()
+    small = next(l for l in out if l.lstrip().startswith("17-32")).split()
+    assert int(big[1]) == L and float(big[2]) == 20.0 and int(small[1]) == L and float(small[2]) == 8.0
+
+
 def _counters(path, dispatches):
     cols = ["Dispatch_Id", "Grid_Size", "Kernel_Name", "Counter_Name", "Counter_Value", "Start_Timestamp"]
     with open(path, "w", newline="") as f:
